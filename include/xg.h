@@ -21,6 +21,9 @@
  *     array of xg_generate_batch_static, reserved when the code loads); each
  *     generating call only enqueues kernels on `stream` (a hipStream_t passed
  *     as void*; NULL is the null stream) and returns.
+ *   - Until a call has run, its output region may hold intermediate values
+ *     (launches of few streams keep the start states of their rows' parts
+ *     there); nothing outside the region is written.
  *   - Invalid arguments are rejected synchronously with a negative status;
  *     then nothing is enqueued and no state changes.  A launch failure
  *     reported by the HIP runtime right after the launch gives XG_EHIP.

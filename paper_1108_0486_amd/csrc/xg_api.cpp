@@ -58,6 +58,7 @@ xg_status make_ctx(xg_ctx **out, void *d_state, size_t state_bytes, uint64_t num
   std::memcpy(c->arch, arch, sizeof arch);
   c->plain = xg::kDefaultPlain;
   c->family = family;
+  c->split_table = xg::split_table(family, dev);
   c->d_batch = nullptr;
   *out = c;
   return XG_OK;
@@ -127,6 +128,18 @@ xg::Shape plain_shape(const xg_ctx *ctx, uint64_t count, xg::Kind kind, bool fil
   return s;
 }
 
+// The parts of a plain launch (xg_split.h), none unless the launch shape is
+// automatic.  A row of 2^15 words takes one wavefront 17 us; jumping to the
+// parts' starts and running them takes 15 us and then grows hardly at all
+// (2^20 words of one stream: 544 us on one wavefront, 15.8 us in 256 parts;
+// 24 streams of 100 003: 63 and 25 us).  With more than half the chip's SIMDs
+// at work already a second wavefront on some of them gains too little.
+xg::Split split_for(const xg_ctx *ctx, xg::Kind kind, uint64_t count, uint64_t n) {
+  if (!ctx->split_table || ctx->plain.waves_per_block || ctx->plain.unroll || kind == xg::kMoments) return {};
+  const uint64_t slots = 4 * (uint64_t)(ctx->num_cus > 0 ? ctx->num_cus : 1);
+  return xg::plan_split(count, n, slots, 1ull << 15);
+}
+
 // u32 / f32 (and u64 / f64) of the further members, both layouts.
 xg_status family_words(xg_ctx *ctx, xg::Kind kind, bool fill_layout, uint64_t first, uint64_t count, uint64_t n,
                        void *out, void *stream) {
@@ -157,6 +170,10 @@ xg_status plain(xg_ctx *ctx, xg::Kind kind, uint64_t first, uint64_t count, uint
   const uint64_t per_stream = kind == xg::kMoments ? 2 : n;
   xg_status st = check_range(ctx, first, count, n, out, per_stream);
   if (st != XG_OK || n == 0) return st;
+  const xg::Split sp = split_for(ctx, kind, count, n);
+  if (sp.parts)
+    return xg::launch_split(kind, false, sp, ctx->d_state, first, count, n, ctx->split_table, out, ctx->num_cus,
+                            static_cast<hipStream_t>(stream)) == hipSuccess ? XG_OK : XG_EHIP;
   const hipError_t e = xg::launch_generate(kind, plain_shape(ctx, count, kind, false), ctx->d_state, first, count,
                                            n, out, ctx->num_cus, static_cast<hipStream_t>(stream));
   return e == hipSuccess ? XG_OK : XG_EHIP;
@@ -168,6 +185,10 @@ xg_status fill(xg_ctx *ctx, xg::Kind kind, uint64_t first, uint64_t count, uint6
   if (ctx && !paper_member(ctx)) return XG_ENOTSUP;
   xg_status st = check_range(ctx, first, count, n, out, n);
   if (st != XG_OK || n == 0) return st;
+  const xg::Split sp = split_for(ctx, kind, count, n);
+  if (sp.parts)
+    return xg::launch_split(kind, true, sp, ctx->d_state, first, count, n, ctx->split_table, out, ctx->num_cus,
+                            static_cast<hipStream_t>(stream)) == hipSuccess ? XG_OK : XG_EHIP;
   const hipError_t e = xg::launch_fill(kind, plain_shape(ctx, count, kind, true), ctx->d_state, first, count, n,
                                        static_cast<uint32_t *>(out), static_cast<hipStream_t>(stream));
   return e == hipSuccess ? XG_OK : XG_EHIP;

@@ -8,6 +8,7 @@
 #include "xg.h"
 #include "xg_host.h"
 #include "xg_plan_dev.h"
+#include "xg_split.h"
 
 namespace xg {
 
@@ -63,6 +64,13 @@ hipError_t launch_generate(Kind kind, const Shape &shape, uint32_t *state, uint6
 // Bulk-fill layout of xg_fill_u32 / xg_fill_f32 (kind kU32 or kF32).
 hipError_t launch_fill(Kind kind, const Shape &shape, uint32_t *state, uint64_t first, uint64_t count,
                        uint64_t n, uint32_t *out, hipStream_t stream);
+
+// Split launches (xg_split.h).  split_table: the member's polynomials in the
+// memory of device dev (current); nullptr when they cannot be found.
+// launch_split: kind kU32, kF32 (either layout) or kNormal, sp.parts > 1.
+const uint64_t *split_table(uint32_t family, int dev);
+hipError_t launch_split(Kind kind, bool fill, const Split &sp, uint32_t *state, uint64_t first, uint64_t count,
+                        uint64_t n, const uint64_t *table, void *out, int num_cus, hipStream_t stream);
 
 hipError_t launch_box_muller(const uint32_t *words, uint64_t pairs, float *out, hipStream_t stream);
 
@@ -171,6 +179,7 @@ struct xg_ctx {
   char arch[32];    // device architecture name without feature suffixes
   xg::Shape plain;
   uint32_t family;  // XG_FAMILY_*
+  const uint64_t *split_table;  // the member's polynomials for split launches, or nullptr
   // Scratch of the one-call batch (xg_set_batch_scratch); d_batch == nullptr: none.
   void *d_batch;
   xg::PlanLayout batch_layout;

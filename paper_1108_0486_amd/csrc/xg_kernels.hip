@@ -319,30 +319,39 @@ __device__ __forceinline__ void serve_words(uint32_t *st, uint64_t n, uint32_t *
 // packed, at out[64 (n / 64) count + k rem ..].  The values are those of the
 // stream-major layout; only their places differ.
 // ---------------------------------------------------------------------------
-template <uint32_t KIND, int UNROLL>
-__device__ __forceinline__ void serve_words_fill(uint32_t *__restrict__ st, uint64_t n, uint64_t k,
-                                                 uint64_t count, uint32_t *__restrict__ out) {
-  WordStream s = open_stream(st);
+template <uint32_t KIND, int UNROLL, bool NT = true>
+__device__ __forceinline__ void serve_chunks(const StreamState &s0, uint64_t n, uint32_t *o, uint64_t stride,
+                                             uint32_t *tail, uint32_t *dst) {
+  WordStream s = open_from(s0);
   const uint64_t nfull = n >> 6;
   const uint32_t rem = (uint32_t)(n & 63u);
-  const uint64_t stride = count * 64;
-  uint32_t *o = out + k * 64 + s.lane;
   const uint64_t nouter = nfull / UNROLL;
   for (uint64_t it = 0; it != nouter; ++it) {
     if constexpr (UNROLL == 1) {
-      emit_word<KIND>(o, next_chunk(s));
+      emit_word<KIND, false, NT>(o, next_chunk(s));
     } else {
 #pragma unroll
-      for (int u = 0; u < UNROLL; ++u) emit_word<KIND>(o + u * stride, next_chunk(s));
+      for (int u = 0; u < UNROLL; ++u) emit_word<KIND, false, NT>(o + u * stride, next_chunk(s));
     }
     o += UNROLL * stride;
   }
   const uint32_t nleft = (uint32_t)(nfull % UNROLL);
   for (uint32_t c = 0; c != nleft; ++c) {
-    emit_word<KIND>(o, next_chunk(s));
+    emit_word<KIND, false, NT>(o, next_chunk(s));
     o += stride;
   }
-  close_stream<KIND>(st, s, n, rem, out + nfull * stride + k * rem + s.lane);
+  close_stream<KIND, NT>(dst, s, n, rem, tail);
+}
+
+template <uint32_t KIND, int UNROLL>
+__device__ __forceinline__ void serve_words_fill(uint32_t *__restrict__ st, uint64_t n, uint64_t k,
+                                                 uint64_t count, uint32_t *__restrict__ out) {
+  const uint32_t lane = lane_id();
+  const uint64_t nfull = n >> 6;
+  const uint32_t rem = (uint32_t)(n & 63u);
+  const uint64_t stride = count * 64;
+  serve_chunks<KIND, UNROLL>(load_state(st), n, out + k * 64 + lane, stride,
+                             out + nfull * stride + k * rem + lane, st);
 }
 
 // ---------------------------------------------------------------------------
@@ -744,6 +753,80 @@ __global__ __launch_bounds__(kSegWaves * 64) void k_skip_wg(uint32_t *__restrict
   if (wave == 0) write_state(st, s.prev, s.cur, 0u, 0u, s.weyl, s.pos, lane_id());
 }
 
+// ---------------------------------------------------------------------------
+// Rows cut into parts (xg_split.h): launches of few streams.
+// ---------------------------------------------------------------------------
+// Where part k of the launch's i-th stream keeps its start state: word t at
+// out[i row + k part + (t / 64) chunk + t % 64], i.e. in the part's own first
+// three chunks in either layout (a part has at least four).
+struct SplitPlaces {
+  uint64_t row, part, chunk;
+};
+
+// Start states of all parts: workgroup b jumps stream b % count by
+// (b / count) 2^exp words (part 0: a copy) and leaves ring, Weyl value and
+// position in the part's place in the output.  Nothing else reads the streams'
+// states after this kernel, so k_split_* may write them back.
+__global__ __launch_bounds__(kSegWaves * 64) void k_split_starts(const uint32_t *__restrict__ state, uint64_t first,
+                                                                 uint32_t count, uint32_t exp,
+                                                                 const uint64_t *__restrict__ table,
+                                                                 uint32_t *__restrict__ out, SplitPlaces at) {
+  __shared__ JumpLds lds;
+  const uint32_t lane = lane_id();
+  const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const uint32_t k = blockIdx.x / count, i = blockIdx.x % count;
+  StreamState s = load_state(state + (first + i) * kStateWords);
+  if (k) {
+    const uint64_t h = table[(uint64_t)split_entry(exp, k) * 64 + lane];  // lane c holds h_c
+    jump_state_wg(s, (int)(uint32_t)h, (int)(uint32_t)(h >> 32), (uint64_t)k << exp, lds, wave);
+  }
+  if (wave != 0) return;
+  uint32_t *o = out + i * at.row + k * at.part;
+  o[lane] = s.prev;
+  o[at.chunk + lane] = s.cur;
+  if (lane < 3u) o[2 * at.chunk + lane] = lane == 0 ? s.weyl : (uint32_t)(s.pos >> (32u * (lane - 1u)));
+}
+
+__device__ __forceinline__ StreamState load_split(const uint32_t *o, uint64_t chunk) {
+  const uint32_t lane = lane_id();
+  StreamState s;
+  s.prev = o[lane];
+  s.cur = o[chunk + lane];
+  const int v = lane < 3u ? (int)o[2 * chunk + lane] : 0;
+  s.weyl = (uint32_t)__builtin_amdgcn_readlane(v, 0);
+  s.pos = (uint64_t)(uint32_t)__builtin_amdgcn_readlane(v, 1) |
+          ((uint64_t)(uint32_t)__builtin_amdgcn_readlane(v, 2) << 32);
+  return s;
+}
+
+// One wavefront per part: wavefront (k, i) starts from the state in part k's
+// place, writes the part's values over it (every value depends on all of the
+// state, so the loads are done first), and the last part writes the stream's
+// end state.
+template <uint32_t KIND, bool FILL>
+__global__ __launch_bounds__(256) void k_split(uint32_t *__restrict__ state, uint64_t first, uint32_t count,
+                                               uint64_t n, uint32_t parts, uint32_t exp, uint32_t *out,
+                                               SplitPlaces at) {
+  const uint32_t wid = (uint32_t)__builtin_amdgcn_readfirstlane((int)((blockIdx.x * blockDim.x + threadIdx.x) >> 6));
+  const uint32_t k = wid / count, i = wid % count;
+  if (k >= parts) return;
+  const uint64_t done = (uint64_t)k << exp;
+  const bool last = k + 1 == parts;
+  const uint64_t nk = last ? n - done : 1ull << exp;
+  uint32_t *o = out + i * at.row + k * at.part;
+  const StreamState s0 = load_split(o, at.chunk);
+  uint32_t *dst = last ? state + (first + i) * kStateWords : nullptr;
+  if constexpr (KIND == kNormal) {
+    serve_normals_from<false, 8, true, false>(s0, nk, reinterpret_cast<float *>(o), nullptr, dst);
+  } else if constexpr (FILL) {
+    const uint32_t lane = lane_id();
+    uint32_t *tail = out + (n >> 6) * at.chunk + i * (n & 63u) + lane;
+    serve_chunks<KIND, 8, false>(s0, nk, o + lane, at.chunk, tail, dst);
+  } else {
+    serve_words_from<KIND, 8, false, false, false>(s0, nk, o, dst);
+  }
+}
+
 // Box-Muller on caller-supplied word pairs (the same device function the
 // generators use): out[2m], out[2m + 1] from words[2m], words[2m + 1].
 __global__ __launch_bounds__(256) void k_box_muller(const uint32_t *__restrict__ words, uint64_t pairs,
@@ -1000,6 +1083,25 @@ hipError_t launch_generate(Kind kind, const Shape &shape, uint32_t *state, uint6
       return launch_generate_k<kNormal>(shape, grid, block, state, first, count, n, out, num_cus, stream);
     default: return launch_generate_k<kMoments>(shape, grid, block, state, first, count, n, out, num_cus, stream);
   }
+}
+
+hipError_t launch_split(Kind kind, bool fill, const Split &sp, uint32_t *state, uint64_t first, uint64_t count,
+                        uint64_t n, const uint64_t *table, void *out, int num_cus, hipStream_t stream) {
+  const uint64_t waves = count * sp.parts;
+  const uint64_t wpb = auto_waves_per_block(waves, num_cus);
+  uint32_t *o = static_cast<uint32_t *>(out);
+  const uint64_t part = 1ull << sp.exp;
+  const SplitPlaces at = fill ? SplitPlaces{64, part * count, 64 * count} : SplitPlaces{n, part, 64};
+  hipError_t e = launch(k_split_starts, dim3((uint32_t)waves), dim3(kSegWaves * 64), 0, stream, state, first, count,
+                        sp.exp, table, o, at);
+  if (e != hipSuccess) return e;
+  auto run = [&](auto kernel) {
+    return launch(kernel, dim3((uint32_t)((waves + wpb - 1) / wpb)), dim3((uint32_t)(wpb * kWave)), 0, stream, state,
+                  first, count, n, sp.parts, sp.exp, o, at);
+  };
+  if (kind == kNormal) return run(k_split<kNormal, false>);
+  if (kind == kF32) return fill ? run(k_split<kF32, true>) : run(k_split<kF32, false>);
+  return fill ? run(k_split<kU32, true>) : run(k_split<kU32, false>);
 }
 
 hipError_t launch_work_init(uint32_t *work, uint32_t num_groups, uint32_t num_reqs, hipStream_t stream) {
