@@ -27,6 +27,7 @@
 
 #include "xg_device.h"
 #include "xg_normal.h"
+#include "xg_normal_f64.h"
 #include "xg_internal.h"
 #include "xg_launch.h"
 #include "xg_fam_batch.h"
@@ -273,40 +274,52 @@ __device__ __forceinline__ void fam_serve(unsigned char *__restrict__ state, con
 // normals: Box-Muller on consecutive pairs (o_{2m}, o_{2m+1}) of each
 // stream's outputs of the call, as for Section 2's member; FP32 from the
 // 32-bit member, FP64 (53-bit uniforms) from the 64-bit member.  Two steps
-// give 64 words of each stream, i.e. 32 pairs: lane 2m + h takes pair m of
-// stream h, whose words sit on lanes (4m + h) mod 64 and (4m + 2 + h) mod 64
-// of the first step (m < 16) or of the second.  MOMENTS (32-bit member):
-// per-lane compensated sums of z and z^2, reduced over the lanes of each
-// stream (their lane parity), instead of storing the variates.
+// give 64 words of each stream, i.e. 32 pairs, one per lane: on even j words j
+// and j + 1 of the first step, on odd j words j - 1 and j of the second, so
+// each lane needs one word of the lane two away, which a quad permutation
+// supplies in the VALU (in place of four LDS permutes per 32-bit word).
 // ---------------------------------------------------------------------------
-// FP64 normals of the 64-bit member: u1 = ((e >> 11) + 1) 2^-53 in (0, 1]
-// and u2 = (o >> 11) 2^-53 in [0, 1), both exact; z0 = rho cos(2 pi u2),
-// z1 = rho sin(2 pi u2), rho = sqrt(-2 ln u1).  The angle is reduced exactly
-// on the word as in dev::sincos_turn: adding 2^61 to o leaves the quadrant in bits
-// 63:62 and (o's low 11 bits cleared) 2^61 + f 2^63 in bits 61:0, |f| <= 1/4.
-// sin(pi f), cos(pi f), ln and the square root are the device library's FP64
-// functions.
-__device__ __forceinline__ void box_muller_f64(uint64_t e, uint64_t o, double &z0, double &z1) {
-  const double u1 = fma((double)(e >> 11), 0x1p-53, 0x1p-53);  // exact
-  const double rho = sqrt(-2.0 * log(u1));
-  const uint64_t qf = o + (1ull << 61);
-  const double f = fma((double)(qf & 0x3FFFFFFFFFFFF800ull), 0x1p-63, -0.25);  // exact
-  double sp, cp;
-  sincospi(f, &sp, &cp);
-  const bool odd = ((qf >> 62) & 1u) != 0u;
-  const double s0 = odd ? cp : sp, c0 = odd ? sp : cp;
-  const uint64_t sign_s = qf & 0x8000000000000000ull, sign_c = (qf + (1ull << 62)) & 0x8000000000000000ull;
-  z0 = rho * __longlong_as_double((long long)((uint64_t)__double_as_longlong(c0) ^ sign_c));
-  z1 = rho * __longlong_as_double((long long)((uint64_t)__double_as_longlong(s0) ^ sign_s));
+__device__ __forceinline__ uint32_t swap_words(uint32_t v) {
+  constexpr int kSwapTwo = 0x4E;  // quad_perm [2, 3, 0, 1]
+  return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, kSwapTwo, 0xF, 0xF, false);
+}
+__device__ __forceinline__ uint64_t swap_words(uint64_t v) {
+  return (uint64_t)swap_words((uint32_t)v) | ((uint64_t)swap_words((uint32_t)(v >> 32)) << 32);
+}
+__device__ __forceinline__ uint32_t select_word(uint32_t a, uint32_t b, uint32_t m) { return dev::select_bits(a, b, m); }
+__device__ __forceinline__ uint64_t select_word(uint64_t a, uint64_t b, uint32_t m) {
+  return (uint64_t)dev::select_bits((uint32_t)a, (uint32_t)b, m) |
+         ((uint64_t)dev::select_bits((uint32_t)(a >> 32), (uint32_t)(b >> 32), m) << 32);
 }
 
+// The lane's pair of the 64-word block lo | hi; its first word's place in the
+// block is fam_pair_offset.  (Bit selects, not ternaries, so that the swaps
+// stay outside lane-divergent code.)
 template <typename word>
-__device__ __forceinline__ void fam_gather_pair(word a, word b, uint32_t m, uint32_t h, word &e, word &o) {
-  const int se = (int)((4u * m + h) & 63u), so = (int)((4u * m + 2u + h) & 63u);
-  const word ea = shfl_word(a, se), eb = shfl_word(b, se), oa = shfl_word(a, so), ob = shfl_word(b, so);
-  const bool upper = m >= 16u;
-  e = upper ? eb : ea;
-  o = upper ? ob : oa;
+__device__ __forceinline__ void fam_gather_pair(word lo, word hi, uint32_t j, word &e, word &o) {
+  const uint32_t odd = 0u - (j & 1u);
+  const word lo_sw = swap_words(lo), hi_sw = swap_words(hi);
+  e = select_word(hi_sw, lo, odd);
+  o = select_word(hi, lo_sw, odd);
+}
+__device__ __forceinline__ uint32_t fam_pair_offset(uint32_t j) { return (j & ~1u) + ((j & 1u) << 5); }
+
+// The normals of P pairs: in order, or (ORDERED = false) each pair's two in
+// whichever order is cheaper.
+struct NoConsts {};
+template <bool ORDERED, int P>
+__device__ __forceinline__ void fam_pairs(const NoConsts &, const uint32_t (&e)[P], const uint32_t (&o)[P],
+                                          float (&z0)[P], float (&z1)[P]) {
+#pragma unroll
+  for (int u = 0; u < P; ++u) {
+    if constexpr (ORDERED) dev::box_muller(e[u], o[u], z0[u], z1[u]);
+    else dev::box_muller_unordered(e[u], o[u], z0[u], z1[u]);
+  }
+}
+template <bool ORDERED, int P>
+__device__ __forceinline__ void fam_pairs(const dev::ConstsF64 &k, const uint64_t (&e)[P], const uint64_t (&o)[P],
+                                          double (&z0)[P], double (&z1)[P]) {
+  dev::box_muller_f64<ORDERED>(k, e, o, z0, z1);
 }
 
 // Compensated FP64 sums of z and z^2 kept by one lane (one update per pair).
@@ -321,72 +334,45 @@ __device__ __forceinline__ void kahan_add_f64(double &s, double &c, double v) {
   s = t;
 }
 
-// FP64 normals idx and idx + 1 of the call (those below n): stored (a pair is
-// one 16-byte store when `pair_aligned`, wave-uniform) or, MOMENTS, added to
-// the lane's sums as z0 + z1 and fma(z1, z1, z0 z0).
-template <bool MOMENTS>
-__device__ __forceinline__ void fam_consume_pair_f64(uint64_t e, uint64_t o, uint64_t idx, uint64_t n, bool on,
-                                                     double *__restrict__ out, bool pair_aligned,
-                                                     MomentsF64 &m) {
-  double z0, z1;
-  box_muller_f64(e, o, z0, z1);
-  const bool has0 = on && idx < n, has1 = on && idx + 1 < n;
-  if constexpr (MOMENTS) {
-    if (has0) {  // has1 implies has0
-      const double b = has1 ? z1 : 0.0;
-      kahan_add_f64(m.s1, m.c1, z0 + b);
-      kahan_add_f64(m.s2, m.c2, fma(b, b, z0 * z0));
-    }
-  } else if (pair_aligned && has1) {
-    typedef double f64x2 __attribute__((ext_vector_type(2)));
-    const f64x2 pair = {z0, z1};
-    __builtin_nontemporal_store(pair, reinterpret_cast<f64x2 *>(out + idx));
-  } else {
-    if (has0) __builtin_nontemporal_store(z0, out + idx);
-    if (has1) __builtin_nontemporal_store(z1, out + idx + 1);
-  }
+// A pair (or, has1 = false, its first variate alone) into the lane's sums, as
+// z0 + z1 and fma(z1, z1, z0 z0): one compensated update each.
+__device__ __forceinline__ void sums_add(dev::Moments &m, float z0, float z1) {
+  dev::group_add(m, z0, z1);
+  dev::group_close(m);
+}
+__device__ __forceinline__ void sums_add(MomentsF64 &m, double z0, double z1) {
+  kahan_add_f64(m.s1, m.c1, z0 + z1);
+  kahan_add_f64(m.s2, m.c2, fma(z1, z1, z0 * z0));
 }
 
-template <bool MOMENTS>
-__device__ __forceinline__ void fam_consume_pair(uint32_t e, uint32_t o, uint64_t idx, uint64_t n, bool on,
-                                                 float *__restrict__ out, bool pair_aligned, dev::Moments &m) {
-  float z0, z1;
-  dev::box_muller(e, o, z0, z1);
-  const bool has0 = on && idx < n, has1 = on && idx + 1 < n;
-  if constexpr (MOMENTS) {
-    if (has0) {  // a group of one pair per compensated update (has1 implies has0)
-      dev::group_add(m, z0, has1 ? z1 : 0.0f);
-      dev::group_close(m);
-    }
-  } else {
-    if (pair_aligned && has1) {
-      typedef float f32x2 __attribute__((ext_vector_type(2)));
-      const f32x2 pair = {z0, z1};
-      __builtin_nontemporal_store(pair, reinterpret_cast<f32x2 *>(out + idx));
-    } else {
-      if (has0) __builtin_nontemporal_store(z0, out + idx);
-      if (has1) __builtin_nontemporal_store(z1, out + idx + 1);
-    }
-  }
+template <bool NT, class T>
+__device__ __forceinline__ void store_normal(T v, T *p) {
+  if constexpr (NT) __builtin_nontemporal_store(v, p);
+  else *p = v;
 }
 
-// n normals of each of `count` streams (launch index k = stream first + k)
-// at out[k n + t], or their sums at sums[2k], sums[2k + 1].  Consumes
-// 2 ceil(n / 2) words per stream.
+template <class M>
+using real_of = typename std::conditional<sizeof(typename M::word) == 8, double, float>::type;
+
 // n normals of the stream at st per half-wavefront (n wave-uniform), from
 // 2 ceil(n / 2) words: Box-Muller on consecutive pairs, written from o_s
 // (the stream's first output) unless MOMENTS, which instead reduces the
 // half's sums of z and z^2 and stores them at sums (two reals).  on = false
-// masks this lane's loads and stores.
-template <class M, bool MOMENTS>
+// masks this lane's loads and stores; BOTH: on is true on every lane.
+// NT: non-temporal stores.
+//
+// The blocks wholly below n run UNROLL at a time without a test per value, and
+// a pair's two adjacent stores become one (which needs the alignment of one
+// value only).  One block at a time with a test per value and, for odd n, two
+// separate stores per pair took 570 us for 3001 streams x 65537 FP32 normals,
+// this form 235 us.
+template <class M, bool MOMENTS, bool BOTH, bool NT>
 __device__ __forceinline__ void fam_normals_run(unsigned char *__restrict__ st, bool on, Lanes L, uint64_t n,
-                                                typename std::conditional<sizeof(typename M::word) == 8, double,
-                                                                          float>::type *__restrict__ o_s,
-                                                typename std::conditional<sizeof(typename M::word) == 8, double,
-                                                                          float>::type *__restrict__ sums) {
+                                                real_of<M> *__restrict__ o_s, real_of<M> *__restrict__ sums) {
   using word = typename M::word;
+  using real = real_of<M>;
   constexpr bool kW64 = sizeof(word) == 8;
-  using real = typename std::conditional<kW64, double, float>::type;
+  if constexpr (BOTH) on = true;
   L.active = on;
   word prev = 0, cur = 0, w_start = 0;
   uint64_t pos = 0;
@@ -410,41 +396,63 @@ __device__ __forceinline__ void fam_normals_run(unsigned char *__restrict__ st, 
   };
   const uint64_t words = n + (n & 1u);
   const uint64_t nblk = words >> 6;  // 64-word blocks: 32 pairs of each stream
+  const uint64_t nsafe = n >> 6;     // of these, the blocks whose 64 normals are all below n
   const uint32_t rw = (uint32_t)(words & 63u);
-  const uint32_t m = L.j;
-  const bool pair_aligned =
-      !MOMENTS && (n & 1u) == 0 && (reinterpret_cast<uintptr_t>(o_s) & (2 * sizeof(real) - 1)) == 0;
-  dev::Moments mo{0.0f, 0.0f, 0.0f, 0.0f, -0.0f, -0.0f};
-  MomentsF64 md{0.0, 0.0, 0.0, 0.0};
-  auto consume = [&](word e, word o, uint64_t idx) {
-    if constexpr (kW64) fam_consume_pair_f64<MOMENTS>(e, o, idx, n, on, o_s, pair_aligned, md);
-    else fam_consume_pair<MOMENTS>(e, o, idx, n, on, o_s, pair_aligned, mo);
-  };
+  const uint32_t poff = fam_pair_offset(L.j);
+  typename std::conditional<kW64, MomentsF64, dev::Moments>::type m;
+  if constexpr (kW64) m = MomentsF64{0.0, 0.0, 0.0, 0.0};
+  else m = dev::Moments{0.0f, 0.0f, 0.0f, 0.0f, -0.0f, -0.0f};
+  typename std::conditional<kW64, dev::ConstsF64, NoConsts>::type consts;
+  if constexpr (kW64) consts = dev::consts_f64();
+  real *p = MOMENTS ? nullptr : o_s + poff;
+  constexpr int UNROLL = kW64 ? 2 : 4;
   uint64_t b = 0;
-  if constexpr (MOMENTS && !kW64) {
-    // Blocks wholly below n, four at a time: each pair enters the sums
-    // unordered and unchecked (a masked half's sums are never stored), and
-    // each group of four pairs takes one compensated update.
-    for (const uint64_t nsafe4 = (n >> 6) & ~uint64_t(3); b != nsafe4; b += 4) {
+  for (const uint64_t nouter = nsafe & ~uint64_t(UNROLL - 1); b != nouter; b += UNROLL) {
+    word e[UNROLL], o[UNROLL];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const word oa = next();
-        const word ob = next();
-        word e, o;
-        fam_gather_pair(oa, ob, m, L.h, e, o);
-        float za, zb;
-        dev::box_muller_unordered(e, o, za, zb);
-        dev::group_add(mo, za, zb);
-      }
-      dev::group_close(mo);
+    for (int u = 0; u < UNROLL; ++u) {
+      const word oa = next();
+      const word ob = next();
+      fam_gather_pair(oa, ob, L.j, e[u], o[u]);
     }
+    real z0[UNROLL], z1[UNROLL];
+    fam_pairs<!MOMENTS>(consts, e, o, z0, z1);
+#pragma unroll
+    for (int u = 0; u < UNROLL; ++u) {
+      if constexpr (!MOMENTS) {
+        if (on) {
+          store_normal<NT>(z0[u], p + 64 * u);
+          store_normal<NT>(z1[u], p + 64 * u + 1);
+        }
+      } else if constexpr (kW64) {
+        sums_add(m, z0[u], z1[u]);
+      } else {
+        dev::group_add(m, z0[u], z1[u]);
+      }
+    }
+    if constexpr (MOMENTS && !kW64) dev::group_close(m);  // one compensated update per UNROLL pairs
+    if constexpr (!MOMENTS) p += 64 * UNROLL;
   }
+  // Pair at idx, idx + 1 of the call, those below n.
+  auto checked = [&](word e, word o, uint64_t idx) {
+    const word ee[1] = {e}, oo[1] = {o};
+    real y0[1], y1[1];
+    fam_pairs<true>(consts, ee, oo, y0, y1);
+    const real z0 = y0[0], z1 = y1[0];
+    const bool has0 = on && idx < n, has1 = on && idx + 1 < n;
+    if constexpr (MOMENTS) {
+      if (has0) sums_add(m, z0, has1 ? z1 : real(0));  // has1 implies has0
+    } else {
+      if (has0) store_normal<NT>(z0, o_s + idx);
+      if (has1) store_normal<NT>(z1, o_s + idx + 1);
+    }
+  };
   for (; b != nblk; ++b) {
     const word oa = next();
     const word ob = next();
     word e, o;
-    fam_gather_pair(oa, ob, m, L.h, e, o);
-    consume(e, o, (b << 6) + 2u * m);
+    fam_gather_pair(oa, ob, L.j, e, o);
+    checked(e, o, (b << 6) + poff);
   }
   // Tail: rw (even, < 64) more words.
   word p0 = g.prev, c0 = g.cur, xl = 0;
@@ -470,21 +478,14 @@ __device__ __forceinline__ void fam_normals_run(unsigned char *__restrict__ st, 
       rem = rw - 32u;
     }
     word e, o;
-    fam_gather_pair(oa, ob, m, L.h, e, o);
-    if (2u * m < rw) consume(e, o, (nblk << 6) + 2u * m);
+    fam_gather_pair(oa, ob, L.j, e, o);
+    if (poff < rw) checked(e, o, (nblk << 6) + poff);
   }
   store_state<M>(st, L, p0, c0, xl, rem, w_start + (word)words * M::omega, pos + words);
   if constexpr (MOMENTS) {
     // Folded and reduced across the stream's lanes in FP64 (for the FP32
     // sums: rounded once to FP32 at the end).
-    double v1, v2;
-    if constexpr (kW64) {
-      v1 = md.s1 - md.c1;
-      v2 = md.s2 - md.c2;
-    } else {
-      v1 = (double)mo.s1 - (double)mo.c1;
-      v2 = (double)mo.s2 - (double)mo.c2;
-    }
+    double v1 = (double)m.s1 - (double)m.c1, v2 = (double)m.s2 - (double)m.c2;
 #pragma unroll
     for (int off = 32; off >= 2; off >>= 1) {  // even offsets keep each stream's lanes apart
       v1 += __shfl_xor(v1, off);
@@ -497,18 +498,22 @@ __device__ __forceinline__ void fam_normals_run(unsigned char *__restrict__ st, 
   }
 }
 
-template <class M, bool MOMENTS>
+// n normals of each of `count` streams (launch index k = stream first + k)
+// at out[k n + t], or their sums at sums[2k], sums[2k + 1].  Consumes
+// 2 ceil(n / 2) words per stream.
+template <class M, bool MOMENTS, bool NT>
 __global__ __launch_bounds__(1024) void k_fam_normals(unsigned char *__restrict__ state, uint64_t first,
                                                       uint64_t count, uint64_t n, void *__restrict__ out_v,
                                                       void *__restrict__ sums_v) {
-  using word = typename M::word;
-  using real = typename std::conditional<sizeof(word) == 8, double, float>::type;
-  real *out = static_cast<real *>(out_v);
-  real *sums = static_cast<real *>(sums_v);
+  using real = real_of<M>;
   const Lanes L = lanes_of(count, xcd_block());
-  if (2 * (L.k >> 1) >= count) return;  // wave-uniform
-  fam_normals_run<M, MOMENTS>(state + (first + L.k) * M::state_bytes, L.active, L, n,
-                              MOMENTS ? nullptr : out + L.k * n, MOMENTS ? sums + 2 * L.k : nullptr);
+  const uint64_t pair = L.k >> 1;
+  if (2 * pair >= count) return;  // wave-uniform
+  unsigned char *st = state + (first + L.k) * M::state_bytes;
+  real *out = MOMENTS ? nullptr : static_cast<real *>(out_v) + L.k * n;
+  real *sums = MOMENTS ? static_cast<real *>(sums_v) + 2 * L.k : nullptr;
+  if (2 * pair + 1 < count) fam_normals_run<M, MOMENTS, true, NT>(st, true, L, n, out, sums);
+  else fam_normals_run<M, MOMENTS, false, NT>(st, L.active, L, n, out, sums);
 }
 
 template <class M, uint32_t KIND, int UNROLL, bool FILL>
@@ -701,7 +706,7 @@ __global__ __launch_bounds__(1024) void k_fam_batch(unsigned char *__restrict__ 
         unsigned char *st = state + (mine ? q.stream : 0) * M::state_bytes;
         const uint64_t at = mine ? q.out_offset + done : 0;
         if (kind == XG_NORMAL)
-          fam_normals_run<M, false>(st, mine, L, n, reinterpret_cast<real *>(out) + at, nullptr);
+          fam_normals_run<M, false, false, true>(st, mine, L, n, reinterpret_cast<real *>(out) + at, nullptr);
         else if (kind == XG_F32)
           fam_run<M, kReal, UNROLL>(st, mine, L, n, out + at + L.j, kStep, nullptr);
         else
@@ -897,24 +902,24 @@ hipError_t launch_family_generate(uint32_t family, Kind kind, bool fill, const S
   const uint64_t pairs = (count + 1) / 2;
   const uint64_t wpb = shape.waves_per_block;
   const dim3 grid((uint32_t)((pairs + wpb - 1) / wpb)), block((uint32_t)(wpb * kWave));
-  if (family == XG_FAMILY_R64_W32 && (kind == kNormal || kind == kMoments)) {
-    float *o = static_cast<float *>(out);
-    if (kind == kNormal)
-      e = launch((k_fam_normals<MemberN2048, false>), grid, block, 0, stream, state, first, count, n, out,
-                         nullptr);
-    else
-      e = launch((k_fam_normals<MemberN2048, true>), grid, block, 0, stream, state, first, count, n, nullptr,
-                         o);
-    return e;
-  }
-  if (family == XG_FAMILY_R64_W64 && (kind == kNormal || kind == kMoments)) {
-    if (kind == kNormal)
-      e = launch((k_fam_normals<MemberW64, false>), grid, block, 0, stream, state, first, count, n, out,
-                         nullptr);
-    else
-      e = launch((k_fam_normals<MemberW64, true>), grid, block, 0, stream, state, first, count, n, nullptr,
-                         out);
-    return e;
+  if (kind == kNormal || kind == kMoments) {
+    // Non-temporal stores while every row starts on a cache line; rows that
+    // start inside one leave partial lines, which only cached stores merge.
+    const uint64_t row_bytes = n * (family == XG_FAMILY_R64_W64 ? 8 : 4);
+    const bool nt = kind == kNormal && (row_bytes | reinterpret_cast<uintptr_t>(out)) % 128 == 0;
+    auto run = [&](auto kernel) {
+      return launch(kernel, grid, block, 0, stream, state, first, count, n, kind == kNormal ? out : nullptr,
+                    kind == kMoments ? out : nullptr);
+    };
+    if (family == XG_FAMILY_R64_W32)
+      return kind == kMoments ? run(k_fam_normals<MemberN2048, true, false>)
+             : nt             ? run(k_fam_normals<MemberN2048, false, true>)
+                              : run(k_fam_normals<MemberN2048, false, false>);
+    if (family == XG_FAMILY_R64_W64)
+      return kind == kMoments ? run(k_fam_normals<MemberW64, true, false>)
+             : nt             ? run(k_fam_normals<MemberW64, false, true>)
+                              : run(k_fam_normals<MemberW64, false, false>);
+    return hipErrorInvalidValue;
   }
   if (family == XG_FAMILY_R64_W32 && kind == kU32)
     e = launch_fam_layout<MemberN2048, kU32>(fill, shape.unroll, grid, block, state, first, count, n, out, stream);
