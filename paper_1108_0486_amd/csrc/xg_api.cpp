@@ -130,9 +130,9 @@ xg::Shape plain_shape(const xg_ctx *ctx, uint64_t count, xg::Kind kind, bool fil
 
 // The parts of a plain launch (xg_split.h), none unless the launch shape is
 // automatic.  A row of 2^15 words takes one wavefront 17 us; jumping to the
-// parts' starts and running them takes 15 us and then grows hardly at all
-// (2^20 words of one stream: 544 us on one wavefront, 15.8 us in 256 parts;
-// 24 streams of 100 003: 63 and 25 us).  With more than half the chip's SIMDs
+// parts' starts and running them takes 11 us and then grows hardly at all
+// (2^20 words of one stream: 544 us on one wavefront, 10.5 us in 256 parts;
+// 24 streams of 100 003: 63 and 18 us).  With more than half the chip's SIMDs
 // at work already a second wavefront on some of them gains too little.
 xg::Split split_for(const xg_ctx *ctx, xg::Kind kind, uint64_t count, uint64_t n) {
   if (!ctx->split_table || ctx->plain.waves_per_block || ctx->plain.unroll || kind == xg::kMoments) return {};

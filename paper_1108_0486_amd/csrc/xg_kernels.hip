@@ -22,6 +22,7 @@
 #include <stdint.h>
 
 #include "xg_device.h"
+#include "xg_jump_mm.h"
 #include "xg_normal.h"
 #include "xg_internal.h"
 #include "xg_launch.h"
@@ -39,7 +40,6 @@ using dev::wave_lds_sync;
 using dev::splitmix64_at;
 using dev::xcd_block;
 using dev::xor3;
-using dev::xor_and;
 
 constexpr uint32_t kOmega = 0x9E3779B9u;       // odd integer nearest 2^31 (sqrt 5 - 1)
 constexpr uint32_t kChunkOmega = 64u * kOmega;  // Weyl advance per chunk (mod 2^32)
@@ -605,152 +605,175 @@ __device__ __forceinline__ void skip_by_stepping(uint32_t *st, uint64_t J) {
   store_weyl_pos(st, s.w_start + (uint32_t)J * kOmega, s.pos + J, s.lane);
 }
 
-// By jumping: with g = z^J mod P = sum_c z^(64 c) h_c(z) (h_c of degree < 64),
-// T^J S0 = g(T) S0 is evaluated by Horner's rule in steps of 64 words,
-//     S <- T^64 S  xor  h_c(T) S0,      c = 63 .. 0,
-// where T^64 S is one wavefront chunk step on the state S, and
-// h_c(T) S0 = xor of the windows T^i S0 (i < 64, bit i of h_c set); window i
-// holds words x_{i-128} .. x_{i-1} of S0's continuation, so lane j's two words
-// of it are x_{i-128+j} and x_{i-64+j}, staged once through LDS into
-// registers.  word(c) returns h_c as 64 bits.  Needs the wavefront's LDS slot.
-template <typename WordOf>
-__device__ __forceinline__ void jump_state(StreamState &s, WordOf word, uint64_t J) {
+// By jumping (xg_jump_mm.h): n = 4096, r = 128 words of 32 bits, so the
+// continuation has 66 blocks of 64 words and the result four tiles of 32.
+constexpr uint32_t kJumpWords = 128;               // words of z^J mod P
+constexpr uint32_t kJumpBlocks = (4096 + 128) / 64;
+
+// Wavefronts of a workgroup that shares one jump.
+constexpr uint32_t kJumpWaves = 8;  // four took 8.0 us for one stream, eight take 5.9 (VALU window sums: 11.2)
+constexpr uint32_t kJumpBlocksPerCu = 2;           // such workgroups that a compute unit runs at once
+constexpr int kJumpQ0 = -3;                        // G's first q (tile 3 of block 0)
+constexpr uint32_t kJumpQs = 2 * kJumpBlocks - kJumpQ0;
+
+struct JumpLds {
+  uint32_t s[64 * kJumpBlocks];          // the continuation's words
+  uint32_t g[kJumpWords];
+  uint32_t rows[32 * kJumpQs];           // toeplitz_word(q, row_word(rho)) at 32 (q - kJumpQ0) + rho
+  uint32_t part[kJumpWaves][kJumpWords];  // each wavefront's share of the result
+};
+
+// One jump by a workgroup of kJumpWaves wavefronts, for launches where
+// latency counts.  Wavefront 0 runs the 64 dependent steps of the
+// continuation (1.6 us) while the others lay out G's rows; then each
+// wavefront takes a run of consecutive blocks, all four tiles of them (tiles 2
+// and 3 of a block are tiles 0 and 1 of the block before, so a block needs two
+// new fragments of G and one of s), and the shares are added as words.  s is
+// the stream's state on every wavefront and h_lo, h_hi the polynomial's 64-bit
+// word of the lane's index.  Returns word threadIdx.x of the jumped ring (wavefronts 0
+// and 1; zero elsewhere).  Every thread of the workgroup calls it.
+__device__ __forceinline__ uint32_t jump_ring_wg(const StreamState &s, uint32_t h_lo, uint32_t h_hi, JumpLds &lds,
+                                                 uint32_t wave) {
   const uint32_t lane = lane_id();
-  const bool lane0 = lane == 0;
-  Ring r = ring_from(s.prev, s.cur);
-  const uint32_t x0 = ring_step(r, lane0);             // x_0 .. x_63
-  uint32_t *buf = wave_stage();                          // x_{-128} .. x_{63}
-  buf[lane] = s.prev;
-  buf[64 + lane] = s.cur;
-  buf[128 + lane] = x0;
-  wave_lds_sync();
-  uint32_t xw[128];                                      // xw[k] = x_{k-128+j}
-#pragma unroll
-  for (int k = 0; k < 128; ++k) xw[k] = buf[lane + k];
-  wave_lds_sync();                                       // the slot may be reused after this
-  uint32_t slo = 0u, shi = 0u;
-#pragma unroll 1
-  for (int c = 63; c >= 0; --c) {
-    if (c != 63) {
-      Ring q = ring_from(slo, shi);
-      const uint32_t nx = ring_step(q, lane0);
-      slo = shi;
-      shi = nx;
-    }
-    const uint64_t h = word(c);
-    const uint32_t hlo = (uint32_t)h, hhi = (uint32_t)(h >> 32);
-    uint32_t alo = 0u, ahi = 0u;
-#pragma unroll
-    for (int i = 0; i < 64; ++i) {
-      const uint32_t bits = i < 32 ? hlo : hhi;
-      const uint32_t m = (uint32_t)((int32_t)(bits << (31 - (i & 31))) >> 31);  // bit i of h_c, all ones or zero
-      alo = xor_and(alo, xw[i], m);
-      ahi = xor_and(ahi, xw[64 + i], m);
-    }
-    slo ^= alo;
-    shi ^= ahi;
+  __syncthreads();  // an earlier jump's reads of lds are done
+  if (wave == 1) {
+    lds.g[2 * lane] = h_lo;
+    lds.g[2 * lane + 1] = h_hi;
   }
-  s.prev = slo;
-  s.cur = shi;
+  __syncthreads();
+  if (wave == 0) {
+    const bool lane0 = lane == 0;
+    lds.s[lane] = s.prev;
+    lds.s[64 + lane] = s.cur;
+    Ring r = ring_from(s.prev, s.cur);
+#pragma unroll 4
+    for (uint32_t c = 2; c < kJumpBlocks; ++c) lds.s[64 * c + lane] = ring_step(r, lane0);
+  } else {
+    for (uint32_t i = threadIdx.x - 64; i < 32 * kJumpQs; i += 64 * (kJumpWaves - 1))
+      lds.rows[i] = dev::toeplitz_word(lds.g, kJumpWords, (int)(i / 32) + kJumpQ0, dev::row_word(i % 32));
+  }
+  __syncthreads();
+  const dev::TransposeLane tl = dev::transpose_lane(lane);
+  constexpr uint32_t kEach = kJumpBlocks / kJumpWaves, kMore = kJumpBlocks % kJumpWaves;  // the last kMore take one more
+  const uint32_t late = wave > kJumpWaves - kMore ? wave - (kJumpWaves - kMore) : 0u;
+  const uint32_t c0 = kEach * wave + late;
+  // Tile t of block c: q = 2 c - t + h.
+  const uint32_t *rows = lds.rows + 32 * (2 * c0 - kJumpQ0) + lane;
+  dev::tile_t acc[4] = {};
+  dev::frag_t a2 = dev::frag(dev::one_bits(rows[-64])), a3 = dev::frag(dev::one_bits(rows[-96]));
+  auto block = [&](uint32_t c) {
+    const dev::frag_t b = dev::frag(dev::half_bits(dev::word_bits(lds.s[64 * c + lane], tl)));
+    const dev::frag_t a0 = dev::frag(dev::one_bits(rows[0])), a1 = dev::frag(dev::one_bits(rows[-32]));
+    acc[0] = dev::mm_step(a0, b, acc[0]);
+    acc[1] = dev::mm_step(a1, b, acc[1]);
+    acc[2] = dev::mm_step(a2, b, acc[2]);
+    acc[3] = dev::mm_step(a3, b, acc[3]);
+    a2 = a0;
+    a3 = a1;
+    rows += 64;
+  };
+#pragma unroll
+  for (uint32_t i = 0; i < kEach; ++i) block(c0 + i);
+  if (wave >= kJumpWaves - kMore) block(c0 + kEach);
+  lds.part[wave][lane] = dev::tile_words(acc[0], acc[1], tl);
+  lds.part[wave][64 + lane] = dev::tile_words(acc[2], acc[3], tl);
+  __syncthreads();
+  uint32_t y = 0;
+  if (wave < 2) {
+#pragma unroll
+    for (uint32_t w = 0; w < kJumpWaves; ++w) y ^= lds.part[w][threadIdx.x];
+  }
+  return y;
+}
+
+__device__ __forceinline__ void jump_weyl(StreamState &s, uint64_t J) {
   s.weyl += (uint32_t)J * kOmega;
   s.pos += J;
 }
 
-template <bool JUMP>
-__global__ __launch_bounds__(256) void k_skip(uint32_t *__restrict__ state, uint64_t first, uint64_t count,
-                                              uint64_t J, JumpPoly g) {
-  const uint64_t wid = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-  if (wid >= count) return;
-  uint32_t *st = state + (first + wid) * kStateWords;
-  if constexpr (JUMP) {
-    StreamState s = load_state(st);
-    jump_state(s, [&](int c) { return g.w[c]; }, J);
-    write_state(st, s.prev, s.cur, 0u, 0u, s.weyl, s.pos, lane_id());
-  } else {
-    skip_by_stepping(st, J);
-  }
-}
-
-// Wavefronts that share one jump.  Four: at the 137-148 VGPRs per lane of the
-// kernels below (at most 170 leave room for three wavefronts per SIMD), three
-// such workgroups fit on a compute unit.
-constexpr uint32_t kSegWaves = 4;
-constexpr uint32_t kSegBlocksPerCu = 3;
-
-// LDS of one workgroup jump: the window x_{-128} .. x_{63} of the stream's
-// continuation, and the 64 window sums A_c (acc[128 c + j] lane j's low word,
-// acc[128 c + 64 + j] its high word).
-struct JumpLds {
-  uint32_t win[192];
-  uint32_t acc[64 * 128];
-};
-
-// jump_state's Horner evaluation split over the kSegWaves wavefronts of a
-// workgroup: the window sums A_c = h_c(T) S0 do not depend on each other, so
-// wavefront w computes A_c for c = w, w + kSegWaves, ... into LDS; then
-// wavefront 0 runs the chain S <- T^64 S xor A_c, c = 63 .. 0, and its s holds
-// T^J s on return (the others' s is unchanged).  Every thread of the
-// workgroup calls it with the same s; lane c's h_lo / h_hi hold h_c (so the
-// coefficients come from registers, read with v_readlane, and the masks from
-// scalar bit-field extracts).  Ends with a barrier: lds may be reused at once.
-__device__ __forceinline__ void jump_state_wg(StreamState &s, int h_lo, int h_hi, uint64_t J, JumpLds &lds,
-                                              uint32_t wave) {
-  const uint32_t lane = lane_id();
-  const bool lane0 = lane == 0;
-  if (wave == 0) {
-    Ring r0 = ring_from(s.prev, s.cur);
-    const uint32_t x0 = ring_step(r0, lane0);  // x_0 .. x_63
-    lds.win[lane] = s.prev;
-    lds.win[64 + lane] = s.cur;
-    lds.win[128 + lane] = x0;
-  }
-  __syncthreads();
-  uint32_t xw[128];  // xw[i] = x_{i-128+j}
-#pragma unroll
-  for (int i = 0; i < 128; ++i) xw[i] = lds.win[lane + i];
-#pragma unroll 1
-  for (uint32_t c = wave; c < 64u; c += kSegWaves) {
-    const uint32_t hlo = (uint32_t)__builtin_amdgcn_readlane(h_lo, (int)c);
-    const uint32_t hhi = (uint32_t)__builtin_amdgcn_readlane(h_hi, (int)c);
-    uint32_t alo = 0u, ahi = 0u;
-#pragma unroll
-    for (int i = 0; i < 64; ++i) {
-      const uint32_t bits = i < 32 ? hlo : hhi;
-      const uint32_t m = (uint32_t)((int32_t)(bits << (31 - (i & 31))) >> 31);  // bit i of h_c, all ones or zero
-      alo = xor_and(alo, xw[i], m);
-      ahi = xor_and(ahi, xw[64 + i], m);
-    }
-    lds.acc[128u * c + lane] = alo;
-    lds.acc[128u * c + 64u + lane] = ahi;
-  }
-  __syncthreads();
-  if (wave == 0) {
-    uint32_t slo = lds.acc[128u * 63u + lane], shi = lds.acc[128u * 63u + 64u + lane];
-#pragma unroll 4
-    for (int c = 62; c >= 0; --c) {
-      Ring rc = ring_from(slo, shi);
-      const uint32_t nx = ring_step(rc, lane0);
-      slo = shi ^ lds.acc[128u * c + lane];
-      shi = nx ^ lds.acc[128u * c + 64u + lane];
-    }
-    s.prev = slo;
-    s.cur = shi;
-    s.weyl += (uint32_t)J * kOmega;
-    s.pos += J;
-  }
-  __syncthreads();  // win and acc are free again
-}
-
-// Few streams: one workgroup of kSegWaves wavefronts per stream.
-__global__ __launch_bounds__(kSegWaves * 64) void k_skip_wg(uint32_t *__restrict__ state, uint64_t first, uint64_t J,
-                                                            JumpPoly g) {
+// Few streams: one workgroup each.
+__global__ __launch_bounds__(kJumpWaves * 64, 4) void k_skip_wg(uint32_t *__restrict__ state, uint64_t first, uint64_t J,
+                                                             JumpPoly g) {
   __shared__ JumpLds lds;
+  const uint32_t lane = lane_id();
   const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   uint32_t *st = state + (first + blockIdx.x) * kStateWords;
   StreamState s = load_state(st);
-  const uint64_t h = g.w[lane_id()];  // lane c holds h_c
-  jump_state_wg(s, (int)(uint32_t)h, (int)(uint32_t)(h >> 32), J, lds, wave);
-  if (wave == 0) write_state(st, s.prev, s.cur, 0u, 0u, s.weyl, s.pos, lane_id());
+  const uint64_t h = g.w[lane];
+  const uint32_t y = jump_ring_wg(s, (uint32_t)h, (uint32_t)(h >> 32), lds, wave);
+  jump_weyl(s, J);
+  if (wave < 2) st[threadIdx.x] = y;
+  if (wave == 0) store_weyl_pos(st, s.weyl, s.pos, lane);
+}
+
+// Many streams by one J: a wavefront per stream, with G's fragments laid out
+// once per workgroup in LDS, 16 bytes per lane (tiles 2 and 3 of a block are
+// tiles 0 and 1 of the block before).  Per 64 words a wavefront spends about
+// 35 VALU instructions (step, bit transpose, expansion; some 110 cycles) beside
+// four matrix instructions (4 x 32 cycles); with four wavefronts per SIMD the
+// two together take 205 cycles.  4096 streams: 28 us, 65536: 392 us (70 and
+// 951 us with the window sums on the VALU).
+constexpr uint32_t kSkipWaves = 8;
+constexpr uint32_t kSkipQs = 2 * kJumpBlocks + 3;  // q from -1, and a block more than is used
+
+__global__ __launch_bounds__(kSkipWaves * 64, 4) void k_skip_many(uint32_t *__restrict__ state, uint64_t first,
+                                                               uint64_t count, uint64_t J, JumpPoly g) {
+  __shared__ uint4 frags[32 * kSkipQs];
+  __shared__ uint32_t gw[kJumpWords];
+  const uint32_t lane = lane_id();
+  if (threadIdx.x < 64) {
+    const uint64_t h = g.w[lane];
+    gw[2 * lane] = (uint32_t)h;
+    gw[2 * lane + 1] = (uint32_t)(h >> 32);
+  }
+  __syncthreads();
+  for (uint32_t i = threadIdx.x; i < 32 * kSkipQs; i += 64 * kSkipWaves)
+    frags[i] = dev::one_bits(dev::toeplitz_word(gw, kJumpWords, (int)(i / 32) - 1, dev::row_word(i % 32)));
+  __syncthreads();
+  const dev::TransposeLane tl = dev::transpose_lane(lane);
+  const bool lane0 = lane == 0;
+  const uint64_t waves = (uint64_t)gridDim.x * kSkipWaves;
+  for (uint64_t k = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6; k < count; k += waves) {
+    uint32_t *st = state + (first + k) * kStateWords;
+    StreamState s = load_state(st);
+    Ring r = ring_from(s.prev, s.cur);
+    dev::tile_t acc[4] = {};
+    uint4 a2 = make_uint4(0, 0, 0, 0), a3 = a2;
+    const uint4 *f = frags + lane;
+    uint4 a1 = f[0], a0 = f[32];  // q = 2 c - 1 + h, 2 c + h
+    uint4 b = dev::half_bits(dev::word_bits(s.prev, tl));
+    // Each trip multiplies block c while it prepares block c + 1 (x: its
+    // words), so that the VALU work fills the matrix instructions' time.
+    auto block = [&](uint32_t x) {
+      f += 64;
+      const uint4 n1 = f[0], n0 = f[32];
+      acc[0] = dev::mm_step(dev::frag(a0), dev::frag(b), acc[0]);
+      acc[1] = dev::mm_step(dev::frag(a1), dev::frag(b), acc[1]);
+      acc[2] = dev::mm_step(dev::frag(a2), dev::frag(b), acc[2]);
+      acc[3] = dev::mm_step(dev::frag(a3), dev::frag(b), acc[3]);
+      const uint4 bn = dev::half_bits(dev::word_bits(x, tl));
+      a2 = a0;
+      a3 = a1;
+      a0 = n0;
+      a1 = n1;
+      b = bn;
+    };
+    block(s.cur);
+#pragma unroll 2
+    for (uint32_t c = 2; c < kJumpBlocks; ++c) block(ring_step(r, lane0));
+    block(0u);
+    jump_weyl(s, J);
+    st[lane] = dev::tile_words(acc[0], acc[1], tl);
+    st[64 + lane] = dev::tile_words(acc[2], acc[3], tl);
+    store_weyl_pos(st, s.weyl, s.pos, lane);
+  }
+}
+
+__global__ __launch_bounds__(256) void k_skip_steps(uint32_t *__restrict__ state, uint64_t first, uint64_t count,
+                                                    uint64_t J) {
+  const uint64_t wid = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
+  if (wid >= count) return;
+  skip_by_stepping(state + (first + wid) * kStateWords, J);
 }
 
 // ---------------------------------------------------------------------------
@@ -767,24 +790,25 @@ struct SplitPlaces {
 // (b / count) 2^exp words (part 0: a copy) and leaves ring, Weyl value and
 // position in the part's place in the output.  Nothing else reads the streams'
 // states after this kernel, so k_split_* may write them back.
-__global__ __launch_bounds__(kSegWaves * 64) void k_split_starts(const uint32_t *__restrict__ state, uint64_t first,
-                                                                 uint32_t count, uint32_t exp,
-                                                                 const uint64_t *__restrict__ table,
-                                                                 uint32_t *__restrict__ out, SplitPlaces at) {
+__global__ __launch_bounds__(kJumpWaves * 64, 4) void k_split_starts(const uint32_t *__restrict__ state, uint64_t first,
+                                                                  uint32_t count, uint32_t exp,
+                                                                  const uint64_t *__restrict__ table,
+                                                                  uint32_t *__restrict__ out, SplitPlaces at) {
   __shared__ JumpLds lds;
   const uint32_t lane = lane_id();
   const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const uint32_t k = blockIdx.x / count, i = blockIdx.x % count;
   StreamState s = load_state(state + (first + i) * kStateWords);
-  if (k) {
-    const uint64_t h = table[(uint64_t)split_entry(exp, k) * 64 + lane];  // lane c holds h_c
-    jump_state_wg(s, (int)(uint32_t)h, (int)(uint32_t)(h >> 32), (uint64_t)k << exp, lds, wave);
-  }
-  if (wave != 0) return;
   uint32_t *o = out + i * at.row + k * at.part;
-  o[lane] = s.prev;
-  o[at.chunk + lane] = s.cur;
-  if (lane < 3u) o[2 * at.chunk + lane] = lane == 0 ? s.weyl : (uint32_t)(s.pos >> (32u * (lane - 1u)));
+  if (k) {
+    const uint64_t h = table[(uint64_t)split_entry(exp, k) * 64 + lane];
+    const uint32_t y = jump_ring_wg(s, (uint32_t)h, (uint32_t)(h >> 32), lds, wave);
+    jump_weyl(s, (uint64_t)k << exp);
+    if (wave < 2) o[wave * at.chunk + lane] = y;
+  } else if (wave < 2) {
+    o[wave * at.chunk + lane] = wave ? s.cur : s.prev;
+  }
+  if (wave == 0 && lane < 3u) o[2 * at.chunk + lane] = lane == 0 ? s.weyl : (uint32_t)(s.pos >> (32u * (lane - 1u)));
 }
 
 __device__ __forceinline__ StreamState load_split(const uint32_t *o, uint64_t chunk) {
@@ -864,13 +888,13 @@ __device__ __forceinline__ bool seg_entry_ok(const xg_request &q, uint64_t num_s
 // skipped (the batch kernel skips those too).  The batch kernel then starts
 // each segment from its slot, so no segment reads a stream state that the
 // request's last segment rewrites.
-__global__ __launch_bounds__(kSegWaves * 64) void k_seg_starts(const uint32_t *__restrict__ state,
-                                                               uint64_t num_streams,
-                                                               const xg_request *__restrict__ reqs,
-                                                               const uint32_t *__restrict__ work,
-                                                               SegmentArgs seg) {
+__global__ __launch_bounds__(kJumpWaves * 64, 4) void k_seg_starts(const uint32_t *__restrict__ state,
+                                                                uint64_t num_streams,
+                                                                const xg_request *__restrict__ reqs,
+                                                                const uint32_t *__restrict__ work,
+                                                                SegmentArgs seg) {
   // One workgroup per segment entry (grid-stride over the table); the jump by
-  // k L words is jump_state_wg with the polynomial of table entry k - 1.
+  // k L words is jump_ring_wg with the polynomial of table entry k - 1.
   __shared__ JumpLds lds;
   const uint32_t lane = lane_id();
   const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -883,10 +907,14 @@ __global__ __launch_bounds__(kSegWaves * 64) void k_seg_starts(const uint32_t *_
     StreamState s = load_state(state + q.stream * kStateWords);
     uint32_t *dst = seg.stage + (uint64_t)slot * kStateWords;
     if (k) {
-      const uint64_t h = seg.jump_table[(uint64_t)(k - 1) * 64 + lane];  // lane c holds h_c
-      jump_state_wg(s, (int)(uint32_t)h, (int)(uint32_t)(h >> 32), (uint64_t)k * seg.seg_words, lds, wave);
+      const uint64_t h = seg.jump_table[(uint64_t)(k - 1) * 64 + lane];
+      const uint32_t y = jump_ring_wg(s, (uint32_t)h, (uint32_t)(h >> 32), lds, wave);
+      jump_weyl(s, (uint64_t)k * seg.seg_words);
+      if (wave < 2) dst[threadIdx.x] = y;
+    } else if (wave < 2) {
+      dst[threadIdx.x] = wave ? s.cur : s.prev;
     }
-    if (wave == 0) write_state(dst, s.prev, s.cur, 0u, 0u, s.weyl, s.pos, lane);
+    if (wave == 0) store_weyl_pos(dst, s.weyl, s.pos, lane);
   }
 }
 
@@ -1055,20 +1083,17 @@ hipError_t launch_box_muller(const uint32_t *words, uint64_t pairs, float *out, 
 
 hipError_t launch_skip(uint32_t *state, uint64_t first, uint64_t count, uint64_t J, const JumpPoly *g,
                        int num_cus, hipStream_t stream) {
-  hipError_t e = hipSuccess;
-  const dim3 grid((uint32_t)((count + 3) / 4)), block(256);
-  if (g && count <= (uint64_t)(num_cus > 0 ? num_cus : 1) * kSegBlocksPerCu) {
-    // Streams that all fit on the chip at once as workgroup jumps: each jump
-    // takes about a quarter of one wavefront's time.
-    e = launch(k_skip_wg, dim3((uint32_t)count), dim3(kSegWaves * 64), 0, stream, state, first, J, *g);
-  } else if (g) {
-    e = launch((k_skip<true>), grid, block, 4 * 1024, stream, state, first, count, J, *g);
-  } else {
-    JumpPoly none;
-    for (int i = 0; i < 64; ++i) none.w[i] = 0;
-    e = launch((k_skip<false>), grid, block, 0, stream, state, first, count, J, none);
-  }
-  return e;
+  const uint64_t cus = num_cus > 0 ? (uint64_t)num_cus : 1;
+  if (!g)
+    return launch(k_skip_steps, dim3((uint32_t)((count + 3) / 4)), dim3(256), 0, stream, state, first, count, J);
+  // Up to four streams per compute unit a workgroup each (7.0 us up to one, 9
+  // up to two, 12.7 up to three, 16.0 at four), beyond that a wavefront each
+  // (16.8 us up to eight, 30 us at sixteen).
+  if (count <= 4 * cus)
+    return launch(k_skip_wg, dim3((uint32_t)count), dim3(kJumpWaves * 64), 0, stream, state, first, J, *g);
+  const uint64_t blocks = (count + kSkipWaves - 1) / kSkipWaves;
+  return launch(k_skip_many, dim3((uint32_t)(blocks < 2 * cus ? blocks : 2 * cus)), dim3(kSkipWaves * 64), 0, stream,
+                state, first, count, J, *g);
 }
 
 hipError_t launch_generate(Kind kind, const Shape &shape, uint32_t *state, uint64_t first,
@@ -1092,7 +1117,7 @@ hipError_t launch_split(Kind kind, bool fill, const Split &sp, uint32_t *state, 
   uint32_t *o = static_cast<uint32_t *>(out);
   const uint64_t part = 1ull << sp.exp;
   const SplitPlaces at = fill ? SplitPlaces{64, part * count, 64 * count} : SplitPlaces{n, part, 64};
-  hipError_t e = launch(k_split_starts, dim3((uint32_t)waves), dim3(kSegWaves * 64), 0, stream, state, first, count,
+  hipError_t e = launch(k_split_starts, dim3((uint32_t)waves), dim3(kJumpWaves * 64), 0, stream, state, first, count,
                         sp.exp, table, o, at);
   if (e != hipSuccess) return e;
   auto run = [&](auto kernel) {
@@ -1118,9 +1143,9 @@ hipError_t launch_seg_starts(const uint32_t *state, uint64_t num_streams, const 
   if (max_entries == 0) return hipSuccess;
   // As many workgroups as fit on the chip at once, each taking every
   // gridDim-th entry.
-  const uint32_t slots = (num_cus > 0 ? (uint32_t)num_cus : 1u) * kSegBlocksPerCu;
+  const uint32_t slots = (num_cus > 0 ? (uint32_t)num_cus : 1u) * kJumpBlocksPerCu;
   const uint32_t blocks = max_entries < slots ? max_entries : slots;
-  return launch(k_seg_starts, dim3(blocks), dim3(kSegWaves * 64), 0, stream, state, num_streams, reqs, work, seg);
+  return launch(k_seg_starts, dim3(blocks), dim3(kJumpWaves * 64), 0, stream, state, num_streams, reqs, work, seg);
 }
 
 hipError_t launch_batch(const Shape &shape, int num_cus, uint32_t *state, uint64_t num_streams,
