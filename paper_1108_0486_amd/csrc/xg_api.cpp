@@ -129,15 +129,38 @@ xg::Shape plain_shape(const xg_ctx *ctx, uint64_t count, xg::Kind kind, bool fil
 }
 
 // The parts of a plain launch (xg_split.h), none unless the launch shape is
-// automatic.  A row of 2^15 words takes one wavefront 17 us; jumping to the
-// parts' starts and running them takes 11 us and then grows hardly at all
-// (2^20 words of one stream: 544 us on one wavefront, 10.5 us in 256 parts;
-// 24 streams of 100 003: 63 and 18 us).  With more than half the chip's SIMDs
-// at work already a second wavefront on some of them gains too little.
+// automatic.  Where the parts begin to pay (times in us, split and whole):
+//   one stream     R128 words 2^15: 9.9, 16.7; normals 2^14: 10, 16
+//                  r64 w32 words 2^14: 11, 24; w64 words 2^14: 19, 29
+//   200 streams    R128 words 2^16: 29, 34; w64 words 2^17: 85, 172
+//   512 streams    R128 words 2^17: 51, 64; normals 2^16: 44, 61
+// and 2^20 words of one stream take 10.5 us in 256 parts, 544 whole.
 xg::Split split_for(const xg_ctx *ctx, xg::Kind kind, uint64_t count, uint64_t n) {
   if (!ctx->split_table || ctx->plain.waves_per_block || ctx->plain.unroll || kind == xg::kMoments) return {};
-  const uint64_t slots = 4 * (uint64_t)(ctx->num_cus > 0 ? ctx->num_cus : 1);
-  return xg::plan_split(count, n, slots, 1ull << 15);
+  const uint64_t waves = paper_member(ctx) ? count : (count + 1) / 2;
+  return xg::plan_split(waves, n, ctx->num_cus > 0 ? (uint64_t)ctx->num_cus : 1,
+                        xg::kSplitCost[ctx->family][kind == xg::kNormal]);
+}
+
+// A launch over streams [first, first + count), whose arguments were checked.
+xg_status run_plain(xg_ctx *ctx, xg::Kind kind, bool fill_layout, uint64_t first, uint64_t count, uint64_t n, void *out,
+                    void *stream) {
+  const hipStream_t s = static_cast<hipStream_t>(stream);
+  const xg::Split sp = split_for(ctx, kind, count, n);
+  unsigned char *state = reinterpret_cast<unsigned char *>(ctx->d_state);
+  const xg::Shape shape = plain_shape(ctx, count, kind, fill_layout);
+  hipError_t e;
+  if (ctx->family != XG_FAMILY_R128_W32)
+    e = sp.parts ? xg::launch_family_split(ctx->family, kind, fill_layout, sp, state, first, count, n,
+                                           ctx->split_table, out, ctx->num_cus, s)
+                 : xg::launch_family_generate(ctx->family, kind, fill_layout, shape, state, first, count, n, out, s);
+  else if (sp.parts)
+    e = xg::launch_split(kind, fill_layout, sp, ctx->d_state, first, count, n, ctx->split_table, out, ctx->num_cus, s);
+  else if (fill_layout)
+    e = xg::launch_fill(kind, shape, ctx->d_state, first, count, n, static_cast<uint32_t *>(out), s);
+  else
+    e = xg::launch_generate(kind, shape, ctx->d_state, first, count, n, out, ctx->num_cus, s);
+  return e == hipSuccess ? XG_OK : XG_EHIP;
 }
 
 // u32 / f32 (and u64 / f64) of the further members, both layouts.
@@ -148,50 +171,24 @@ xg_status family_words(xg_ctx *ctx, xg::Kind kind, bool fill_layout, uint64_t fi
   if (ctx->family != (w64 ? XG_FAMILY_R64_W64 : XG_FAMILY_R64_W32)) return XG_ENOTSUP;
   xg_status st = check_range(ctx, first, count, n, out, n, w64 ? 8 : 4);
   if (st != XG_OK || n == 0) return st;
-  const hipError_t e = xg::launch_family_generate(ctx->family, kind, fill_layout, plain_shape(ctx, count, kind, fill_layout),
-                                                  reinterpret_cast<unsigned char *>(ctx->d_state), first, count,
-                                                  n, out, static_cast<hipStream_t>(stream));
-  return e == hipSuccess ? XG_OK : XG_EHIP;
+  return run_plain(ctx, kind, fill_layout, first, count, n, out, stream);
 }
 
 xg_status plain(xg_ctx *ctx, xg::Kind kind, uint64_t first, uint64_t count, uint64_t n, void *out,
                 void *stream) {
-  if (ctx && ctx->family == XG_FAMILY_R64_W32) {
-    if (kind == xg::kU32 || kind == xg::kF32) return family_words(ctx, kind, false, first, count, n, out, stream);
-    // normals and their fused moments (kNormal, kMoments)
-    xg_status st = check_range(ctx, first, count, n, out, kind == xg::kMoments ? 2 : n);
-    if (st != XG_OK || n == 0) return st;
-    const hipError_t e = xg::launch_family_generate(ctx->family, kind, false, plain_shape(ctx, count, kind, false),
-                                                    reinterpret_cast<unsigned char *>(ctx->d_state), first, count,
-                                                    n, out, static_cast<hipStream_t>(stream));
-    return e == hipSuccess ? XG_OK : XG_EHIP;
-  }
-  if (ctx && !paper_member(ctx)) return XG_ENOTSUP;
-  const uint64_t per_stream = kind == xg::kMoments ? 2 : n;
-  xg_status st = check_range(ctx, first, count, n, out, per_stream);
+  // The 32-bit members alike; the 64-bit member has calls of its own.
+  if (ctx && ctx->family == XG_FAMILY_R64_W64) return XG_ENOTSUP;
+  xg_status st = check_range(ctx, first, count, n, out, kind == xg::kMoments ? 2 : n);
   if (st != XG_OK || n == 0) return st;
-  const xg::Split sp = split_for(ctx, kind, count, n);
-  if (sp.parts)
-    return xg::launch_split(kind, false, sp, ctx->d_state, first, count, n, ctx->split_table, out, ctx->num_cus,
-                            static_cast<hipStream_t>(stream)) == hipSuccess ? XG_OK : XG_EHIP;
-  const hipError_t e = xg::launch_generate(kind, plain_shape(ctx, count, kind, false), ctx->d_state, first, count,
-                                           n, out, ctx->num_cus, static_cast<hipStream_t>(stream));
-  return e == hipSuccess ? XG_OK : XG_EHIP;
+  return run_plain(ctx, kind, false, first, count, n, out, stream);
 }
 
 xg_status fill(xg_ctx *ctx, xg::Kind kind, uint64_t first, uint64_t count, uint64_t n, void *out,
                void *stream) {
-  if (ctx && ctx->family == XG_FAMILY_R64_W32) return family_words(ctx, kind, true, first, count, n, out, stream);
-  if (ctx && !paper_member(ctx)) return XG_ENOTSUP;
+  if (ctx && ctx->family == XG_FAMILY_R64_W64) return XG_ENOTSUP;
   xg_status st = check_range(ctx, first, count, n, out, n);
   if (st != XG_OK || n == 0) return st;
-  const xg::Split sp = split_for(ctx, kind, count, n);
-  if (sp.parts)
-    return xg::launch_split(kind, true, sp, ctx->d_state, first, count, n, ctx->split_table, out, ctx->num_cus,
-                            static_cast<hipStream_t>(stream)) == hipSuccess ? XG_OK : XG_EHIP;
-  const hipError_t e = xg::launch_fill(kind, plain_shape(ctx, count, kind, true), ctx->d_state, first, count, n,
-                                       static_cast<uint32_t *>(out), static_cast<hipStream_t>(stream));
-  return e == hipSuccess ? XG_OK : XG_EHIP;
+  return run_plain(ctx, kind, true, first, count, n, out, stream);
 }
 
 // FP64 normals (kNormal: n doubles per stream) or their fused sums
@@ -202,10 +199,7 @@ xg_status normals_f64(xg_ctx *ctx, xg::Kind kind, uint64_t first, uint64_t count
   if (ctx->family != XG_FAMILY_R64_W64) return XG_ENOTSUP;
   const xg_status st = check_range(ctx, first, count, n, d_out, kind == xg::kMoments ? 2 : n, 8);
   if (st != XG_OK || n == 0) return st;
-  const hipError_t e = xg::launch_family_generate(ctx->family, kind, false, plain_shape(ctx, count, kind, false),
-                                                  reinterpret_cast<unsigned char *>(ctx->d_state), first, count,
-                                                  n, d_out, static_cast<hipStream_t>(stream));
-  return e == hipSuccess ? XG_OK : XG_EHIP;
+  return run_plain(ctx, kind, false, first, count, n, d_out, stream);
 }
 
 bool tune_to_shape(const xg_tune *t, uint32_t blocks_per_cu, xg::Shape *s) {
@@ -383,7 +377,7 @@ xg_status xg_skip(xg_ctx *ctx, uint64_t first, uint64_t count, uint64_t J, void 
     e = xg::launch_skip(ctx->d_state, first, count, J, step ? nullptr : &g, ctx->num_cus, s);
   else
     e = xg::launch_family_skip(ctx->family, reinterpret_cast<unsigned char *>(ctx->d_state), first, count, J,
-                               step ? nullptr : &g, s);
+                               step ? nullptr : &g, ctx->num_cus, s);
   return e == hipSuccess ? XG_OK : XG_EHIP;
 }
 

@@ -26,6 +26,7 @@
 #include <type_traits>
 
 #include "xg_device.h"
+#include "xg_jump_mm.h"
 #include "xg_normal.h"
 #include "xg_normal_f64.h"
 #include "xg_internal.h"
@@ -193,28 +194,49 @@ __global__ __launch_bounds__(256) void k_fam_init(unsigned char *__restrict__ st
   store_state<M>(state + L.k * M::state_bytes, L, g.prev, g.cur, word(0), 0u, w0 + word(256) * M::omega, 0ull);
 }
 
-// n words of one stream per half-wavefront from its state at st: the full
+// A stream's state held by its half of a wavefront: ring words j and 32 + j,
+// the Weyl value W_{pos-1} and the position.
+template <class M>
+struct FamState {
+  typename M::word prev = 0, cur = 0, weyl = 0;
+  uint64_t pos = 0;
+};
+
+template <class M>
+__device__ __forceinline__ FamState<M> fam_load(const unsigned char *__restrict__ st, bool on, const Lanes &L) {
+  using word = typename M::word;
+  FamState<M> s;
+  if (on) {
+    const word *ring = reinterpret_cast<const word *>(st);
+    s.prev = ring[L.j];
+    s.cur = ring[32 + L.j];
+    s.weyl = *reinterpret_cast<const word *>(st + M::weyl_off);
+    s.pos = *reinterpret_cast<const uint64_t *>(st + M::pos_off);
+  }
+  return s;
+}
+
+template <bool NT, class T>
+__device__ __forceinline__ void store_value(T v, T *p) {
+  if constexpr (NT) __builtin_nontemporal_store(v, p);
+  else *p = v;
+}
+
+// n words of one stream per half-wavefront from state s0: the full
 // steps go to o, o + stride, ... (o already offset to word j of the step),
 // the ragged last step (rem = n mod 32 words) to tail + j, or after the full
-// steps when tail is NULL.  on = false masks this lane's loads and stores
-// (that half's stream is absent); n is wave-uniform.
-template <class M, uint32_t KIND, int UNROLL>
-__device__ __forceinline__ void fam_run(unsigned char *__restrict__ st, bool on, Lanes L, uint64_t n,
-                                        typename M::word *__restrict__ o, uint64_t stride,
+// steps when tail is NULL; the end state goes to st.  on = false masks this
+// lane's stores (that half's stream is absent), keep = false leaves st as it
+// is; n is wave-uniform.  NT: non-temporal stores.
+template <class M, uint32_t KIND, int UNROLL, bool NT = true>
+__device__ __forceinline__ void fam_run(const FamState<M> &s0, unsigned char *__restrict__ st, bool on, bool keep,
+                                        Lanes L, uint64_t n, typename M::word *__restrict__ o, uint64_t stride,
                                         typename M::word *__restrict__ tail) {
   using word = typename M::word;
-  L.active = on;
-  const word *ring = reinterpret_cast<const word *>(st);
-  word prev = 0, cur = 0, w_start = 0;
-  uint64_t pos = 0;
-  if (on) {
-    prev = ring[L.j];
-    cur = ring[32 + L.j];
-    w_start = *reinterpret_cast<const word *>(st + M::weyl_off);
-    pos = *reinterpret_cast<const uint64_t *>(st + M::pos_off);
-  }
+  L.active = on && keep;
+  const word w_start = s0.weyl;
   Ring2<M> g;
-  g.open(prev, cur);
+  g.open(s0.prev, s0.cur);
   const bool word0 = L.j == 0;
   const word wlane = word(L.j + 1u) * M::omega;  // W_{p+j} = W_{p-1} + (j + 1) omega
   word wbase = w_start;
@@ -227,7 +249,7 @@ __device__ __forceinline__ void fam_run(unsigned char *__restrict__ st, bool on,
       const word x = g.step(word0);
       const word w = wbase + wlane;
       wbase += word(kStep) * M::omega;
-      if (on) __builtin_nontemporal_store(map_out<M, KIND>(x + (word)(w ^ (w >> M::gamma))), o + u * stride);
+      if (on) store_value<NT>(map_out<M, KIND>(x + (word)(w ^ (w >> M::gamma))), o + u * stride);
     }
     o += UNROLL * stride;
   }
@@ -235,7 +257,7 @@ __device__ __forceinline__ void fam_run(unsigned char *__restrict__ st, bool on,
     const word x = g.step(word0);
     const word w = wbase + wlane;
     wbase += word(kStep) * M::omega;
-    if (on) __builtin_nontemporal_store(map_out<M, KIND>(x + (word)(w ^ (w >> M::gamma))), o);
+    if (on) store_value<NT>(map_out<M, KIND>(x + (word)(w ^ (w >> M::gamma))), o);
     o += stride;
   }
   const word p0 = g.prev, c0 = g.cur;
@@ -244,9 +266,9 @@ __device__ __forceinline__ void fam_run(unsigned char *__restrict__ st, bool on,
     x = g.step(word0);
     const word w = wbase + wlane;
     word *t = tail ? tail : o;
-    if (on && L.j < rem) __builtin_nontemporal_store(map_out<M, KIND>(x + (word)(w ^ (w >> M::gamma))), t);
+    if (on && L.j < rem) store_value<NT>(map_out<M, KIND>(x + (word)(w ^ (w >> M::gamma))), t);
   }
-  store_state<M>(st, L, p0, c0, x, rem, w_start + (word)n * M::omega, pos + n);
+  store_state<M>(st, L, p0, c0, x, rem, w_start + (word)n * M::omega, s0.pos + n);
 }
 
 // n words of each of `count` streams (launch index k = stream first + k).
@@ -264,9 +286,9 @@ __device__ __forceinline__ void fam_serve(unsigned char *__restrict__ state, con
   unsigned char *st = state + (first + L.k) * M::state_bytes;
   if constexpr (FILL) {
     word *tail = out + (n / kStep) * count * kStep + L.k * (n % kStep) + L.j;
-    fam_run<M, KIND, UNROLL>(st, on, L, n, out + L.k * kStep + L.j, count * kStep, tail);
+    fam_run<M, KIND, UNROLL>(fam_load<M>(st, on, L), st, on, true, L, n, out + L.k * kStep + L.j, count * kStep, tail);
   } else {
-    fam_run<M, KIND, UNROLL>(st, on, L, n, out + L.k * n + L.j, kStep, nullptr);
+    fam_run<M, KIND, UNROLL>(fam_load<M>(st, on, L), st, on, true, L, n, out + L.k * n + L.j, kStep, nullptr);
   }
 }
 
@@ -345,21 +367,15 @@ __device__ __forceinline__ void sums_add(MomentsF64 &m, double z0, double z1) {
   kahan_add_f64(m.s2, m.c2, fma(z1, z1, z0 * z0));
 }
 
-template <bool NT, class T>
-__device__ __forceinline__ void store_normal(T v, T *p) {
-  if constexpr (NT) __builtin_nontemporal_store(v, p);
-  else *p = v;
-}
-
 template <class M>
 using real_of = typename std::conditional<sizeof(typename M::word) == 8, double, float>::type;
 
-// n normals of the stream at st per half-wavefront (n wave-uniform), from
+// n normals of one stream per half-wavefront (n wave-uniform) from state s0,
 // 2 ceil(n / 2) words: Box-Muller on consecutive pairs, written from o_s
 // (the stream's first output) unless MOMENTS, which instead reduces the
-// half's sums of z and z^2 and stores them at sums (two reals).  on = false
-// masks this lane's loads and stores; BOTH: on is true on every lane.
-// NT: non-temporal stores.
+// half's sums of z and z^2 and stores them at sums (two reals); the end state
+// goes to st.  on = false masks this lane's stores, BOTH: on is true on every
+// lane; keep = false leaves st as it is.  NT: non-temporal stores.
 //
 // The blocks wholly below n run UNROLL at a time without a test per value, and
 // a pair's two adjacent stores become one (which needs the alignment of one
@@ -367,24 +383,18 @@ using real_of = typename std::conditional<sizeof(typename M::word) == 8, double,
 // separate stores per pair took 570 us for 3001 streams x 65537 FP32 normals,
 // this form 235 us.
 template <class M, bool MOMENTS, bool BOTH, bool NT>
-__device__ __forceinline__ void fam_normals_run(unsigned char *__restrict__ st, bool on, Lanes L, uint64_t n,
-                                                real_of<M> *__restrict__ o_s, real_of<M> *__restrict__ sums) {
+__device__ __forceinline__ void fam_normals_run(const FamState<M> &s0, unsigned char *__restrict__ st, bool on,
+                                                bool keep, Lanes L, uint64_t n, real_of<M> *__restrict__ o_s,
+                                                real_of<M> *__restrict__ sums) {
   using word = typename M::word;
   using real = real_of<M>;
   constexpr bool kW64 = sizeof(word) == 8;
   if constexpr (BOTH) on = true;
-  L.active = on;
-  word prev = 0, cur = 0, w_start = 0;
-  uint64_t pos = 0;
-  if (on) {
-    const word *ring = reinterpret_cast<const word *>(st);
-    prev = ring[L.j];
-    cur = ring[32 + L.j];
-    w_start = *reinterpret_cast<const word *>(st + M::weyl_off);
-    pos = *reinterpret_cast<const uint64_t *>(st + M::pos_off);
-  }
+  L.active = on && keep;
+  const word w_start = s0.weyl;
+  const uint64_t pos = s0.pos;
   Ring2<M> g;
-  g.open(prev, cur);
+  g.open(s0.prev, s0.cur);
   const bool word0 = L.j == 0;
   const word wlane = word(L.j + 1u) * M::omega;
   word wbase = w_start;
@@ -421,8 +431,8 @@ __device__ __forceinline__ void fam_normals_run(unsigned char *__restrict__ st, 
     for (int u = 0; u < UNROLL; ++u) {
       if constexpr (!MOMENTS) {
         if (on) {
-          store_normal<NT>(z0[u], p + 64 * u);
-          store_normal<NT>(z1[u], p + 64 * u + 1);
+          store_value<NT>(z0[u], p + 64 * u);
+          store_value<NT>(z1[u], p + 64 * u + 1);
         }
       } else if constexpr (kW64) {
         sums_add(m, z0[u], z1[u]);
@@ -443,8 +453,8 @@ __device__ __forceinline__ void fam_normals_run(unsigned char *__restrict__ st, 
     if constexpr (MOMENTS) {
       if (has0) sums_add(m, z0, has1 ? z1 : real(0));  // has1 implies has0
     } else {
-      if (has0) store_normal<NT>(z0, o_s + idx);
-      if (has1) store_normal<NT>(z1, o_s + idx + 1);
+      if (has0) store_value<NT>(z0, o_s + idx);
+      if (has1) store_value<NT>(z1, o_s + idx + 1);
     }
   };
   for (; b != nblk; ++b) {
@@ -512,8 +522,8 @@ __global__ __launch_bounds__(1024) void k_fam_normals(unsigned char *__restrict_
   unsigned char *st = state + (first + L.k) * M::state_bytes;
   real *out = MOMENTS ? nullptr : static_cast<real *>(out_v) + L.k * n;
   real *sums = MOMENTS ? static_cast<real *>(sums_v) + 2 * L.k : nullptr;
-  if (2 * pair + 1 < count) fam_normals_run<M, MOMENTS, true, NT>(st, true, L, n, out, sums);
-  else fam_normals_run<M, MOMENTS, false, NT>(st, L.active, L, n, out, sums);
+  if (2 * pair + 1 < count) fam_normals_run<M, MOMENTS, true, NT>(fam_load<M>(st, true, L), st, true, true, L, n, out, sums);
+  else fam_normals_run<M, MOMENTS, false, NT>(fam_load<M>(st, L.active, L), st, L.active, true, L, n, out, sums);
 }
 
 template <class M, uint32_t KIND, int UNROLL, bool FILL>
@@ -706,11 +716,11 @@ __global__ __launch_bounds__(1024) void k_fam_batch(unsigned char *__restrict__ 
         unsigned char *st = state + (mine ? q.stream : 0) * M::state_bytes;
         const uint64_t at = mine ? q.out_offset + done : 0;
         if (kind == XG_NORMAL)
-          fam_normals_run<M, false, false, true>(st, mine, L, n, reinterpret_cast<real *>(out) + at, nullptr);
+          fam_normals_run<M, false, false, true>(fam_load<M>(st, mine, L), st, mine, true, L, n, reinterpret_cast<real *>(out) + at, nullptr);
         else if (kind == XG_F32)
-          fam_run<M, kReal, UNROLL>(st, mine, L, n, out + at + L.j, kStep, nullptr);
+          fam_run<M, kReal, UNROLL>(fam_load<M>(st, mine, L), st, mine, true, L, n, out + at + L.j, kStep, nullptr);
         else
-          fam_run<M, kInt, UNROLL>(st, mine, L, n, out + at + L.j, kStep, nullptr);
+          fam_run<M, kInt, UNROLL>(fam_load<M>(st, mine, L), st, mine, true, L, n, out + at + L.j, kStep, nullptr);
         served += n;
         if (mine) {
           done += n;
@@ -823,6 +833,235 @@ __global__ __launch_bounds__(256) void k_fam_skip(unsigned char *__restrict__ st
   }
 }
 
+// ---------------------------------------------------------------------------
+// Jumps on the matrix cores (xg_jump_mm.h) by a workgroup per pair of streams,
+// and rows cut into parts (xg_split.h).
+// ---------------------------------------------------------------------------
+// r = 64 words, so the result has two tiles and the continuation n / 64 + 1
+// blocks; a 64-bit word's halves are two planes of 32 bits that share G.
+template <class M>
+struct FamJump {
+  static constexpr uint32_t kWaves = 8;
+  static constexpr uint32_t kRuns = kWaves / 2;                    // wavefronts of one stream
+  static constexpr uint32_t kPlanes = sizeof(typename M::word) / 4;
+  static constexpr uint32_t kBits = 64 * 32 * kPlanes;             // n
+  static constexpr uint32_t kBlocks = kBits / 64 + 1;
+  static constexpr uint32_t kWords = kBits / 32;                   // 32-bit words of z^J mod P
+  static constexpr int kQ0 = -1;                                   // G's first q (tile 1 of block 0)
+  static constexpr uint32_t kQs = 2 * kBlocks - kQ0;
+
+  struct Lds {
+    uint32_t s[2][kPlanes][64 * kBlocks];     // both streams' continuations by planes
+    uint32_t g[kWords];
+    uint32_t rows[32 * kQs];                  // toeplitz_word(q, row_word(rho)) at 32 (q - kQ0) + rho
+    uint32_t part[kWaves][kPlanes][64];       // each wavefront's share of the result
+  };
+
+  // G's rows of the polynomial g (its words in any memory).  Ends with a barrier.
+  static __device__ __forceinline__ void lay_out(const uint32_t *g, Lds &lds) {
+    __syncthreads();  // an earlier jump's reads of lds are done
+    for (uint32_t i = threadIdx.x; i < kWords; i += 64 * kWaves) lds.g[i] = g[i];
+    __syncthreads();
+    for (uint32_t i = threadIdx.x; i < 32 * kQs; i += 64 * kWaves)
+      lds.rows[i] = dev::toeplitz_word(lds.g, kWords, (int)(i / 32) + kQ0, dev::row_word(i % 32));
+    __syncthreads();
+  }
+
+  // The jump of the pair whose states are s0 (in the pair's lanes, on every
+  // wavefront), after lay_out: wavefront 0 runs the continuation, then each
+  // wavefront multiplies a run of one stream's blocks and the shares are
+  // added as words.  Thread 64 h + w, h < 2, returns word w of stream h.
+  // Every thread of the workgroup calls it.
+  static __device__ __forceinline__ typename M::word jump(const FamState<M> &s0, Lds &lds, const Lanes &L,
+                                                          uint32_t wave) {
+    using word = typename M::word;
+    const uint32_t lane = L.lane;
+    __syncthreads();  // an earlier jump's reads of s and part are done
+    if (wave == 0) {
+      auto put = [&](uint32_t c, word v) {
+        lds.s[L.h][0][kStep * c + L.j] = (uint32_t)v;
+        if constexpr (kPlanes == 2) lds.s[L.h][1][kStep * c + L.j] = (uint32_t)((uint64_t)v >> 32);
+      };
+      Ring2<M> g;
+      g.open(s0.prev, s0.cur);
+      put(0, s0.prev);
+      put(1, s0.cur);
+      const bool word0 = L.j == 0;
+#pragma unroll 4
+      for (uint32_t c = 2; c < 2 * kBlocks; ++c) put(c, g.step(word0));
+    }
+    __syncthreads();
+    const dev::TransposeLane tl = dev::transpose_lane(lane);
+    constexpr uint32_t kEach = kBlocks / kRuns, kMore = kBlocks % kRuns;  // the last kMore runs take one block more
+    static_assert(kMore == 1, "the last run takes the odd block");
+    const uint32_t h = wave & 1u, run = wave >> 1, c0 = kEach * run;
+    const uint32_t *rows = lds.rows + 32 * (2 * c0 - kQ0) + lane;  // tile t of block c: q = 2 c - t + h'
+    const uint32_t *bits = &lds.s[h][0][64 * c0 + lane];
+    dev::tile_t acc[kPlanes][2] = {};
+    auto block = [&]() {
+      const dev::frag_t a0 = dev::frag(dev::one_bits(rows[0])), a1 = dev::frag(dev::one_bits(rows[-32]));
+#pragma unroll
+      for (uint32_t p = 0; p < kPlanes; ++p) {
+        const dev::frag_t b = dev::frag(dev::half_bits(dev::word_bits(bits[64 * kBlocks * p], tl)));
+        acc[p][0] = dev::mm_step(a0, b, acc[p][0]);
+        acc[p][1] = dev::mm_step(a1, b, acc[p][1]);
+      }
+      rows += 64;
+      bits += 64;
+    };
+#pragma unroll 4
+    for (uint32_t i = 0; i < kEach; ++i) block();
+    if (run == kRuns - 1) block();
+#pragma unroll
+    for (uint32_t p = 0; p < kPlanes; ++p) lds.part[wave][p][lane] = dev::tile_words(acc[p][0], acc[p][1], tl);
+    __syncthreads();
+    uint32_t y[2] = {0, 0};
+    if (wave < 2) {
+#pragma unroll
+      for (uint32_t r = 0; r < kRuns; ++r)
+#pragma unroll
+        for (uint32_t p = 0; p < kPlanes; ++p) y[p] ^= lds.part[2 * r + wave][p][lane];
+    }
+    if constexpr (kPlanes == 2) return (uint64_t)y[0] | ((uint64_t)y[1] << 32);
+    else return y[0];
+  }
+};
+
+// Jumps by J: workgroups of 8 wavefronts, each taking every gridDim-th pair.
+template <class M>
+__global__ __launch_bounds__(FamJump<M>::kWaves * 64) void k_fam_skip_wg(unsigned char *__restrict__ state,
+                                                                         uint64_t first, uint64_t count, uint64_t J,
+                                                                         JumpPoly g) {
+  using word = typename M::word;
+  __shared__ typename FamJump<M>::Lds lds;
+  const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  FamJump<M>::lay_out(reinterpret_cast<const uint32_t *>(g.w), lds);
+  Lanes L;
+  L.lane = threadIdx.x & 63u;
+  L.h = L.lane & 1u;
+  L.j = L.lane >> 1;
+  for (uint64_t pair = blockIdx.x; 2 * pair < count; pair += gridDim.x) {
+    L.k = 2 * pair + L.h;
+    L.active = L.k < count;
+    const FamState<M> s0 = fam_load<M>(state + (first + L.k) * M::state_bytes, L.active, L);
+    const word y = FamJump<M>::jump(s0, lds, L, wave);
+    if (wave < 2 && 2 * pair + wave < count) {
+      unsigned char *st = state + (first + 2 * pair + wave) * M::state_bytes;
+      reinterpret_cast<word *>(st)[L.lane] = y;
+    }
+    if (wave == 0 && L.j == 0 && L.active) {
+      unsigned char *st = state + (first + L.k) * M::state_bytes;
+      *reinterpret_cast<word *>(st + M::weyl_off) = s0.weyl + (word)J * M::omega;
+      *reinterpret_cast<uint64_t *>(st + M::pos_off) = s0.pos + J;
+    }
+  }
+}
+
+// Where part k of the launch's i-th stream keeps its start state: word t at
+// out[i row + k part + (t / 32) chunk + t % 32]; W and pos follow the ring.
+struct FamPlaces {
+  uint64_t row, part, chunk;
+};
+
+template <class M>
+__global__ __launch_bounds__(FamJump<M>::kWaves * 64) void k_fam_split_starts(
+    const unsigned char *__restrict__ state, uint64_t first, uint32_t count, uint32_t exp,
+    const uint64_t *__restrict__ table, typename M::word *__restrict__ out, FamPlaces at) {
+  using word = typename M::word;
+  __shared__ typename FamJump<M>::Lds lds;
+  const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const uint32_t pairs = (count + 1) / 2, k = blockIdx.x / pairs, pair = blockIdx.x % pairs;
+  Lanes L;
+  L.lane = threadIdx.x & 63u;
+  L.h = L.lane & 1u;
+  L.j = L.lane >> 1;
+  L.k = 2 * pair + L.h;
+  L.active = L.k < count;
+  FamState<M> s0 = fam_load<M>(state + (first + L.k) * M::state_bytes, L.active, L);
+  word *mine = out + L.k * at.row + k * at.part;
+  if (k) {
+    FamJump<M>::lay_out(reinterpret_cast<const uint32_t *>(table + (uint64_t)split_entry(exp, k) * (FamJump<M>::kWords / 2)),
+                        lds);
+    const word y = FamJump<M>::jump(s0, lds, L, wave);
+    if (wave < 2 && 2 * pair + wave < count)
+      out[(2 * pair + wave) * at.row + k * at.part + (L.lane / 32) * at.chunk + L.lane % 32] = y;
+    const uint64_t by = (uint64_t)k << exp;
+    s0.weyl += (word)by * M::omega;
+    s0.pos += by;
+  } else if (wave == 0 && L.active) {
+    mine[L.j] = s0.prev;
+    mine[at.chunk + L.j] = s0.cur;
+  }
+  if (wave == 0 && L.active && L.j == 0) {
+    word *w = mine + 2 * at.chunk;
+    w[0] = s0.weyl;
+    w[1] = (word)s0.pos;
+    if constexpr (sizeof(word) == 4) w[2] = (word)(s0.pos >> 32);
+  }
+}
+
+// One wavefront per part and pair of streams, from the states that
+// k_fam_split_starts left; the last part writes the streams' end states.
+template <class M, uint32_t KIND, bool FILL>
+__global__ __launch_bounds__(256) void k_fam_split(unsigned char *__restrict__ state, uint64_t first, uint32_t count,
+                                                   uint64_t n, uint32_t parts, uint32_t exp, typename M::word *out,
+                                                   FamPlaces at) {
+  using word = typename M::word;
+  const uint32_t wid = (uint32_t)__builtin_amdgcn_readfirstlane((int)((blockIdx.x * blockDim.x + threadIdx.x) >> 6));
+  const uint32_t pairs = (count + 1) / 2, k = wid / pairs, pair = wid % pairs;
+  if (k >= parts) return;
+  Lanes L;
+  L.lane = threadIdx.x & 63u;
+  L.h = L.lane & 1u;
+  L.j = L.lane >> 1;
+  L.k = 2 * pair + L.h;
+  L.active = L.k < count;
+  const bool on = L.active, last = k + 1 == parts;
+  const uint64_t done = (uint64_t)k << exp, nk = last ? n - done : 1ull << exp;
+  word *o = out + L.k * at.row + k * at.part;
+  FamState<M> s0;
+  if (on) {
+    s0.prev = o[L.j];
+    s0.cur = o[at.chunk + L.j];
+    const word *w = o + 2 * at.chunk;
+    s0.weyl = w[0];
+    s0.pos = (uint64_t)w[1];
+    if constexpr (sizeof(word) == 4) s0.pos |= (uint64_t)w[2] << 32;
+  }
+  // Every word of the state is read before this wavefront writes over it.
+  unsigned char *st = state + (first + L.k) * M::state_bytes;
+  if constexpr (KIND == kNormal) {
+    fam_normals_run<M, false, false, false>(s0, st, on, last, L, nk, reinterpret_cast<real_of<M> *>(o), nullptr);
+  } else {
+    word *tail = FILL ? out + (n / kStep) * at.chunk + L.k * (n % kStep) + L.j : nullptr;
+    fam_run<M, KIND, 8, false>(s0, st, on, last, L, nk, o + L.j, FILL ? at.chunk : kStep, tail);
+  }
+}
+
+template <class M>
+hipError_t launch_fam_split(Kind kind, bool fill, const Split &sp, unsigned char *state, uint64_t first,
+                            uint64_t count, uint64_t n, const uint64_t *table, void *out, int num_cus,
+                            hipStream_t stream) {
+  using word = typename M::word;
+  constexpr uint32_t kInt = sizeof(word) == 4 ? kU32 : kU64, kReal = sizeof(word) == 4 ? kF32 : kF64;
+  const uint64_t waves = (count + 1) / 2 * sp.parts;
+  const uint64_t wpb = auto_waves_per_block(waves, num_cus);
+  word *o = static_cast<word *>(out);
+  const uint64_t part = 1ull << sp.exp;
+  const FamPlaces at = fill ? FamPlaces{kStep, part * count, kStep * count} : FamPlaces{n, part, kStep};
+  hipError_t e = launch(k_fam_split_starts<M>, dim3((uint32_t)waves), dim3(FamJump<M>::kWaves * 64), 0, stream, state,
+                        first, count, sp.exp, table, o, at);
+  if (e != hipSuccess) return e;
+  auto run = [&](auto kernel) {
+    return launch(kernel, dim3((uint32_t)((waves + wpb - 1) / wpb)), dim3((uint32_t)(wpb * kWave)), 0, stream, state,
+                  first, count, n, sp.parts, sp.exp, o, at);
+  };
+  if (kind == kNormal) return run(k_fam_split<M, kNormal, false>);
+  if (kind == kReal) return fill ? run(k_fam_split<M, kReal, true>) : run(k_fam_split<M, kReal, false>);
+  if (kind == kInt) return fill ? run(k_fam_split<M, kInt, true>) : run(k_fam_split<M, kInt, false>);
+  return hipErrorInvalidValue;
+}
+
 template <class M, uint32_t KIND, bool FILL>
 hipError_t launch_fam_k(uint32_t unroll, dim3 grid, dim3 block, unsigned char *state, uint64_t first,
                   uint64_t count, uint64_t n, void *out, hipStream_t stream) {
@@ -878,12 +1117,26 @@ hipError_t launch_family_init(uint32_t family, unsigned char *state, uint64_t nu
 }
 
 hipError_t launch_family_skip(uint32_t family, unsigned char *state, uint64_t first, uint64_t count, uint64_t J,
-                              const JumpPoly *g, hipStream_t stream) {
+                              const JumpPoly *g, int num_cus, hipStream_t stream) {
   hipError_t e = hipSuccess;
-  const uint64_t pairs = (count + 1) / 2;
+  const uint64_t pairs = (count + 1) / 2, cus = num_cus > 0 ? (uint64_t)num_cus : 1;
   const dim3 grid((uint32_t)((pairs + 3) / 4)), block(256);
   JumpPoly zero{};
   const JumpPoly &gp = g ? *g : zero;
+  // The matrix-core form while a workgroup takes at most a few pairs of
+  // streams: its continuation runs on one wavefront, where the other form runs
+  // one per pair (us, this form and the other: 32-bit member 1024 streams 9,
+  // 25; 4096 28, 29; 8192 52, 49; 64-bit member 1024 28, 78; 2048 51, 79; 4096
+  // 96, 91).
+  if (g && pairs <= (family == XG_FAMILY_R64_W32 ? 8 : 6) * cus) {
+    const dim3 wgrid((uint32_t)(pairs < 2 * cus ? pairs : 2 * cus));
+    auto run = [&](auto kernel, uint32_t waves) {
+      return launch(kernel, wgrid, dim3(waves * 64), 0, stream, state, first, count, J, gp);
+    };
+    if (family == XG_FAMILY_R64_W32) return run(k_fam_skip_wg<MemberN2048>, FamJump<MemberN2048>::kWaves);
+    if (family == XG_FAMILY_R64_W64) return run(k_fam_skip_wg<MemberW64>, FamJump<MemberW64>::kWaves);
+    return hipErrorInvalidValue;
+  }
   if (family == XG_FAMILY_R64_W32) {
     if (g) e = launch((k_fam_skip<MemberN2048, true>), grid, block, 4 * 192 * 4, stream, state, first, count, J, gp);
     else e = launch((k_fam_skip<MemberN2048, false>), grid, block, 0, stream, state, first, count, J, gp);
@@ -894,6 +1147,16 @@ hipError_t launch_family_skip(uint32_t family, unsigned char *state, uint64_t fi
     return hipErrorInvalidValue;
   }
   return e;
+}
+
+hipError_t launch_family_split(uint32_t family, Kind kind, bool fill, const Split &sp, unsigned char *state,
+                               uint64_t first, uint64_t count, uint64_t n, const uint64_t *table, void *out,
+                               int num_cus, hipStream_t stream) {
+  if (family == XG_FAMILY_R64_W32)
+    return launch_fam_split<MemberN2048>(kind, fill, sp, state, first, count, n, table, out, num_cus, stream);
+  if (family == XG_FAMILY_R64_W64)
+    return launch_fam_split<MemberW64>(kind, fill, sp, state, first, count, n, table, out, num_cus, stream);
+  return hipErrorInvalidValue;
 }
 
 hipError_t launch_family_generate(uint32_t family, Kind kind, bool fill, const Shape &shape, unsigned char *state,

@@ -139,7 +139,11 @@ hipError_t launch_family_generate(uint32_t family, Kind kind, bool fill, const S
 // stepping when g == nullptr, else by evaluating g(T) (g = z^J mod P, its
 // member_degree / 64 low words used).
 hipError_t launch_family_skip(uint32_t family, unsigned char *state, uint64_t first, uint64_t count, uint64_t J,
-                              const JumpPoly *g, hipStream_t stream);
+                              const JumpPoly *g, int num_cus, hipStream_t stream);
+// Split launch of a further member (kind: its integers, its reals, or kNormal).
+hipError_t launch_family_split(uint32_t family, Kind kind, bool fill, const Split &sp, unsigned char *state,
+                               uint64_t first, uint64_t count, uint64_t n, const uint64_t *table, void *out,
+                               int num_cus, hipStream_t stream);
 
 
 }  // namespace xg

@@ -44,22 +44,47 @@ struct Split {
   uint32_t exp = 0;
 };
 
+// What a launch's member and kind cost: picoseconds a wavefront takes per value of
+// a row, nanoseconds of a round of jumps (a workgroup per compute unit), and
+// the bytes of all wavefronts' values with one n (values of a wavefront: one
+// per stream, two streams for the r = 64 members).
+struct SplitCost {
+  uint32_t value_ps, round_ns, value_bytes;
+};
+constexpr uint64_t kSplitLaunchNs = 3000;  // a plain launch without its values
+constexpr uint64_t kSplitBaseNs = 5000;    // the two launches without jumps and values
+constexpr uint64_t kSplitBytesPerNs = 5000;  // what either form writes at best
+// Measured (a wavefront alone on its SIMD; 1 to 1024 workgroups).  By member
+// (XG_FAMILY_*), then words and normals.
+constexpr SplitCost kSplitCost[3][2] = {
+    {{470, 3200, 4}, {900, 3200, 4}},
+    {{1000, 4500, 8}, {1900, 4500, 8}},
+    {{1320, 14000, 16}, {4000, 14000, 16}},
+};
+
 // The parts of a launch of `waves` wavefronts (one per stream, or one per two
-// streams for the r = 64 members) with n values per stream: the shortest
-// parts that give no more than `slots` wavefronts in all.
-inline Split plan_split(uint64_t waves, uint64_t n, uint64_t slots, uint64_t min_n) {
+// streams for the r = 64 members) with n values per stream on `cus` compute
+// units: those of the least time by the costs above, with at most one
+// wavefront per SIMD; none where that saves less than a fifth, or where more
+// than half of the SIMDs have a wavefront as it is.
+inline Split plan_split(uint64_t waves, uint64_t n, uint64_t cus, const SplitCost &c) {
   Split s;
-  if (waves == 0 || n < min_n || 2 * waves > slots) return s;
-  uint64_t want = slots / waves;
-  if (want > kSplitMaxParts) want = kSplitMaxParts;
+  const uint64_t slots = 4 * cus;
+  if (waves == 0 || n < 2 * kSplitMinPart || 2 * waves > slots || n >> 40) return s;
+  const uint64_t write_ns = n * waves * c.value_bytes / kSplitBytesPerNs, whole_ns = n * c.value_ps / 1000;
+  uint64_t best = (kSplitLaunchNs + (whole_ns > write_ns ? whole_ns : write_ns)) * 4 / 5;
   for (uint32_t e = kSplitMinExp; e <= kSplitMaxExp; ++e) {
     const uint64_t parts = ((n - kSplitMinPart) >> e) + 1;
-    if (parts <= want) {
-      if (parts > 1) {
-        s.parts = (uint32_t)parts;
-        s.exp = e;
-      }
-      return s;
+    if (parts < 2) break;
+    if (parts > kSplitMaxParts || parts * waves > slots) continue;
+    const uint64_t last = n - ((parts - 1) << e), longest = last > (1ull << e) ? last : 1ull << e;
+    const uint64_t part_ns = longest * c.value_ps / 1000;
+    const uint64_t ns = kSplitBaseNs + (parts * waves + cus - 1) / cus * c.round_ns +
+                        (part_ns > write_ns ? part_ns : write_ns);
+    if (ns < best) {
+      best = ns;
+      s.parts = (uint32_t)parts;
+      s.exp = e;
     }
   }
   return s;

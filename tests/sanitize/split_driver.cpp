@@ -37,17 +37,17 @@ int main() {
   uint64_t split = 0;
   for (uint64_t waves : {1, 2, 3, 5, 24, 100, 255, 256, 257, 511, 512, 513, 1024, 100000})
     for (uint64_t n : sizes)
-      for (uint64_t min_n : {256ull, 1ull << 15}) {
-        const Split s = plan_split(waves, n, 1024, min_n);
+      for (int kind = 0; kind < 6; ++kind) {
+        const Split s = plan_split(waves, n, 256, kSplitCost[kind / 2][kind % 2]);
         if (!s.parts) continue;
         ++split;
-        CHECK(n >= min_n && s.parts > 1 && s.parts <= kSplitMaxParts && s.parts * waves <= 1024);
+        CHECK(s.parts > 1 && s.parts <= kSplitMaxParts && s.parts * waves <= 1024);
         CHECK(s.exp >= kSplitMinExp && s.exp <= kSplitMaxExp);
         const uint64_t done = (uint64_t)(s.parts - 1) << s.exp;
         CHECK(n > done && n - done >= kSplitMinPart && n - done < (1ull << s.exp) + kSplitMinPart);
       }
   CHECK(split > 1000);
-  CHECK(plan_split(0, 1 << 20, 1024, 256).parts == 0);
+  CHECK(plan_split(0, 1 << 20, 256, kSplitCost[0][0]).parts == 0);
 
   std::vector<int> seen(kSplitEntries, 0);
   for (uint32_t e = kSplitMinExp; e <= kSplitMaxExp; ++e)

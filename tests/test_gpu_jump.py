@@ -54,3 +54,26 @@ def test_jump_of_one_bit_states():
     g = O.poly_to_words(O.z_pow_mod(J, O.charpoly(O.PAPER)), 64)
     for i in range(S):
         assert (ring[i] == O.xpart_jump_poly(O.PAPER, ring0[i], g)).all(), i
+
+
+@pytest.mark.parametrize("family,params", [(1, O.R64), (2, O.W64)])
+@pytest.mark.parametrize("per_cu,more", [(1, 1), (6, 5), (20, 3)])
+def test_member_jump_forms_agree(family, params, per_cu, more):
+    """The further members: a few pairs of streams per workgroup, and beyond
+    that a wavefront per pair, with one stream alone in the last pair."""
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    S, J = per_cu * cus + more, (1 << 40) + 777
+    a, b = XorgensStreams(S, seed=21, family=family), XorgensStreams(S, seed=21, family=family)
+    a.skip(J)
+    for first in range(0, S, cus + 1):
+        b.skip(J, first=first, count=min(cus + 1, S - first))
+    assert torch.equal(a.state, b.state)
+    rows = [0, 1, S // 2, S - 1]
+    one = (lambda i: O.OracleStreams64(21 + i, 1, O.W64)) if family == 2 else (
+        lambda i: O.OracleStreams(21 + i, 1, params=O.R64))
+    g = O.poly_to_words(O.z_pow_mod(J, O.charpoly(params)), params.n // 64)
+    ring, weyl, pos = a.host_state(rows)
+    for j in range(len(rows)):
+        want = np.asarray(O.xpart_jump_poly(params, one(rows[j]).ring[0], g)).astype(ring.dtype)
+        assert (ring[j] == want).all(), rows[j]
+    assert (pos == np.uint64(J)).all()

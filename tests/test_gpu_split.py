@@ -15,7 +15,7 @@ from paper_1108_0486_amd import xg  # noqa: E402
 from paper_1108_0486_amd.streams import XorgensStreams, as_u32  # noqa: E402
 
 PART = 1 << 11   # the shortest part
-FAMILIES = [xg.XG_FAMILY_R128_W32]
+FAMILIES = [xg.XG_FAMILY_R128_W32, xg.XG_FAMILY_R64_W32, xg.XG_FAMILY_R64_W64]
 
 
 def _calls(family):
@@ -26,18 +26,18 @@ def _calls(family):
 
 @pytest.mark.parametrize("family", FAMILIES)
 @pytest.mark.parametrize("count,n", [
-    (1, 1 << 15),                    # the shortest row that is split
-    (1, (1 << 15) - 1),              # the longest that is not
+    (1, 3000),                       # too short to be split
     (1, 17 * PART + 255),            # the rest stays with the last part
     (1, 17 * PART + 256),            # the shortest last part
     (1, 17 * PART + 257),
+    (1, 1 << 15),
     (1, 256 * PART + 255),           # the most parts of the shortest length
     (1, 256 * PART + 256),           # the next length
     (3, 100_003),
     (2, 1 << 20),
-    (100, 40_001),
-    (512, 33_333),                   # the most streams
-    (513, 33_333),
+    (101, 40_001),
+    (512, 140_001),                  # the most streams (R128)
+    (1023, 140_001),                 # the most pairs of streams, one stream alone
 ])
 def test_split_equals_unsplit(family, count, n):
     """Every output bit and end state of every kind of call, from a position
