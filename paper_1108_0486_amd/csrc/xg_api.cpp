@@ -103,8 +103,10 @@ bool paper_member(const xg_ctx *ctx) { return ctx && ctx->family == XG_FAMILY_R1
 // uint32 / FP32 take 2 as well (u32 764-779 us against 828 us, f32 740-754
 // against 789-812 us, three boxes); its fills keep 8.
 // Those were measured with a wavefront on every SIMD; smaller launches (fewer
-// than 4 x CUs wavefronts, e.g. one stream per launch) keep unroll 8, as does
-// the 64-bit member.
+// than 4 x CUs wavefronts, e.g. one stream per launch) take unroll 8, as does
+// the 64-bit member.  Every automatic shape stores 4 bytes per lane.  Rows of
+// Section 2's member that take cached stores (cached_stores) have a kernel of their own,
+// unroll 8.
 xg::Shape plain_shape(const xg_ctx *ctx, uint64_t count, xg::Kind kind, bool fill_layout) {
   xg::Shape s = ctx->plain;
   const uint64_t waves = ctx->family == XG_FAMILY_R128_W32 ? count : (count + 1) / 2;
@@ -112,13 +114,13 @@ xg::Shape plain_shape(const xg_ctx *ctx, uint64_t count, xg::Kind kind, bool fil
     s.waves_per_block = ctx->family == XG_FAMILY_R64_W64 ? 1u : xg::auto_waves_per_block(waves, ctx->num_cus);
   if (s.unroll == 0) {
     s.unroll = 8;
+    s.store_words = 1;  // LDS-staged 16-byte stores are slower (512 x 2^16 uint32: 43 us against 34)
     const bool every_simd = waves >= 4 * (uint64_t)(ctx->num_cus > 0 ? ctx->num_cus : 1);
     if (ctx->family == XG_FAMILY_R128_W32 && every_simd && (kind == xg::kU32 || kind == xg::kF32)) {
       if (fill_layout) {
         s.unroll = kind == xg::kU32 ? 4u : 8u;
       } else {
         s.unroll = 2;
-        s.store_words = 1;
       }
     } else if (ctx->family == XG_FAMILY_R64_W32 && every_simd && !fill_layout &&
                (kind == xg::kU32 || kind == xg::kF32)) {
@@ -153,11 +155,14 @@ xg_status run_plain(xg_ctx *ctx, xg::Kind kind, bool fill_layout, uint64_t first
   if (ctx->family != XG_FAMILY_R128_W32)
     e = sp.parts ? xg::launch_family_split(ctx->family, kind, fill_layout, sp, state, first, count, n,
                                            ctx->split_table, out, ctx->num_cus, s)
-                 : xg::launch_family_generate(ctx->family, kind, fill_layout, shape, state, first, count, n, out, s);
+                 : xg::launch_family_generate(ctx->family, kind, fill_layout, shape, state, first, count, n, out,
+                                                  ctx->num_cus, s);
   else if (sp.parts)
     e = xg::launch_split(kind, fill_layout, sp, ctx->d_state, first, count, n, ctx->split_table, out, ctx->num_cus, s);
   else if (fill_layout)
     e = xg::launch_fill(kind, shape, ctx->d_state, first, count, n, static_cast<uint32_t *>(out), s);
+  else if (!ctx->plain.unroll && xg::cached_stores(kind, count, n, out, ctx->num_cus))
+    e = xg::launch_rows_cached(kind, shape.waves_per_block, ctx->d_state, first, count, n, out, ctx->num_cus, s);
   else
     e = xg::launch_generate(kind, shape, ctx->d_state, first, count, n, out, ctx->num_cus, s);
   return e == hipSuccess ? XG_OK : XG_EHIP;

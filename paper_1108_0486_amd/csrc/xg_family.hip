@@ -129,18 +129,25 @@ __device__ __forceinline__ typename M::word seed_word(uint64_t v) {
 struct Lanes {
   uint32_t lane, h, j;
   uint64_t k;    // stream index within the launch
-  bool active;   // k < count
+  bool active;   // whether this half writes its stream's state
 };
 
-__device__ __forceinline__ Lanes lanes_of(uint64_t count, uint32_t block) {
+// The lanes of a wavefront that serves pair `pair` of a launch's `count`
+// streams.  The last of an odd number of streams runs in both halves, which
+// then store the same values to the same places: cheaper than a mask on every
+// store of the loop.
+__device__ __forceinline__ Lanes pair_lanes(uint64_t pair, uint64_t count) {
   Lanes L;
   L.lane = threadIdx.x & 63u;
   L.h = L.lane & 1u;
   L.j = L.lane >> 1;
-  const uint64_t pair = ((uint64_t)block * blockDim.x + threadIdx.x) >> 6;
-  L.k = 2 * pair + L.h;
-  L.active = L.k < count;
+  L.k = 2 * pair + L.h < count ? 2 * pair + L.h : count - 1;
+  L.active = true;
   return L;
+}
+
+__device__ __forceinline__ uint64_t pair_of(uint32_t block) {
+  return ((uint64_t)block * blockDim.x + threadIdx.x) >> 6;
 }
 
 // Writes the 64-word window that ends `rem` words into chunk x (rem in 0..31)
@@ -177,8 +184,9 @@ template <class M>
 __global__ __launch_bounds__(256) void k_fam_init(unsigned char *__restrict__ state, uint64_t num_streams,
                                                   uint64_t seed) {
   using word = typename M::word;
-  const Lanes L = lanes_of(num_streams, blockIdx.x);
-  if (2 * (L.k >> 1) >= num_streams) return;  // wave-uniform: both streams of the pair absent
+  const uint64_t pair = pair_of(blockIdx.x);
+  if (2 * pair >= num_streams) return;  // wave-uniform
+  const Lanes L = pair_lanes(pair, num_streams);
   const uint64_t s = seed + L.k;
   word prev = seed_word<M>(splitmix64_at(s, L.j + 1u));
   word cur = seed_word<M>(splitmix64_at(s, L.j + 33u));
@@ -276,19 +284,18 @@ __device__ __forceinline__ void fam_run(const FamState<M> &s0, unsigned char *__
 // 32c .. 32c + 31) of stream k at out[(c count + k) 32 ..], the ragged last
 // chunks (rem = n mod 32 words each) packed after them at
 // out[32 (n / 32) count + k rem ..]; a wavefront's step then writes 64
-// adjacent words.  CHECK: the wavefront's second stream is absent (odd count,
-// last pair), so that half's loads and stores are masked.
-template <class M, uint32_t KIND, int UNROLL, bool FILL, bool CHECK>
+// adjacent words.  NT: non-temporal stores.
+template <class M, uint32_t KIND, int UNROLL, bool FILL, bool NT>
 __device__ __forceinline__ void fam_serve(unsigned char *__restrict__ state, const Lanes &L, uint64_t first,
                                           uint64_t count, uint64_t n, typename M::word *__restrict__ out) {
   using word = typename M::word;
-  const bool on = !CHECK || L.active;
   unsigned char *st = state + (first + L.k) * M::state_bytes;
+  const FamState<M> s0 = fam_load<M>(st, true, L);
   if constexpr (FILL) {
     word *tail = out + (n / kStep) * count * kStep + L.k * (n % kStep) + L.j;
-    fam_run<M, KIND, UNROLL>(fam_load<M>(st, on, L), st, on, true, L, n, out + L.k * kStep + L.j, count * kStep, tail);
+    fam_run<M, KIND, UNROLL, NT>(s0, st, true, true, L, n, out + L.k * kStep + L.j, count * kStep, tail);
   } else {
-    fam_run<M, KIND, UNROLL>(fam_load<M>(st, on, L), st, on, true, L, n, out + L.k * n + L.j, kStep, nullptr);
+    fam_run<M, KIND, UNROLL, NT>(s0, st, true, true, L, n, out + L.k * n + L.j, kStep, nullptr);
   }
 }
 
@@ -516,30 +523,25 @@ __global__ __launch_bounds__(1024) void k_fam_normals(unsigned char *__restrict_
                                                       uint64_t count, uint64_t n, void *__restrict__ out_v,
                                                       void *__restrict__ sums_v) {
   using real = real_of<M>;
-  const Lanes L = lanes_of(count, xcd_block());
-  const uint64_t pair = L.k >> 1;
+  const uint64_t pair = pair_of(xcd_block());
   if (2 * pair >= count) return;  // wave-uniform
+  const Lanes L = pair_lanes(pair, count);
   unsigned char *st = state + (first + L.k) * M::state_bytes;
   real *out = MOMENTS ? nullptr : static_cast<real *>(out_v) + L.k * n;
   real *sums = MOMENTS ? static_cast<real *>(sums_v) + 2 * L.k : nullptr;
-  if (2 * pair + 1 < count) fam_normals_run<M, MOMENTS, true, NT>(fam_load<M>(st, true, L), st, true, true, L, n, out, sums);
-  else fam_normals_run<M, MOMENTS, false, NT>(fam_load<M>(st, L.active, L), st, L.active, true, L, n, out, sums);
+  fam_normals_run<M, MOMENTS, true, NT>(fam_load<M>(st, true, L), st, true, true, L, n, out, sums);
 }
 
-template <class M, uint32_t KIND, int UNROLL, bool FILL>
+template <class M, uint32_t KIND, int UNROLL, bool FILL, bool NT>
 __global__ __launch_bounds__(1024) void k_fam_generate(unsigned char *__restrict__ state, uint64_t first,
                                                        uint64_t count, uint64_t n, void *__restrict__ out) {
   // Stream-major: each XCD takes a contiguous range of streams; bulk fill:
   // plain order, so every XCD's writes spread over the whole dense front
   // (each measured the faster for its layout).
-  const Lanes L = lanes_of(count, FILL ? blockIdx.x : xcd_block());
-  const uint64_t pair = L.k >> 1;
+  const uint64_t pair = pair_of(FILL ? blockIdx.x : xcd_block());
   if (2 * pair >= count) return;  // wave-uniform
-  using word = typename M::word;
-  if (2 * pair + 1 < count)
-    fam_serve<M, KIND, UNROLL, FILL, false>(state, L, first, count, n, reinterpret_cast<word *>(out));
-  else
-    fam_serve<M, KIND, UNROLL, FILL, true>(state, L, first, count, n, reinterpret_cast<word *>(out));
+  fam_serve<M, KIND, UNROLL, FILL, NT>(state, pair_lanes(pair, count), first, count, n,
+                                       reinterpret_cast<typename M::word *>(out));
 }
 
 // ---------------------------------------------------------------------------
@@ -776,18 +778,13 @@ __global__ __launch_bounds__(256) void k_fam_skip(unsigned char *__restrict__ st
                                                   uint64_t count, uint64_t J, JumpPoly g) {
   using word = typename M::word;
   constexpr uint32_t kN = 64u * 8u * sizeof(word);  // n = r w with r = 64
-  const Lanes L = lanes_of(count, blockIdx.x);
-  if (2 * (L.k >> 1) >= count) return;  // wave-uniform
+  const uint64_t pair = pair_of(blockIdx.x);
+  if (2 * pair >= count) return;  // wave-uniform
+  const Lanes L = pair_lanes(pair, count);
   unsigned char *st = state + (first + L.k) * M::state_bytes;
-  word prev = 0, cur = 0, w_start = 0;
-  uint64_t pos = 0;
-  if (L.active) {
-    const word *ring = reinterpret_cast<const word *>(st);
-    prev = ring[L.j];
-    cur = ring[32 + L.j];
-    w_start = *reinterpret_cast<const word *>(st + M::weyl_off);
-    pos = *reinterpret_cast<const uint64_t *>(st + M::pos_off);
-  }
+  const FamState<M> s0 = fam_load<M>(st, true, L);
+  const word prev = s0.prev, cur = s0.cur, w_start = s0.weyl;
+  const uint64_t pos = s0.pos;
   const bool word0 = L.j == 0;
   const word w_end = w_start + (word)J * M::omega;
   if constexpr (!JUMP) {
@@ -936,20 +933,15 @@ __global__ __launch_bounds__(FamJump<M>::kWaves * 64) void k_fam_skip_wg(unsigne
   __shared__ typename FamJump<M>::Lds lds;
   const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   FamJump<M>::lay_out(reinterpret_cast<const uint32_t *>(g.w), lds);
-  Lanes L;
-  L.lane = threadIdx.x & 63u;
-  L.h = L.lane & 1u;
-  L.j = L.lane >> 1;
   for (uint64_t pair = blockIdx.x; 2 * pair < count; pair += gridDim.x) {
-    L.k = 2 * pair + L.h;
-    L.active = L.k < count;
-    const FamState<M> s0 = fam_load<M>(state + (first + L.k) * M::state_bytes, L.active, L);
+    const Lanes L = pair_lanes(pair, count);
+    const FamState<M> s0 = fam_load<M>(state + (first + L.k) * M::state_bytes, true, L);
     const word y = FamJump<M>::jump(s0, lds, L, wave);
     if (wave < 2 && 2 * pair + wave < count) {
       unsigned char *st = state + (first + 2 * pair + wave) * M::state_bytes;
       reinterpret_cast<word *>(st)[L.lane] = y;
     }
-    if (wave == 0 && L.j == 0 && L.active) {
+    if (wave == 0 && L.j == 0) {
       unsigned char *st = state + (first + L.k) * M::state_bytes;
       *reinterpret_cast<word *>(st + M::weyl_off) = s0.weyl + (word)J * M::omega;
       *reinterpret_cast<uint64_t *>(st + M::pos_off) = s0.pos + J;
@@ -971,13 +963,8 @@ __global__ __launch_bounds__(FamJump<M>::kWaves * 64) void k_fam_split_starts(
   __shared__ typename FamJump<M>::Lds lds;
   const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const uint32_t pairs = (count + 1) / 2, k = blockIdx.x / pairs, pair = blockIdx.x % pairs;
-  Lanes L;
-  L.lane = threadIdx.x & 63u;
-  L.h = L.lane & 1u;
-  L.j = L.lane >> 1;
-  L.k = 2 * pair + L.h;
-  L.active = L.k < count;
-  FamState<M> s0 = fam_load<M>(state + (first + L.k) * M::state_bytes, L.active, L);
+  const Lanes L = pair_lanes(pair, count);
+  FamState<M> s0 = fam_load<M>(state + (first + L.k) * M::state_bytes, true, L);
   word *mine = out + L.k * at.row + k * at.part;
   if (k) {
     FamJump<M>::lay_out(reinterpret_cast<const uint32_t *>(table + (uint64_t)split_entry(exp, k) * (FamJump<M>::kWords / 2)),
@@ -988,11 +975,11 @@ __global__ __launch_bounds__(FamJump<M>::kWaves * 64) void k_fam_split_starts(
     const uint64_t by = (uint64_t)k << exp;
     s0.weyl += (word)by * M::omega;
     s0.pos += by;
-  } else if (wave == 0 && L.active) {
+  } else if (wave == 0) {
     mine[L.j] = s0.prev;
     mine[at.chunk + L.j] = s0.cur;
   }
-  if (wave == 0 && L.active && L.j == 0) {
+  if (wave == 0 && L.j == 0) {
     word *w = mine + 2 * at.chunk;
     w[0] = s0.weyl;
     w[1] = (word)s0.pos;
@@ -1010,31 +997,24 @@ __global__ __launch_bounds__(256) void k_fam_split(unsigned char *__restrict__ s
   const uint32_t wid = (uint32_t)__builtin_amdgcn_readfirstlane((int)((blockIdx.x * blockDim.x + threadIdx.x) >> 6));
   const uint32_t pairs = (count + 1) / 2, k = wid / pairs, pair = wid % pairs;
   if (k >= parts) return;
-  Lanes L;
-  L.lane = threadIdx.x & 63u;
-  L.h = L.lane & 1u;
-  L.j = L.lane >> 1;
-  L.k = 2 * pair + L.h;
-  L.active = L.k < count;
-  const bool on = L.active, last = k + 1 == parts;
+  const Lanes L = pair_lanes(pair, count);
+  const bool last = k + 1 == parts;
   const uint64_t done = (uint64_t)k << exp, nk = last ? n - done : 1ull << exp;
   word *o = out + L.k * at.row + k * at.part;
+  const word *w = o + 2 * at.chunk;
   FamState<M> s0;
-  if (on) {
-    s0.prev = o[L.j];
-    s0.cur = o[at.chunk + L.j];
-    const word *w = o + 2 * at.chunk;
-    s0.weyl = w[0];
-    s0.pos = (uint64_t)w[1];
-    if constexpr (sizeof(word) == 4) s0.pos |= (uint64_t)w[2] << 32;
-  }
+  s0.prev = o[L.j];
+  s0.cur = o[at.chunk + L.j];
+  s0.weyl = w[0];
+  s0.pos = (uint64_t)w[1];
+  if constexpr (sizeof(word) == 4) s0.pos |= (uint64_t)w[2] << 32;
   // Every word of the state is read before this wavefront writes over it.
   unsigned char *st = state + (first + L.k) * M::state_bytes;
   if constexpr (KIND == kNormal) {
-    fam_normals_run<M, false, false, false>(s0, st, on, last, L, nk, reinterpret_cast<real_of<M> *>(o), nullptr);
+    fam_normals_run<M, false, true, false>(s0, st, true, last, L, nk, reinterpret_cast<real_of<M> *>(o), nullptr);
   } else {
     word *tail = FILL ? out + (n / kStep) * at.chunk + L.k * (n % kStep) + L.j : nullptr;
-    fam_run<M, KIND, 8, false>(s0, st, on, last, L, nk, o + L.j, FILL ? at.chunk : kStep, tail);
+    fam_run<M, KIND, 8, false>(s0, st, true, last, L, nk, o + L.j, FILL ? at.chunk : kStep, tail);
   }
 }
 
@@ -1062,24 +1042,31 @@ hipError_t launch_fam_split(Kind kind, bool fill, const Split &sp, unsigned char
   return hipErrorInvalidValue;
 }
 
-template <class M, uint32_t KIND, bool FILL>
+template <class M, uint32_t KIND, bool FILL, bool NT>
 hipError_t launch_fam_k(uint32_t unroll, dim3 grid, dim3 block, unsigned char *state, uint64_t first,
                   uint64_t count, uint64_t n, void *out, hipStream_t stream) {
-  hipError_t e = hipSuccess;
+  auto run = [&](auto kernel) { return launch(kernel, grid, block, 0, stream, state, first, count, n, out); };
   switch (unroll) {
-    case 1: e = launch((k_fam_generate<M, KIND, 1, FILL>), grid, block, 0, stream, state, first, count, n, out); break;
-    case 2: e = launch((k_fam_generate<M, KIND, 2, FILL>), grid, block, 0, stream, state, first, count, n, out); break;
-    case 4: e = launch((k_fam_generate<M, KIND, 4, FILL>), grid, block, 0, stream, state, first, count, n, out); break;
-    default: e = launch((k_fam_generate<M, KIND, 8, FILL>), grid, block, 0, stream, state, first, count, n, out); break;
+    case 1: return run(k_fam_generate<M, KIND, 1, FILL, NT>);
+    case 2: return run(k_fam_generate<M, KIND, 2, FILL, NT>);
+    case 4: return run(k_fam_generate<M, KIND, 4, FILL, NT>);
+    default: return run(k_fam_generate<M, KIND, 8, FILL, NT>);
   }
-  return e;
 }
 
+// The bulk-fill layout takes non-temporal stores, as do stream-major rows on
+// whole 128-byte lines with less than a wavefront per SIMD (5 % faster than
+// cached ones: 300 x 10016 uint64 16.5 us against 17.3); the others cached
+// ones (64-bit member, 4096 x 2^16: 390 us against 414; rows that start inside
+// a line, 4096 x 65537: 403 and 727 us, 32-bit member 211 and 535).
 template <class M, uint32_t KIND>
-hipError_t launch_fam_layout(bool fill, uint32_t unroll, dim3 grid, dim3 block, unsigned char *state,
+hipError_t launch_fam_layout(bool fill, uint32_t unroll, int num_cus, dim3 grid, dim3 block, unsigned char *state,
                              uint64_t first, uint64_t count, uint64_t n, void *out, hipStream_t stream) {
-  if (fill) return launch_fam_k<M, KIND, true>(unroll, grid, block, state, first, count, n, out, stream);
-  return launch_fam_k<M, KIND, false>(unroll, grid, block, state, first, count, n, out, stream);
+  if (fill) return launch_fam_k<M, KIND, true, true>(unroll, grid, block, state, first, count, n, out, stream);
+  const bool lines = (n * sizeof(typename M::word) | reinterpret_cast<uintptr_t>(out)) % 128 == 0;
+  if (lines && count < 8 * (uint64_t)(num_cus > 0 ? num_cus : 1))
+    return launch_fam_k<M, KIND, false, true>(unroll, grid, block, state, first, count, n, out, stream);
+  return launch_fam_k<M, KIND, false, false>(unroll, grid, block, state, first, count, n, out, stream);
 }
 
 }  // namespace
@@ -1160,7 +1147,8 @@ hipError_t launch_family_split(uint32_t family, Kind kind, bool fill, const Spli
 }
 
 hipError_t launch_family_generate(uint32_t family, Kind kind, bool fill, const Shape &shape, unsigned char *state,
-                                  uint64_t first, uint64_t count, uint64_t n, void *out, hipStream_t stream) {
+                                  uint64_t first, uint64_t count, uint64_t n, void *out, int num_cus,
+                                  hipStream_t stream) {
   hipError_t e = hipSuccess;
   const uint64_t pairs = (count + 1) / 2;
   const uint64_t wpb = shape.waves_per_block;
@@ -1185,13 +1173,17 @@ hipError_t launch_family_generate(uint32_t family, Kind kind, bool fill, const S
     return hipErrorInvalidValue;
   }
   if (family == XG_FAMILY_R64_W32 && kind == kU32)
-    e = launch_fam_layout<MemberN2048, kU32>(fill, shape.unroll, grid, block, state, first, count, n, out, stream);
+    e = launch_fam_layout<MemberN2048, kU32>(fill, shape.unroll, num_cus, grid, block, state, first, count, n, out,
+                                                stream);
   else if (family == XG_FAMILY_R64_W32 && kind == kF32)
-    e = launch_fam_layout<MemberN2048, kF32>(fill, shape.unroll, grid, block, state, first, count, n, out, stream);
+    e = launch_fam_layout<MemberN2048, kF32>(fill, shape.unroll, num_cus, grid, block, state, first, count, n, out,
+                                                stream);
   else if (family == XG_FAMILY_R64_W64 && kind == kU64)
-    e = launch_fam_layout<MemberW64, kU64>(fill, shape.unroll, grid, block, state, first, count, n, out, stream);
+    e = launch_fam_layout<MemberW64, kU64>(fill, shape.unroll, num_cus, grid, block, state, first, count, n, out,
+                                                stream);
   else if (family == XG_FAMILY_R64_W64 && kind == kF64)
-    e = launch_fam_layout<MemberW64, kF64>(fill, shape.unroll, grid, block, state, first, count, n, out, stream);
+    e = launch_fam_layout<MemberW64, kF64>(fill, shape.unroll, num_cus, grid, block, state, first, count, n, out,
+                                                stream);
   else
     return hipErrorInvalidValue;
   return e;

@@ -29,8 +29,9 @@ struct Shape {
 constexpr Shape kDefaultPlain{0, 0, 1, 4};  // waves_per_block and unroll chosen per launch
 
 // Waves per block for a plain launch of `count` streams on `num_cus` compute
-// units: one stream per wavefront, and at least as many blocks as compute
-// units, so that the wavefronts spread one per SIMD before any SIMD gets two.
+// units: four once that gives every compute unit a block, else one, so that
+// the wavefronts spread one per SIMD before any SIMD gets two.  (Blocks of two
+// do not: 700 streams x 100003 uint32 took 84 us in them, 52 in blocks of one.)
 uint32_t auto_waves_per_block(uint64_t count, int num_cus);
 // Default persistent-batch shapes, chosen by the number of queue items.  With
 // at least eight items per compute unit the batch is bound by HBM writes, and
@@ -60,6 +61,24 @@ hipError_t launch_init(uint32_t *state, uint64_t num_streams, uint64_t seed, hip
 // the pair gather that needs no LDS.
 hipError_t launch_generate(Kind kind, const Shape &shape, uint32_t *state, uint64_t first,
                            uint64_t count, uint64_t n, void *out, int num_cus, hipStream_t stream);
+
+// Whether a stream-major launch of Section 2's member takes cached stores
+// (launch_rows_cached) instead of non-temporal ones:
+//  - where rows start inside a 128-byte line: non-temporal stores write both
+//    ends of each wavefront's 256 bytes as partial lines (4096 x 65537 uint32:
+//    366 us against 199; 1024 x 100003: 137 and 80, normals 137 and 98).  Outputs
+//    under 32 MB keep them, since what a launch leaves in the caches is written
+//    back at its end (1071 x 4848 FP32: 7.8 us against 8.4);
+//  - uint32 and FP32 with two wavefronts or more per SIMD (4096 x 2^18 uint32:
+//    805 us and 760); normals stay 2 % faster with non-temporal ones, as does
+//    one wavefront per SIMD (1024 x 2^20 uint32: 705 us and 730).
+inline bool cached_stores(Kind kind, uint64_t count, uint64_t n, const void *out, int num_cus) {
+  if (kind != kU32 && kind != kF32 && kind != kNormal) return false;
+  if ((n * 4 | reinterpret_cast<uintptr_t>(out)) % 128 != 0 && count * n >= (32ull << 20) / 4) return true;
+  return kind != kNormal && count >= 8u * (uint64_t)(num_cus > 0 ? num_cus : 1);
+}
+hipError_t launch_rows_cached(Kind kind, uint32_t waves_per_block, uint32_t *state, uint64_t first, uint64_t count,
+                              uint64_t n, void *out, int num_cus, hipStream_t stream);
 
 // Bulk-fill layout of xg_fill_u32 / xg_fill_f32 (kind kU32 or kF32).
 hipError_t launch_fill(Kind kind, const Shape &shape, uint32_t *state, uint64_t first, uint64_t count,
@@ -134,7 +153,8 @@ hipError_t launch_family_init(uint32_t family, unsigned char *state, uint64_t nu
 // fill selects the bulk-fill layout (32-word chunks).  shape.waves_per_block
 // counts wavefronts, i.e. pairs of streams.
 hipError_t launch_family_generate(uint32_t family, Kind kind, bool fill, const Shape &shape, unsigned char *state,
-                                  uint64_t first, uint64_t count, uint64_t n, void *out, hipStream_t stream);
+                                  uint64_t first, uint64_t count, uint64_t n, void *out, int num_cus,
+                                  hipStream_t stream);
 // Advances streams [first, first + count) of a further member by J words: by
 // stepping when g == nullptr, else by evaluating g(T) (g = z^J mod P, its
 // member_degree / 64 low words used).

@@ -575,6 +575,21 @@ __global__ __launch_bounds__(1024) void k_generate(uint32_t *__restrict__ state,
   }
 }
 
+// The same with cached stores, for rows that start inside a cache line and for
+// words with two or more wavefronts per SIMD (cached_stores in xg_internal.h).
+template <uint32_t KIND, bool DPP = false>
+__global__ __launch_bounds__(1024) void k_rows_cached(uint32_t *__restrict__ state, uint64_t first, uint64_t count,
+                                                      uint64_t n, uint32_t *__restrict__ out) {
+  const uint64_t wid = ((uint64_t)xcd_block() * blockDim.x + threadIdx.x) >> 6;
+  if (wid >= count) return;
+  uint32_t *st = state + (first + wid) * kStateWords;
+  if constexpr (KIND == kNormal) {
+    serve_normals_from<false, 8, DPP, false>(load_state(st), n, reinterpret_cast<float *>(out) + wid * n, nullptr, st);
+  } else {
+    serve_words_from<KIND, 8, false, false, false>(load_state(st), n, out + wid * n, st);
+  }
+}
+
 // Bulk-fill layout (see serve_words_fill): uint32 / FP32 only.
 template <uint32_t KIND, int UNROLL>
 __global__ __launch_bounds__(1024) void k_fill(uint32_t *__restrict__ state, uint64_t first,
@@ -1030,10 +1045,7 @@ hipError_t launch_generate_k(const Shape &sh, dim3 grid, dim3 block, uint32_t *s
 }  // namespace
 
 uint32_t auto_waves_per_block(uint64_t count, int num_cus) {
-  const uint64_t cus = num_cus > 0 ? (uint64_t)num_cus : 1;
-  if (count >= 4 * cus) return 4;
-  if (count >= 2 * cus) return 2;
-  return 1;
+  return count >= 4 * (uint64_t)(num_cus > 0 ? num_cus : 1) ? 4 : 1;
 }
 
 bool shape_valid(const Shape &s) {
@@ -1127,6 +1139,20 @@ hipError_t launch_split(Kind kind, bool fill, const Split &sp, uint32_t *state, 
   if (kind == kNormal) return run(k_split<kNormal, false>);
   if (kind == kF32) return fill ? run(k_split<kF32, true>) : run(k_split<kF32, false>);
   return fill ? run(k_split<kU32, true>) : run(k_split<kU32, false>);
+}
+
+hipError_t launch_rows_cached(Kind kind, uint32_t waves_per_block, uint32_t *state, uint64_t first, uint64_t count,
+                              uint64_t n, void *out, int num_cus, hipStream_t stream) {
+  const uint64_t wpb = waves_per_block;
+  auto run = [&](auto kernel) {
+    return launch(kernel, dim3((uint32_t)((count + wpb - 1) / wpb)), dim3((uint32_t)(wpb * kWave)), 0, stream, state,
+                  first, count, n, static_cast<uint32_t *>(out));
+  };
+  if (kind == kU32) return run(k_rows_cached<kU32>);
+  if (kind == kF32) return run(k_rows_cached<kF32>);
+  // Normals: the pair gather as for launch_generate.
+  const bool dpp = count < 8u * (uint64_t)(num_cus > 0 ? num_cus : 1);
+  return dpp ? run(k_rows_cached<kNormal, true>) : run(k_rows_cached<kNormal, false>);
 }
 
 hipError_t launch_work_init(uint32_t *work, uint32_t num_groups, uint32_t num_reqs, hipStream_t stream) {
