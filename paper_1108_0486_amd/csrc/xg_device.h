@@ -15,6 +15,33 @@ __device__ __forceinline__ uint32_t lanes_rotate_up(uint32_t v) {
   return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x13C, 0xF, 0xF, true);
 }
 
+// Lane l receives lane l ^ D's value, in the VALU (D a power of two up to 32).
+template <uint32_t D>
+__device__ __forceinline__ uint32_t lane_xor(uint32_t v) {
+  if constexpr (D == 1) {
+    return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0xB1, 0xF, 0xF, false);  // quad_perm [1, 0, 3, 2]
+  } else if constexpr (D == 2) {
+    return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x4E, 0xF, 0xF, false);  // quad_perm [2, 3, 0, 1]
+  } else if constexpr (D == 4) {
+    // Lanes 0-3 and 8-11 of a row take lane + 4 (row_shl:4), the others lane - 4 (row_shr:4).
+    const int q = __builtin_amdgcn_update_dpp(0, (int)v, 0x104, 0xF, 0x5, false);
+    return (uint32_t)__builtin_amdgcn_update_dpp(q, (int)v, 0x114, 0xF, 0xA, false);
+  } else if constexpr (D == 8) {
+    return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x128, 0xF, 0xF, false);  // row_ror:8
+  } else if constexpr (D == 16) {
+    const auto rows = __builtin_amdgcn_permlane16_swap(v, v, false, false);  // {even rows twice, odd rows twice}
+    return threadIdx.x & 16u ? rows[0] : rows[1];
+  } else {
+    static_assert(D == 32, "a lane's distance");
+    const auto halves = __builtin_amdgcn_permlane32_swap(v, v, false, false);  // {low half twice, high half twice}
+    return threadIdx.x & 32u ? halves[0] : halves[1];
+  }
+}
+template <uint32_t D>
+__device__ __forceinline__ uint64_t lane_xor(uint64_t v) {
+  return (uint64_t)lane_xor<D>((uint32_t)v) | ((uint64_t)lane_xor<D>((uint32_t)(v >> 32)) << 32);
+}
+
 // A truth table of v_bitop3_b32 is the function's value on the operand
 // patterns a = 0xF0, b = 0xCC, c = 0xAA.
 // a xor b xor c: 0x96.

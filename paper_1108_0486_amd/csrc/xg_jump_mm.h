@@ -76,16 +76,12 @@ __device__ __forceinline__ uint32_t word_bits(uint32_t v, const TransposeLane &k
   // 16: even rows of 16 lanes take the low halves of both rows, odd rows the high ones.
   const auto rows = __builtin_amdgcn_permlane16_swap(v, v, false, false);  // {even rows twice, odd rows twice}
   v = __builtin_amdgcn_perm(rows[0], rows[1], k.sel16);
-  // 8: lane ^ 8 is a rotation of the row by 8.
-  uint32_t p = (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x128, 0xF, 0xF, false);
-  v = __builtin_amdgcn_perm(v, p, k.sel8);
-  // 4: lanes 0-3 and 8-11 of a row take lane + 4 (row_shl:4), the others lane - 4 (row_shr:4).
-  int q = __builtin_amdgcn_update_dpp(0, (int)v, 0x104, 0xF, 0x5, false);
-  q = __builtin_amdgcn_update_dpp(q, (int)v, 0x114, 0xF, 0xA, false);
-  v = select_bits(v, __builtin_amdgcn_alignbit((uint32_t)q, (uint32_t)q, k.rot4), k.keep4);
-  p = (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x4E, 0xF, 0xF, false);  // lane ^ 2
+  v = __builtin_amdgcn_perm(v, lane_xor<8>(v), k.sel8);
+  uint32_t p = lane_xor<4>(v);
+  v = select_bits(v, __builtin_amdgcn_alignbit(p, p, k.rot4), k.keep4);
+  p = lane_xor<2>(v);
   v = select_bits(v, __builtin_amdgcn_alignbit(p, p, k.rot2), k.keep2);
-  p = (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0xB1, 0xF, 0xF, false);  // lane ^ 1
+  p = lane_xor<1>(v);
   return select_bits(v, __builtin_amdgcn_alignbit(p, p, k.rot1), k.keep1);
 }
 

@@ -17,6 +17,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "xg_device.h"
 #include "xg_host.h"
 #include "xg_internal.h"
 #include "xg_launch.h"
@@ -432,22 +433,25 @@ __global__ __launch_bounds__(256) void k_plan_emit(const xg_request *__restrict_
 
 // ---- small tables: the whole plan in one workgroup ---------------------------
 
-// Table entries plus tile slots that one workgroup of 1024 threads plans in
-// LDS with a single launch instead of the multi-kernel sequence above (the
-// plan is the same): EPT consecutive elements per thread, EPT = 1, 2 or 4, at
-// most 4096 elements (128 KB of LDS; gfx950 gives a workgroup 160 KB).
-constexpr uint32_t kPlanThreads = 1024;
-constexpr uint32_t kSmallPlanMax = 4 * kPlanThreads;
+// Table entries plus tile slots that one workgroup plans with a single launch
+// instead of the multi-kernel sequence above (the plan is the same): N
+// elements, EPT = N / THREADS consecutive ones per thread, N from 256 to 4096 (160
+// KB of LDS).  Latency bounds it, so the sorts keep their keys in registers
+// and exchange them by lane swaps; only distances beyond a wavefront go
+// through LDS, with one barrier each.  384 requests take 9 us (24 us with
+// every pass through LDS in 1024 elements).
+constexpr uint32_t kSmallPlanMax = 4096;
 
 // Exclusive prefix sums of the workgroup's values, EPT consecutive ones per
 // thread (v[e] is element EPT t + e): on return v[e] holds the sum of every
-// element before it, and *total the sum of all.  wsum holds 16 values of T.
-template <typename T, int EPT>
+// element before it, and *total the sum of all.  wsum holds a value per wavefront.
+template <typename T, uint32_t THREADS, uint32_t EPT>
 __device__ __forceinline__ void wg_exclusive(T (&v)[EPT], T *wsum, T *total) {
+  constexpr uint32_t kWaves = THREADS / 64;
   const uint32_t t = threadIdx.x, lane = t & 63u, w = t >> 6;
   T mine = 0;
 #pragma unroll
-  for (int e = 0; e < EPT; ++e) mine += v[e];
+  for (uint32_t e = 0; e < EPT; ++e) mine += v[e];
   T x = mine;
 #pragma unroll
   for (uint32_t d = 1; d < 64u; d <<= 1) {
@@ -456,205 +460,266 @@ __device__ __forceinline__ void wg_exclusive(T (&v)[EPT], T *wsum, T *total) {
   }
   if (lane == 63u) wsum[w] = x;
   __syncthreads();
-  if (w == 0) {
-    T s = lane < 16u ? wsum[lane] : T(0);
+  T run = x - mine, all = 0;
 #pragma unroll
-    for (uint32_t d = 1; d < 16u; d <<= 1) {
-      const T y = __shfl_up(s, d);
-      if (lane >= d) s += y;
-    }
-    if (lane < 16u) wsum[lane] = s;
+  for (uint32_t i = 0; i < kWaves; ++i) {
+    const T s = wsum[i];
+    if (i < w) run += s;
+    all += s;
   }
-  __syncthreads();
-  T run = (w ? wsum[w - 1] : T(0)) + x - mine;
-  *total = wsum[15];
+  *total = all;
   __syncthreads();  // wsum is reused by the next scan
 #pragma unroll
-  for (int e = 0; e < EPT; ++e) {
+  for (uint32_t e = 0; e < EPT; ++e) {
     const T here = v[e];
     v[e] = run;
     run += here;
   }
 }
 
-// Ascending bitonic sort of N keys in LDS (EPT / 2 pairs per thread and pass,
-// or half the threads with one pair each when EPT == 1).
-template <uint32_t N>
-__device__ __forceinline__ void wg_sort(uint64_t *s) {
-  const uint32_t t = threadIdx.x;
-  constexpr uint32_t kPairs = N / 2;
-  for (uint32_t k = 2; k <= N; k <<= 1) {
-    for (uint32_t j = k >> 1; j > 0; j >>= 1) {
+// One compare-exchange pass (stage K, distance J) of the bitonic network on
+// element EPT t + e in k[e].  Distances of a wavefront or more go through one
+// half of lds (2 N keys), the halves in turn, so that one barrier is enough.
+template <uint32_t N, uint32_t THREADS, uint32_t K, uint32_t J>
+__device__ __forceinline__ void sort_pass(uint64_t (&k)[N / THREADS], uint64_t *lds, uint32_t &half) {
+  constexpr uint32_t EPT = N / THREADS;
+  const uint32_t i0 = threadIdx.x * EPT;
+  if constexpr (J < EPT) {
 #pragma unroll
-      for (uint32_t pr = t; pr < kPairs; pr += kPlanThreads) {
-        const uint32_t i = ((pr & ~(j - 1u)) << 1) | (pr & (j - 1u));
-        const uint32_t l = i | j;
-        const bool asc = (i & k) == 0u;
-        const uint64_t x = s[i], y = s[l];
-        if ((x > y) == asc) {
-          s[i] = y;
-          s[l] = x;
-        }
-      }
+    for (uint32_t e = 0; e < EPT; ++e) {
+      if (e & J) continue;
+      const bool asc = ((i0 + e) & K) == 0u;
+      const uint64_t x = k[e], y = k[e | J];
+      const bool swap = (x > y) == asc;
+      k[e] = swap ? y : x;
+      k[e | J] = swap ? x : y;
+    }
+  } else {
+    uint64_t y[EPT];
+    if constexpr (J < 64 * EPT) {
+#pragma unroll
+      for (uint32_t e = 0; e < EPT; ++e) y[e] = dev::lane_xor<J / EPT>(k[e]);
+    } else {
+      uint64_t *s = lds + half * N;
+      half ^= 1u;
+#pragma unroll
+      for (uint32_t e = 0; e < EPT; ++e) s[i0 + e] = k[e];
       __syncthreads();
+#pragma unroll
+      for (uint32_t e = 0; e < EPT; ++e) y[e] = s[(i0 + e) ^ J];
+    }
+#pragma unroll
+    for (uint32_t e = 0; e < EPT; ++e) {
+      const uint32_t i = i0 + e;
+      const bool least = ((i & J) == 0u) == ((i & K) == 0u);  // the lower place of an ascending pair, and so on
+      k[e] = (k[e] > y[e]) == least ? y[e] : k[e];
     }
   }
 }
 
-// The planner for num_reqs + tile_cap <= N = 1024 EPT: the steps of the
-// kernels above (keys, sort, group heads and cost sums, tiles and their
-// budget, queue items, their sort, entry counts, table) on EPT consecutive
-// elements per thread, with the arrays in LDS.  Writes offs[0 .. num_reqs +
-// tile_cap], the table and work[0 .. 63] (counts in work[2], work[3], the
-// error word in work[1]).
-template <int EPT>
-__global__ __launch_bounds__(kPlanThreads) void k_plan_small(const xg_request *__restrict__ reqs,
-                                                             uint32_t num_reqs, uint64_t num_streams,
-                                                             uint64_t tile_words, uint32_t tile_cap,
-                                                             uint32_t *__restrict__ work,
-                                                             uint32_t *__restrict__ offs_out,
-                                                             xg_request *__restrict__ table) {
-  constexpr uint32_t N = kPlanThreads * EPT;
-  __shared__ uint64_t keys[N];       // sort keys, then queue item keys
-  __shared__ uint64_t costs[N + 1];  // cost prefix sums over sorted requests
+template <uint32_t N, uint32_t THREADS, uint32_t K, uint32_t J>
+__device__ __forceinline__ void sort_passes(uint64_t (&k)[N / THREADS], uint64_t *lds, uint32_t &half) {
+  sort_pass<N, THREADS, K, J>(k, lds, half);
+  if constexpr (J > 1) sort_passes<N, THREADS, K, J / 2>(k, lds, half);
+}
+
+// Sorts the workgroup's N distinct-or-all-ones keys ascending.  lds holds 2 N keys.
+template <uint32_t N, uint32_t THREADS, uint32_t K = 2>
+__device__ __forceinline__ void wg_sort(uint64_t (&k)[N / THREADS], uint64_t *lds, uint32_t &half) {
+  sort_passes<N, THREADS, K, K / 2>(k, lds, half);
+  if constexpr (K < N) wg_sort<N, THREADS, 2 * K>(k, lds, half);
+}
+
+// Adds the workgroup's flags to *count: one atomic per wavefront.
+template <uint32_t EPT>
+__device__ __forceinline__ void count_flags(const bool (&f)[EPT], uint32_t *count) {
+  uint32_t c = 0;
+#pragma unroll
+  for (uint32_t e = 0; e < EPT; ++e) c += (uint32_t)__popcll(__ballot(f[e]));
+  if ((threadIdx.x & 63u) == 0 && c) atomicAdd(count, c);
+}
+
+// The planner for num_reqs + tile_cap <= N: the steps of the kernels above
+// (keys, sort, group heads and cost sums, tiles and their budget, queue items,
+// their sort, entry counts, table) on EPT consecutive elements per thread.
+// Writes offs[0 .. num_reqs + tile_cap], the table and work[0 .. 63] (counts
+// in work[2], work[3], the error word in work[1]).
+template <uint32_t N, uint32_t THREADS>
+__global__ __launch_bounds__(THREADS) void k_plan_small(const xg_request *__restrict__ reqs, uint32_t num_reqs,
+                                                        uint64_t num_streams, uint64_t tile_words, uint32_t tile_cap,
+                                                        uint32_t *__restrict__ work, uint32_t *__restrict__ offs_out,
+                                                        xg_request *__restrict__ table) {
+  constexpr uint32_t EPT = N / THREADS;
+  __shared__ uint64_t swap[2 * N];   // the sorts' exchanges; between them the item keys by place
+  __shared__ uint64_t costs[N + 1];  // request costs by index, then cost prefix sums over sorted requests
   __shared__ uint32_t idx[N];        // request index at each sorted position
-  __shared__ uint32_t heads[N + 1];  // group prefix sums, then entry offsets of items
   __shared__ uint32_t hp[N + 1];     // first sorted position of each group
   __shared__ uint32_t tiles[N + 1];  // tile prefix sums per group
-  __shared__ uint64_t wsum[16];
+  __shared__ uint64_t wsum[THREADS / 64];
   __shared__ uint32_t cnt[4];        // valid requests, error, tile slots used, items
   const uint32_t t = threadIdx.x, n = num_reqs, i0 = t * EPT;
   uint32_t *wsum32 = reinterpret_cast<uint32_t *>(wsum);
+  uint32_t *heads = reinterpret_cast<uint32_t *>(swap + N);  // entry offsets of items, N + 1, after the sorts
+  uint32_t half = 0;
   if (t >= 4u && t < 64u) work[t] = 0u;
   if (t < 4u) cnt[t] = 0u;
   __syncthreads();
 
+  uint64_t key[EPT];
+  bool valid[EPT], bad[EPT];
 #pragma unroll
-  for (int e = 0; e < EPT; ++e) {
+  for (uint32_t e = 0; e < EPT; ++e) {
     const uint32_t i = i0 + e;
-    uint64_t key = ~0ull;
+    key[e] = ~0ull;
+    valid[e] = bad[e] = false;
     if (i < n) {
       const xg_request q = reqs[i];
-      const bool valid = q.stream < num_streams && q.dtype <= XG_NORMAL && q.flags == 0u;
-      key = ((valid ? q.stream : 0xFFFFFFFFull) << 32) | i;
-      if (valid) atomicAdd(&cnt[0], 1u);
-      else atomicOr(&cnt[1], 1u);
+      valid[e] = q.stream < num_streams && q.dtype <= XG_NORMAL && q.flags == 0u;
+      bad[e] = !valid[e];
+      key[e] = ((valid[e] ? q.stream : 0xFFFFFFFFull) << 32) | i;
+      costs[i] = cost_of(q.n, q.dtype);
     }
-    keys[i] = key;
   }
-  __syncthreads();
-  wg_sort<N>(keys);
+  count_flags(valid, &cnt[0]);
+  count_flags(bad, &cnt[1]);
+  wg_sort<N, THREADS>(key, swap, half);
+  __syncthreads();  // cnt and costs are written on every path by now
 
   const uint32_t valid_n = cnt[0];
+  // Each thread's predecessor's last key: within the wavefront by a lane
+  // shift, across wavefronts through LDS (idx is free until the keys go in).
+  uint64_t before = __shfl_up(key[EPT - 1], 1u);
+  if ((t & 63u) == 63u) wsum[t >> 6] = key[EPT - 1];
+  __syncthreads();
+  if ((t & 63u) == 0u && t) before = wsum[(t >> 6) - 1];
   uint32_t head[EPT], hx[EPT];
   uint64_t cx[EPT];
 #pragma unroll
-  for (int e = 0; e < EPT; ++e) {
+  for (uint32_t e = 0; e < EPT; ++e) {
     const uint32_t i = i0 + e;
-    const uint64_t k = keys[i];
-    idx[i] = (uint32_t)k;
+    idx[i] = (uint32_t)key[e];
     head[e] = 0;
     cx[e] = 0;
     if (i < valid_n) {
-      head[e] = i == 0 || (k >> 32) != (keys[i - 1] >> 32);
-      const xg_request q = reqs[(uint32_t)k];
-      cx[e] = cost_of(q.n, q.dtype);
+      head[e] = i == 0 || (key[e] >> 32) != ((e ? key[e - 1] : before) >> 32);
+      cx[e] = costs[(uint32_t)key[e]];
     }
     hx[e] = head[e];
   }
+  __syncthreads();  // costs and wsum are rewritten below
   uint32_t num_groups;
-  wg_exclusive<uint32_t, EPT>(hx, wsum32, &num_groups);
+  wg_exclusive<uint32_t, THREADS, EPT>(hx, wsum32, &num_groups);
   uint64_t cost_total;
-  wg_exclusive<uint64_t, EPT>(cx, wsum, &cost_total);
+  wg_exclusive<uint64_t, THREADS, EPT>(cx, wsum, &cost_total);
 #pragma unroll
-  for (int e = 0; e < EPT; ++e) {
-    heads[i0 + e] = hx[e];
+  for (uint32_t e = 0; e < EPT; ++e) {
     costs[i0 + e] = cx[e];
-  }
-  if (t == kPlanThreads - 1u) {
-    heads[N] = num_groups;
-    costs[N] = cost_total;
-  }
-  __syncthreads();
-#pragma unroll
-  for (int e = 0; e < EPT; ++e)
     if (i0 + e < n && head[e]) hp[hx[e]] = i0 + e;
-  if (t == 0) hp[num_groups] = valid_n;
+  }
+  if (t == 0) {
+    costs[N] = cost_total;
+    hp[num_groups] = valid_n;
+  }
   __syncthreads();
 
-  uint32_t want[EPT];
+  // tile_cap is the same on every thread.
+  uint32_t used = 0;
+  if (tile_cap) {
+    uint32_t want[EPT];
 #pragma unroll
-  for (int e = 0; e < EPT; ++e) {
-    const uint32_t g = i0 + e;
-    want[e] = 0;
-    if (tile_cap && g < num_groups && hp[g + 1] - hp[g] == 1u) {
-      const xg_request q = reqs[idx[hp[g]]];
-      const uint64_t parts = (words_of(q.n, q.dtype) + tile_words - 1) / tile_words;
-      if (parts > 1 && parts <= kMaxSegments) want[e] = (uint32_t)parts;
-    }
-  }
-  uint32_t tile_total;
-  wg_exclusive<uint32_t, EPT>(want, wsum32, &tile_total);
-#pragma unroll
-  for (int e = 0; e < EPT; ++e) {
-    tiles[i0 + e] = want[e];
-    if (want[e] && want[e] <= tile_cap) atomicMax(&cnt[2], want[e]);
-  }
-  if (t == kPlanThreads - 1u) tiles[N] = tile_total;
-  if (t == 0 && tile_total && tile_total <= tile_cap) atomicMax(&cnt[2], tile_total);
-#pragma unroll
-  for (int e = 0; e < EPT; ++e) keys[i0 + e] = ~0ull;  // idx holds the request indices now
-  __syncthreads();
-
-  const uint32_t used = cnt[2];
-#pragma unroll
-  for (int e = 0; e < EPT; ++e) {
-    const uint32_t g = i0 + e;
-    if (g >= num_groups) continue;
-    if (group_split(tiles, g, used)) {
-      const xg_request q = reqs[idx[hp[g]]];
-      const uint32_t parts = tiles[g + 1] - tiles[g];
-      for (uint32_t k = 0; k < parts; ++k) {
-        const uint64_t first = k * tile_words;
-        const uint64_t nk = q.n - first < tile_words ? q.n - first : tile_words;
-        keys[tiles[g] + k] = item_key(cost_of(nk, q.dtype), g, k);
+    for (uint32_t e = 0; e < EPT; ++e) {
+      const uint32_t g = i0 + e;
+      want[e] = 0;
+      if (g < num_groups && hp[g + 1] - hp[g] == 1u) {
+        const xg_request q = reqs[idx[hp[g]]];
+        const uint64_t parts = (words_of(q.n, q.dtype) + tile_words - 1) / tile_words;
+        if (parts > 1 && parts <= kMaxSegments) want[e] = (uint32_t)parts;
       }
-      atomicAdd(&cnt[3], parts);
-    } else {
-      keys[tile_cap + g] = item_key(costs[hp[g + 1]] - costs[hp[g]], g, 0);
-      atomicAdd(&cnt[3], 1u);
     }
+    uint32_t tile_total;
+    wg_exclusive<uint32_t, THREADS, EPT>(want, wsum32, &tile_total);
+#pragma unroll
+    for (uint32_t e = 0; e < EPT; ++e) {
+      tiles[i0 + e] = want[e];
+      if (want[e] && want[e] <= tile_cap) atomicMax(&cnt[2], want[e]);
+    }
+    if (t == 0) {
+      tiles[N] = tile_total;
+      if (tile_total && tile_total <= tile_cap) atomicMax(&cnt[2], tile_total);
+    }
+    __syncthreads();
+    used = cnt[2];
   }
-  __syncthreads();
-  wg_sort<N>(keys);
+  auto is_split = [&](uint32_t g) { return tile_cap && group_split(tiles, g, used); };
 
-  const uint32_t num_items = cnt[3];
+  // Queue items: with tiles, by place in swap (the tiles' slots, then the
+  // groups); without, group g on its own thread.
+  uint32_t num_items;
+  if (tile_cap) {
+#pragma unroll
+    for (uint32_t e = 0; e < EPT; ++e) swap[i0 + e] = ~0ull;
+    __syncthreads();
+#pragma unroll
+    for (uint32_t e = 0; e < EPT; ++e) {
+      const uint32_t g = i0 + e;
+      if (g >= num_groups) continue;
+      if (is_split(g)) {
+        const xg_request q = reqs[idx[hp[g]]];
+        const uint32_t parts = tiles[g + 1] - tiles[g];
+        for (uint32_t k = 0; k < parts; ++k) {
+          const uint64_t first = k * tile_words;
+          const uint64_t nk = q.n - first < tile_words ? q.n - first : tile_words;
+          swap[tiles[g] + k] = item_key(cost_of(nk, q.dtype), g, k);
+        }
+        atomicAdd(&cnt[3], parts);
+      } else {
+        swap[tile_cap + g] = item_key(costs[hp[g + 1]] - costs[hp[g]], g, 0);
+        atomicAdd(&cnt[3], 1u);
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (uint32_t e = 0; e < EPT; ++e) key[e] = swap[i0 + e];
+    num_items = cnt[3];
+    __syncthreads();  // the sort reuses swap
+  } else {
+#pragma unroll
+    for (uint32_t e = 0; e < EPT; ++e) {
+      const uint32_t g = i0 + e;
+      key[e] = g < num_groups ? item_key(costs[hp[g + 1]] - costs[hp[g]], g, 0) : ~0ull;
+    }
+    num_items = num_groups;
+  }
+  wg_sort<N, THREADS>(key, swap, half);
+
   uint32_t ox[EPT];
 #pragma unroll
-  for (int e = 0; e < EPT; ++e) {
+  for (uint32_t e = 0; e < EPT; ++e) {
     const uint32_t q = i0 + e;
     ox[e] = 0;
     if (q < num_items) {
-      const uint32_t g = (uint32_t)keys[q] >> 8;
-      ox[e] = group_split(tiles, g, used) ? 1u : hp[g + 1] - hp[g];
+      const uint32_t g = (uint32_t)key[e] >> 8;
+      ox[e] = is_split(g) ? 1u : hp[g + 1] - hp[g];
     }
   }
   uint32_t entries;
-  wg_exclusive<uint32_t, EPT>(ox, wsum32, &entries);
+  wg_exclusive<uint32_t, THREADS, EPT>(ox, wsum32, &entries);
   const uint32_t items = n + tile_cap;
+  __syncthreads();  // the sort's last reads of swap
 #pragma unroll
-  for (int e = 0; e < EPT; ++e) {
-    heads[i0 + e] = ox[e];  // heads now holds the items' table offsets
+  for (uint32_t e = 0; e < EPT; ++e) {
+    heads[i0 + e] = ox[e];
+    swap[i0 + e] = key[e];
     if (i0 + e <= items) offs_out[i0 + e] = ox[e];
   }
-  if (t == kPlanThreads - 1u) {
+  if (t == THREADS - 1u) {
     heads[N] = entries;
     if (items == N) offs_out[N] = entries;
   }
   __syncthreads();
 
 #pragma unroll
-  for (int e = 0; e < EPT; ++e) {
+  for (uint32_t e = 0; e < EPT; ++e) {
     const uint32_t en = i0 + e;
     if (en >= entries) continue;
     uint32_t lo = 0, hi = num_items;  // heads[lo] <= en < heads[hi]
@@ -663,9 +728,9 @@ __global__ __launch_bounds__(kPlanThreads) void k_plan_small(const xg_request *_
       if (heads[mid] <= en) lo = mid;
       else hi = mid;
     }
-    const uint64_t it = keys[lo];
+    const uint64_t it = swap[lo];
     const uint32_t g = (uint32_t)it >> 8, k = (uint32_t)it & 0xFFu;
-    if (group_split(tiles, g, used)) {
+    if (is_split(g)) {
       xg_request q = reqs[idx[hp[g]]];
       const uint64_t first = k * tile_words;
       const uint32_t parts = tiles[g + 1] - tiles[g], slot = tiles[g] + k;
@@ -679,7 +744,7 @@ __global__ __launch_bounds__(kPlanThreads) void k_plan_small(const xg_request *_
   }
   if (t == 0) {
     work[0] = 0u;
-    work[1] = cnt[1];
+    work[1] = cnt[1] ? 1u : 0u;
     work[2] = num_items;
     work[3] = entries;
   }
@@ -748,13 +813,15 @@ hipError_t launch_plan(const PlanPtrs &p, const PlanLayout &l, const xg_request 
   const uint64_t elems = (uint64_t)num_reqs + tile_cap;
   if (elems <= kSmallPlanMax) {
     if (elems + 1 > (uint64_t)(l.table - l.offs) / 4) return hipErrorInvalidValue;
-    auto run = [&](auto kernel) {
-      return launch(kernel, dim3(1), dim3(kPlanThreads), 0, stream, reqs, num_reqs, num_streams, tile_words,
-                    tile_cap, p.work, p.offs, p.table);
+    auto run = [&](auto kernel, uint32_t threads) {
+      return launch(kernel, dim3(1), dim3(threads), 0, stream, reqs, num_reqs, num_streams, tile_words, tile_cap,
+                    p.work, p.offs, p.table);
     };
-    if (elems <= kPlanThreads) return run(k_plan_small<1>);
-    if (elems <= 2 * kPlanThreads) return run(k_plan_small<2>);
-    return run(k_plan_small<4>);
+    if (elems <= 256) return run(k_plan_small<256, 256>, 256);
+    if (elems <= 512) return run(k_plan_small<512, 512>, 512);
+    if (elems <= 1024) return run(k_plan_small<1024, 1024>, 1024);
+    if (elems <= 2048) return run(k_plan_small<2048, 1024>, 1024);
+    return run(k_plan_small<4096, 1024>, 1024);
   }
   const uint32_t key_n = pow2_at_least(num_reqs > kSortBlock ? num_reqs : kSortBlock);
   const uint32_t items = num_reqs + tile_cap;
