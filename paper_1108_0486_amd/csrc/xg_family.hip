@@ -374,6 +374,16 @@ __device__ __forceinline__ void sums_add(MomentsF64 &m, double z0, double z1) {
   kahan_add_f64(m.s2, m.c2, fma(z1, z1, z0 * z0));
 }
 
+// The normals' LDS: two slots of two blocks (128 words of each stream, 32 apart
+// in the banks) per wavefront.
+constexpr uint32_t kFamStage = 2 * (128 + 32);
+extern __shared__ __align__(16) unsigned char fam_lds[];
+
+template <typename word>
+__device__ __forceinline__ word *fam_stage() {
+  return reinterpret_cast<word *>(fam_lds) + (threadIdx.x >> 6) * (2 * kFamStage);
+}
+
 template <class M>
 using real_of = typename std::conditional<sizeof(typename M::word) == 8, double, float>::type;
 
@@ -389,7 +399,7 @@ using real_of = typename std::conditional<sizeof(typename M::word) == 8, double,
 // value only).  One block at a time with a test per value and, for odd n, two
 // separate stores per pair took 570 us for 3001 streams x 65537 FP32 normals,
 // this form 235 us.
-template <class M, bool MOMENTS, bool BOTH, bool NT>
+template <class M, bool MOMENTS, bool BOTH, bool NT, bool STAGED = false>
 __device__ __forceinline__ void fam_normals_run(const FamState<M> &s0, unsigned char *__restrict__ st, bool on,
                                                 bool keep, Lanes L, uint64_t n, real_of<M> *__restrict__ o_s,
                                                 real_of<M> *__restrict__ sums) {
@@ -416,30 +426,51 @@ __device__ __forceinline__ void fam_normals_run(const FamState<M> &s0, unsigned 
   const uint64_t nsafe = n >> 6;     // of these, the blocks whose 64 normals are all below n
   const uint32_t rw = (uint32_t)(words & 63u);
   const uint32_t poff = fam_pair_offset(L.j);
+  constexpr int UNROLL = kW64 ? 2 : 4;
+  static_assert(!(STAGED && kW64), "the staged gather is the 32-bit member's");
   typename std::conditional<kW64, MomentsF64, dev::Moments>::type m;
   if constexpr (kW64) m = MomentsF64{0.0, 0.0, 0.0, 0.0};
   else m = dev::Moments{0.0f, 0.0f, 0.0f, 0.0f, -0.0f, -0.0f};
   typename std::conditional<kW64, dev::ConstsF64, NoConsts>::type consts;
   if constexpr (kW64) consts = dev::consts_f64();
-  real *p = MOMENTS ? nullptr : o_s + poff;
-  constexpr int UNROLL = kW64 ? 2 : 4;
+  real *p = MOMENTS ? nullptr : o_s + (STAGED ? 4 * L.j : poff);
   uint64_t b = 0;
   for (const uint64_t nouter = nsafe & ~uint64_t(UNROLL - 1); b != nouter; b += UNROLL) {
     word e[UNROLL], o[UNROLL];
-#pragma unroll
-    for (int u = 0; u < UNROLL; ++u) {
-      const word oa = next();
-      const word ob = next();
-      fam_gather_pair(oa, ob, L.j, e[u], o[u]);
-    }
     real z0[UNROLL], z1[UNROLL];
+    if constexpr (STAGED) {
+      // Two blocks at a time through the wavefront's LDS: each lane reads four
+      // consecutive words of its stream back, two pairs.
+      word *stage = fam_stage<word>();
+#pragma unroll
+      for (int u = 0; u < UNROLL; u += 2) {
+        word *half = stage + kFamStage * ((u / 2) & 1) + L.h * (128u + 32u);
+#pragma unroll
+        for (uint32_t c = 0; c < 4; ++c) half[kStep * c + L.j] = next();
+        dev::wave_lds_sync();  // the reads below take other lanes' words
+        const word *four = half + 4 * L.j;
+        e[u] = four[0];
+        o[u] = four[1];
+        e[u + 1] = four[2];
+        o[u + 1] = four[3];
+        dev::wave_lds_sync();  // the next writes to this half come after these reads
+      }
+    } else {
+#pragma unroll
+      for (int u = 0; u < UNROLL; ++u) {
+        const word oa = next();
+        const word ob = next();
+        fam_gather_pair(oa, ob, L.j, e[u], o[u]);
+      }
+    }
     fam_pairs<!MOMENTS>(consts, e, o, z0, z1);
 #pragma unroll
     for (int u = 0; u < UNROLL; ++u) {
       if constexpr (!MOMENTS) {
+        real *q = STAGED ? p + 128 * (u / 2) + 2 * (u % 2) : p + 64 * u;
         if (on) {
-          store_value<NT>(z0[u], p + 64 * u);
-          store_value<NT>(z1[u], p + 64 * u + 1);
+          store_value<NT>(z0[u], q);
+          store_value<NT>(z1[u], q + 1);
         }
       } else if constexpr (kW64) {
         sums_add(m, z0[u], z1[u]);
@@ -518,7 +549,7 @@ __device__ __forceinline__ void fam_normals_run(const FamState<M> &s0, unsigned 
 // n normals of each of `count` streams (launch index k = stream first + k)
 // at out[k n + t], or their sums at sums[2k], sums[2k + 1].  Consumes
 // 2 ceil(n / 2) words per stream.
-template <class M, bool MOMENTS, bool NT>
+template <class M, bool MOMENTS, bool NT, bool STAGED>
 __global__ __launch_bounds__(1024) void k_fam_normals(unsigned char *__restrict__ state, uint64_t first,
                                                       uint64_t count, uint64_t n, void *__restrict__ out_v,
                                                       void *__restrict__ sums_v) {
@@ -529,7 +560,7 @@ __global__ __launch_bounds__(1024) void k_fam_normals(unsigned char *__restrict_
   unsigned char *st = state + (first + L.k) * M::state_bytes;
   real *out = MOMENTS ? nullptr : static_cast<real *>(out_v) + L.k * n;
   real *sums = MOMENTS ? static_cast<real *>(sums_v) + 2 * L.k : nullptr;
-  fam_normals_run<M, MOMENTS, true, NT>(fam_load<M>(st, true, L), st, true, true, L, n, out, sums);
+  fam_normals_run<M, MOMENTS, true, NT, STAGED>(fam_load<M>(st, true, L), st, true, true, L, n, out, sums);
 }
 
 template <class M, uint32_t KIND, int UNROLL, bool FILL, bool NT>
@@ -771,8 +802,6 @@ hipError_t launch_fam_batch_k(uint32_t unroll, uint64_t blocks, dim3 block, int 
 // and kept in registers.  The bits of g are wave-uniform (both streams of a
 // wavefront jump by the same J).  W advances by J omega and pos by J.
 // ---------------------------------------------------------------------------
-extern __shared__ __align__(16) unsigned char fam_lds[];
-
 template <class M, bool JUMP>
 __global__ __launch_bounds__(256) void k_fam_skip(unsigned char *__restrict__ state, uint64_t first,
                                                   uint64_t count, uint64_t J, JumpPoly g) {
@@ -1069,6 +1098,33 @@ hipError_t launch_fam_layout(bool fill, uint32_t unroll, int num_cus, dim3 grid,
   return launch_fam_k<M, KIND, false, false>(unroll, grid, block, state, first, count, n, out, stream);
 }
 
+// The 32-bit member's normals with more than a wavefront per SIMD gather their
+// pairs through LDS, which takes selects and swaps off the VALU (3001 streams x
+// 65537: 235 us and 204; moments of 4096 x 2^16: 233 and 218).  One wavefront
+// per SIMD waits for the LDS instead (2048 x 2^17: normals 278 us and 290,
+// moments 247 and 300), and the 64-bit member gains nothing from it (4096 x
+// 2^16: normals 552 and 556).
+template <class M>
+hipError_t launch_fam_normals(Kind kind, bool nt, uint64_t pairs, int num_cus, dim3 grid, dim3 block,
+                              unsigned char *state, uint64_t first, uint64_t count, uint64_t n, void *out,
+                              hipStream_t stream) {
+  auto run = [&](auto kernel, size_t lds) {
+    return launch(kernel, grid, block, lds, stream, state, first, count, n, kind == kNormal ? out : nullptr,
+                  kind == kMoments ? out : nullptr);
+  };
+  if constexpr (sizeof(typename M::word) == 4) {
+    if (pairs > 4 * (uint64_t)(num_cus > 0 ? num_cus : 1)) {
+      const size_t lds = (size_t)block.x / kWave * 2 * kFamStage * sizeof(typename M::word);
+      return kind == kMoments ? run(k_fam_normals<M, true, false, true>, lds)
+             : nt             ? run(k_fam_normals<M, false, true, true>, lds)
+                              : run(k_fam_normals<M, false, false, true>, lds);
+    }
+  }
+  return kind == kMoments ? run(k_fam_normals<M, true, false, false>, 0)
+         : nt             ? run(k_fam_normals<M, false, true, false>, 0)
+                          : run(k_fam_normals<M, false, false, false>, 0);
+}
+
 }  // namespace
 
 uint32_t family_state_bytes(uint32_t family) {
@@ -1158,18 +1214,10 @@ hipError_t launch_family_generate(uint32_t family, Kind kind, bool fill, const S
     // start inside one leave partial lines, which only cached stores merge.
     const uint64_t row_bytes = n * (family == XG_FAMILY_R64_W64 ? 8 : 4);
     const bool nt = kind == kNormal && (row_bytes | reinterpret_cast<uintptr_t>(out)) % 128 == 0;
-    auto run = [&](auto kernel) {
-      return launch(kernel, grid, block, 0, stream, state, first, count, n, kind == kNormal ? out : nullptr,
-                    kind == kMoments ? out : nullptr);
-    };
     if (family == XG_FAMILY_R64_W32)
-      return kind == kMoments ? run(k_fam_normals<MemberN2048, true, false>)
-             : nt             ? run(k_fam_normals<MemberN2048, false, true>)
-                              : run(k_fam_normals<MemberN2048, false, false>);
+      return launch_fam_normals<MemberN2048>(kind, nt, pairs, num_cus, grid, block, state, first, count, n, out, stream);
     if (family == XG_FAMILY_R64_W64)
-      return kind == kMoments ? run(k_fam_normals<MemberW64, true, false>)
-             : nt             ? run(k_fam_normals<MemberW64, false, true>)
-                              : run(k_fam_normals<MemberW64, false, false>);
+      return launch_fam_normals<MemberW64>(kind, nt, pairs, num_cus, grid, block, state, first, count, n, out, stream);
     return hipErrorInvalidValue;
   }
   if (family == XG_FAMILY_R64_W32 && kind == kU32)

@@ -46,6 +46,7 @@ constexpr uint32_t kChunkOmega = 64u * kOmega;  // Weyl advance per chunk (mod 2
 
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4 __attribute__((ext_vector_type(4), aligned(4)));
 
 // x (I + L^12)(I + R^17): the operator applied to x_{i-s}.
 __device__ __forceinline__ uint32_t op_lag_s(uint32_t v) {
@@ -167,6 +168,8 @@ __device__ __forceinline__ void emit_word(uint32_t *p, uint32_t o) {
 extern __shared__ __align__(16) uint32_t xg_lds[];
 
 __device__ __forceinline__ uint32_t *wave_stage() { return xg_lds + (threadIdx.x >> 6) * 256u; }
+// The normals' two slots per wavefront.
+__device__ __forceinline__ uint32_t *normals_stage() { return xg_lds + (threadIdx.x >> 6) * 512u; }
 
 
 // ---------------------------------------------------------------------------
@@ -357,18 +360,22 @@ __device__ __forceinline__ void serve_words_fill(uint32_t *__restrict__ st, uint
 // ---------------------------------------------------------------------------
 // normals: Box-Muller on consecutive output pairs of the call.
 // ---------------------------------------------------------------------------
-// Two ways to give each lane one pair of the 128-word block lo | hi (lo
-// holds words 0..63, one per lane, hi words 64..127); pair_offset gives the
-// pair's first word within the block.
-//  - LDS (lane j takes words 2j and 2j + 1): four ds_bpermute reads and two
-//    selects.  The fewest VALU instructions: with two or more wavefronts per
-//    SIMD the VALU is the bound and the LDS latency hides (3 % faster than DPP
-//    at four per SIMD).
+// Two ways to give the lanes their pairs of consecutive words.
+//  - LDS: two 128-word blocks are written to the wavefront's LDS a chunk at a
+//    time and read back four consecutive words per lane, two pairs, whose
+//    normals leave as one 16-byte store (consume_quad).  No VALU instruction,
+//    for launches with more than one wavefront per SIMD, where the VALU is the
+//    bound and the LDS latency hides: 4096 x 2^18 normals 825 us and moments
+//    722 (870 and 738 with one block at a time by four ds_bpermute and two
+//    selects, which gather_pair does for what the unrolled loop leaves over).
 //  - DPP (an even lane j takes words j and j + 1, an odd lane j words 63 + j
 //    and 64 + j): each lane needs one word of its neighbour in the same chunk,
 //    which a quad permutation (lanes 2i and 2i + 1 swap) supplies in the VALU,
-//    two more instructions but no LDS round trip to wait for (12 % faster than
-//    LDS at one wavefront per SIMD).
+//    with no LDS round trip to wait for.
+// DPP and LDS in us at 2^19 per stream: 1024 streams normals 489 and 507, moments
+// 462 and 502; 1536 streams 811 and 745, 890 and 776; 2048 streams 890 and 851,
+// 894 and 779.  So the line is one wavefront per SIMD.
+// pair_offset gives the first word of a gather_pair pair within the block.
 template <bool DPP>
 __device__ __forceinline__ uint32_t pair_offset(uint32_t lane) {
   return DPP ? (lane & ~1u) + ((lane & 1u) << 6) : 2u * lane;
@@ -419,6 +426,31 @@ __device__ __forceinline__ void consume_pair(uint32_t e, uint32_t o, uint64_t id
   }
 }
 
+// The two pairs of four consecutive words: their four normals stored at out, or
+// added to the open group.  The store needs the alignment of one value only.
+template <bool MOMENTS, bool NT = true>
+__device__ __forceinline__ void consume_quad(u32x4 w, float *out, Moments &m) {
+  f32x4 z;
+  if constexpr (MOMENTS) {
+    float a, b;
+    box_muller_unordered(w.x, w.y, a, b);
+    group_add(m, a, b);
+    box_muller_unordered(w.z, w.w, a, b);
+    group_add(m, a, b);
+  } else {
+    float a, b;
+    box_muller(w.x, w.y, a, b);
+    z.x = a;
+    z.y = b;
+    box_muller(w.z, w.w, a, b);
+    z.z = a;
+    z.w = b;
+    f32x4 *o = reinterpret_cast<f32x4 *>(out);
+    if constexpr (NT) __builtin_nontemporal_store(z, o);
+    else *o = z;
+  }
+}
+
 // n normals of one stream; MOMENTS: reduce to (sum z, sum z^2) in sums[0..1]
 // instead of storing them.  Consumes 2 ceil(n / 2) words.  DPP picks the
 // pair gather (above).
@@ -440,40 +472,48 @@ __device__ __forceinline__ void serve_normals_from(const StreamState &s0, uint64
   const uint32_t poff = pair_offset<DPP>(lane);
   const uint64_t nouter = UNROLL > 1 ? nsafe / UNROLL : 0;  // UNROLL = 1: the loop after this one
   uint64_t b = 0;
+  auto next_word = [&]() {
+    const uint32_t x = ring_step(g, lane0);
+    const uint32_t w = x + temper_weyl(wbase + wlane);
+    wbase += kChunkOmega;
+    return w;
+  };
   for (uint64_t it = 0; it != nouter; ++it, b += UNROLL) {
+    if constexpr (!DPP && UNROLL > 1) {
 #pragma unroll
-    for (int u = 0; u < UNROLL; ++u) {
-      const uint32_t xa = ring_step(g, lane0);
-      const uint32_t oa = xa + temper_weyl(wbase + wlane);
-      wbase += kChunkOmega;
-      const uint32_t xb = ring_step(g, lane0);
-      const uint32_t ob = xb + temper_weyl(wbase + wlane);
-      wbase += kChunkOmega;
-      uint32_t e, o;
-      gather_pair<DPP>(oa, ob, lane, e, o);
-      consume_pair<MOMENTS, false, NT>(e, o, ((b + u) << 7) + poff, n, out, m);
-      if (MOMENTS && ((u & 3) == 3 || u == UNROLL - 1)) group_close(m);
+      for (int u = 0; u < UNROLL; u += 2) {  // two blocks: four words, so two pairs, per lane
+        uint32_t *stage = normals_stage() + 256u * ((u / 2) & 1);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) stage[64 * c + lane] = next_word();
+        wave_lds_sync();  // the read below takes words other lanes wrote
+        const u32x4 w = *reinterpret_cast<const u32x4 *>(stage + 4 * lane);
+        wave_lds_sync();  // the next writes to this half come after this read
+        consume_quad<MOMENTS, NT>(w, out + (((b + u) << 7) + 4 * lane), m);
+        if (MOMENTS && ((u & 2) || u == UNROLL - 2)) group_close(m);
+      }
+    } else {
+#pragma unroll
+      for (int u = 0; u < UNROLL; ++u) {
+        const uint32_t oa = next_word();
+        const uint32_t ob = next_word();
+        uint32_t e, o;
+        gather_pair<DPP>(oa, ob, lane, e, o);
+        consume_pair<MOMENTS, false, NT>(e, o, ((b + u) << 7) + poff, n, out, m);
+        if (MOMENTS && ((u & 3) == 3 || u == UNROLL - 1)) group_close(m);
+      }
     }
   }
   for (; b != nsafe; ++b) {
-    const uint32_t xa = ring_step(g, lane0);
-    const uint32_t oa = xa + temper_weyl(wbase + wlane);
-    wbase += kChunkOmega;
-    const uint32_t xb = ring_step(g, lane0);
-    const uint32_t ob = xb + temper_weyl(wbase + wlane);
-    wbase += kChunkOmega;
+    const uint32_t oa = next_word();
+    const uint32_t ob = next_word();
     uint32_t e, o;
     gather_pair<DPP>(oa, ob, lane, e, o);
     consume_pair<MOMENTS, false, NT>(e, o, (b << 7) + poff, n, out, m);
     if (MOMENTS) group_close(m);
   }
   for (; b != nblk; ++b) {
-    const uint32_t xa = ring_step(g, lane0);
-    const uint32_t oa = xa + temper_weyl(wbase + wlane);
-    wbase += kChunkOmega;
-    const uint32_t xb = ring_step(g, lane0);
-    const uint32_t ob = xb + temper_weyl(wbase + wlane);
-    wbase += kChunkOmega;
+    const uint32_t oa = next_word();
+    const uint32_t ob = next_word();
     uint32_t e, o;
     gather_pair<DPP>(oa, ob, lane, e, o);
     consume_pair<MOMENTS, true, NT>(e, o, (b << 7) + poff, n, out, m);
@@ -1013,8 +1053,8 @@ hipError_t launch_generate_k(const Shape &sh, dim3 grid, dim3 block, uint32_t *s
   hipError_t e = hipSuccess;
   constexpr bool kWords = KIND == kU32 || KIND == kF32;
   if constexpr (!kWords) {
-    // Normals with fewer than two wavefronts per SIMD: the DPP pair gather.
-    if (count < 8u * (uint64_t)(num_cus > 0 ? num_cus : 1)) {
+    // Normals with at most one wavefront per SIMD: the DPP pair gather.
+    if (count <= 4u * (uint64_t)(num_cus > 0 ? num_cus : 1)) {
       switch (sh.unroll) {
         case 1: return launch((k_generate<KIND, 1, false, true>), grid, block, 0, stream, state, first, count, n, out);
         case 2: return launch((k_generate<KIND, 2, false, true>), grid, block, 0, stream, state, first, count, n, out);
@@ -1033,11 +1073,12 @@ hipError_t launch_generate_k(const Shape &sh, dim3 grid, dim3 block, uint32_t *s
     }
     return e;
   }
+  const size_t stage = kWords ? 0u : (size_t)sh.waves_per_block * 2048u;  // normals_stage
   switch (sh.unroll) {
-    case 1: e = launch((k_generate<KIND, 1, false>), grid, block, 0, stream, state, first, count, n, out); break;
-    case 2: e = launch((k_generate<KIND, 2, false>), grid, block, 0, stream, state, first, count, n, out); break;
-    case 4: e = launch((k_generate<KIND, 4, false>), grid, block, 0, stream, state, first, count, n, out); break;
-    default: e = launch((k_generate<KIND, 8, false>), grid, block, 0, stream, state, first, count, n, out); break;
+    case 1: e = launch((k_generate<KIND, 1, false>), grid, block, stage, stream, state, first, count, n, out); break;
+    case 2: e = launch((k_generate<KIND, 2, false>), grid, block, stage, stream, state, first, count, n, out); break;
+    case 4: e = launch((k_generate<KIND, 4, false>), grid, block, stage, stream, state, first, count, n, out); break;
+    default: e = launch((k_generate<KIND, 8, false>), grid, block, stage, stream, state, first, count, n, out); break;
   }
   return e;
 }
@@ -1145,13 +1186,13 @@ hipError_t launch_rows_cached(Kind kind, uint32_t waves_per_block, uint32_t *sta
                               uint64_t n, void *out, int num_cus, hipStream_t stream) {
   const uint64_t wpb = waves_per_block;
   auto run = [&](auto kernel) {
-    return launch(kernel, dim3((uint32_t)((count + wpb - 1) / wpb)), dim3((uint32_t)(wpb * kWave)), 0, stream, state,
-                  first, count, n, static_cast<uint32_t *>(out));
+    return launch(kernel, dim3((uint32_t)((count + wpb - 1) / wpb)), dim3((uint32_t)(wpb * kWave)),
+                  kind == kNormal ? wpb * 2048 : 0, stream, state, first, count, n, static_cast<uint32_t *>(out));
   };
   if (kind == kU32) return run(k_rows_cached<kU32>);
   if (kind == kF32) return run(k_rows_cached<kF32>);
   // Normals: the pair gather as for launch_generate.
-  const bool dpp = count < 8u * (uint64_t)(num_cus > 0 ? num_cus : 1);
+  const bool dpp = count <= 4u * (uint64_t)(num_cus > 0 ? num_cus : 1);
   return dpp ? run(k_rows_cached<kNormal, true>) : run(k_rows_cached<kNormal, false>);
 }
 
