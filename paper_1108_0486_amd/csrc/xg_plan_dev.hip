@@ -10,10 +10,14 @@
 //
 // Grouping is a sort of 64-bit keys (stream << 32 | request index): the keys
 // are distinct, so any correct sort leaves each stream's requests in array
-// order.  A bitonic network (compare-exchange passes in LDS within a
-// workgroup's 2048 keys, global passes above that) sorts them; the queue items
-// are sorted the same way on (inverted cost << 32 | group << 8 | tile).
-// Prefix sums are three-kernel block scans.
+// order.  The queue items are sorted the same way on (inverted cost << 32 |
+// group << 8 | tile).  Launches bound a plan of ordinary size (3 to 8 us each,
+// most of it not work), so each step does all it can before it needs the whole
+// table again: a sort is one launch over blocks of 1024 keys and one for each
+// eightfold merge, and the producer of a prefix sum's input leaves its block sums.
+// Plan and batch of short requests, 11 launches now and 28 before: 4100
+// requests 126 -> 65 us, 16384 199 -> 126, 65536 281 -> 173,
+// 900000 1130 -> 952.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -26,10 +30,9 @@
 namespace xg {
 namespace {
 
-// Keys one workgroup sorts in LDS (1024 threads, two keys each).  8192-key
-// blocks (64 KB, eight keys per thread) need fewer launches but measured
-// slower: 305 against 249 us of sorting per 65536-request plan.
-constexpr uint32_t kSortBlock = 2048;
+constexpr uint32_t kSortBlock = 1024;    // keys one workgroup sorts (kSortThreads threads, two each)
+constexpr uint32_t kSortThreads = 512;
+constexpr uint32_t kLeastKeys = 2048;    // keys that a table has room for at least
 constexpr uint32_t kScanBlock = 1024;  // elements one scan workgroup covers (256 threads, four each)
 
 // Planner counters (meta words).
@@ -54,393 +57,21 @@ __device__ __forceinline__ uint64_t item_key(uint64_t cost, uint32_t g, uint32_t
   return ((uint64_t)(0xFFFFFFFFu - c) << 32) | ((uint64_t)g << 8) | k;
 }
 
-// ---- bitonic sort of 64-bit keys ------------------------------------------
+// ---- sums and sorts inside a workgroup ---------------------------------------
 
-// One compare-exchange pass of the bitonic network over a[0, n): pair
-// (i, i + j) with bit j of i clear, ascending where bit k of i is clear.
-__global__ __launch_bounds__(256) void k_bitonic_step(uint64_t *__restrict__ a, uint32_t n, uint32_t k,
-                                                      uint32_t j) {
-  const uint32_t t = blockIdx.x * 256u + threadIdx.x;
-  if (t >= n / 2) return;
-  const uint32_t i = ((t & ~(j - 1u)) << 1) | (t & (j - 1u));
-  const uint32_t l = i | j;
-  const bool asc = (i & k) == 0u;
-  const uint64_t x = a[i], y = a[l];
-  if ((x > y) == asc) {
-    a[i] = y;
-    a[l] = x;
-  }
-}
-
-// M consecutive global passes j, j / 2, ..., j / 2^(M-1) of stage k in one
-// launch: the 2^M keys whose indices differ only in those M bits are closed
-// under these passes (and share the direction, since j < k), so each thread
-// loads one such group, runs the M passes in registers and stores it back.
-// Consecutive threads take consecutive indices below j / 2^(M-1), so every
-// load and store is coalesced.
-template <int M>
-__global__ __launch_bounds__(256) void k_bitonic_steps(uint64_t *__restrict__ a, uint32_t n, uint32_t k,
-                                                       uint32_t j) {
-  constexpr uint32_t G = 1u << M;
-  const uint32_t t = blockIdx.x * 256u + threadIdx.x;
-  if (t >= n / G) return;
-  const uint32_t jlo = j >> (M - 1);             // the smallest stride
-  const uint32_t i = ((t / jlo) * (jlo * G)) | (t % jlo);  // M zero bits at the strides' positions
-  const bool asc = (i & k) == 0u;
-  uint64_t v[G];
+// The sum of every thread's v.  wsum holds a value per wavefront.
+template <typename T, uint32_t THREADS>
+__device__ __forceinline__ T wg_sum(T v, T *wsum) {
 #pragma unroll
-  for (uint32_t b = 0; b < G; ++b) v[b] = a[i + b * jlo];
-#pragma unroll
-  for (int m = M - 1; m >= 0; --m) {  // stride jlo 2^m: partners differ in bit m of b
-#pragma unroll
-    for (uint32_t b = 0; b < G; ++b) {
-      if (b & (1u << m)) continue;
-      const uint32_t c = b | (1u << m);
-      const uint64_t x = v[b], y = v[c];
-      if ((x > y) == asc) {
-        v[b] = y;
-        v[c] = x;
-      }
-    }
-  }
-#pragma unroll
-  for (uint32_t b = 0; b < G; ++b) a[i + b * jlo] = v[b];
-}
-
-// The passes with j < kSortBlock, in LDS, on each workgroup's kSortBlock
-// keys: the whole network up to k = kSortBlock when k == 0, else the passes
-// j = kSortBlock / 2 .. 1 of stage k.  Each of the 1024 threads takes
-// kSortBlock / 2048 of a pass's kSortBlock / 2 pairs.
-__global__ __launch_bounds__(1024) void k_bitonic_block(uint64_t *__restrict__ a, uint32_t k_stage) {
-  constexpr uint32_t kPer = kSortBlock / 1024u, kPairs = kSortBlock / 2048u;
-  __shared__ uint64_t s[kSortBlock];
-  const uint32_t t = threadIdx.x;
-  const uint32_t base = blockIdx.x * kSortBlock;
-#pragma unroll
-  for (uint32_t q = 0; q < kPer; ++q) s[t + 1024u * q] = a[base + t + 1024u * q];
+  for (uint32_t d = 32; d; d >>= 1) v += __shfl_xor(v, d);
+  if ((threadIdx.x & 63u) == 0) wsum[threadIdx.x >> 6] = v;
   __syncthreads();
-  const uint32_t k_lo = k_stage ? k_stage : 2u, k_hi = k_stage ? k_stage : kSortBlock;
-  for (uint32_t k = k_lo; k <= k_hi; k <<= 1) {
-    for (uint32_t j = (k_stage ? kSortBlock : k) >> 1; j > 0; j >>= 1) {
+  T all = 0;
 #pragma unroll
-      for (uint32_t q = 0; q < kPairs; ++q) {
-        const uint32_t pr = t + 1024u * q;  // pair number in the block
-        const uint32_t i = ((pr & ~(j - 1u)) << 1) | (pr & (j - 1u));
-        const uint32_t l = i | j;
-        const bool asc = ((base + i) & k) == 0u;
-        const uint64_t x = s[i], y = s[l];
-        if ((x > y) == asc) {
-          s[i] = y;
-          s[l] = x;
-        }
-      }
-      __syncthreads();
-    }
-  }
-#pragma unroll
-  for (uint32_t q = 0; q < kPer; ++q) a[base + t + 1024u * q] = s[t + 1024u * q];
+  for (uint32_t i = 0; i < THREADS / 64; ++i) all += wsum[i];
+  __syncthreads();  // wsum may be reused after this
+  return all;
 }
-
-// Sorts a[0, n) ascending; n is a power of two >= kSortBlock.  The global
-// passes of a stage go three at a time (k_bitonic_steps<3>), then the rest.
-hipError_t bitonic_sort(uint64_t *a, uint32_t n, hipStream_t stream) {
-  hipError_t e = launch(k_bitonic_block, dim3(n / kSortBlock), dim3(1024), 0, stream, a, 0u);
-  for (uint32_t k = 2 * kSortBlock; k <= n && e == hipSuccess; k <<= 1) {
-    uint32_t j = k >> 1;
-    while (j >= kSortBlock && e == hipSuccess) {
-      const uint32_t left = 31u - (uint32_t)__builtin_clz(j / kSortBlock) + 1u;  // passes j .. kSortBlock
-      if (left >= 3) {
-        e = launch(k_bitonic_steps<3>, dim3((n / 8 + 255) / 256), dim3(256), 0, stream, a, n, k, j);
-        j >>= 3;
-      } else if (left == 2) {
-        e = launch(k_bitonic_steps<2>, dim3((n / 4 + 255) / 256), dim3(256), 0, stream, a, n, k, j);
-        j >>= 2;
-      } else {
-        e = launch(k_bitonic_step, dim3((n / 2 + 255) / 256), dim3(256), 0, stream, a, n, k, j);
-        j >>= 1;
-      }
-    }
-    if (e == hipSuccess) e = launch(k_bitonic_block, dim3(n / kSortBlock), dim3(1024), 0, stream, a, k);
-  }
-  return e;
-}
-
-// ---- exclusive prefix sums in place, total at a[n] ---------------------------
-
-// Exclusive scan of the block's 256 values v (one per thread); *total gets
-// their sum.  lds holds 256 values.
-template <typename T>
-__device__ __forceinline__ T block_exclusive(T v, T *lds, T *total) {
-  const uint32_t t = threadIdx.x;
-  lds[t] = v;
-  __syncthreads();
-  for (uint32_t d = 1; d < 256u; d <<= 1) {
-    const T add = t >= d ? lds[t - d] : T(0);
-    __syncthreads();
-    lds[t] += add;
-    __syncthreads();
-  }
-  const T incl = lds[t];
-  *total = lds[255];
-  __syncthreads();  // lds may be reused after this
-  return incl - v;
-}
-
-template <typename T>
-__global__ __launch_bounds__(256) void k_scan_reduce(const T *__restrict__ a, uint32_t n, T *__restrict__ sums) {
-  __shared__ T lds[256];
-  const uint32_t i0 = blockIdx.x * kScanBlock + 4u * threadIdx.x;
-  T v = 0;
-  for (uint32_t q = 0; q < 4u; ++q)
-    if (i0 + q < n) v += a[i0 + q];
-  T total;
-  (void)block_exclusive(v, lds, &total);
-  if (threadIdx.x == 0) sums[blockIdx.x] = total;
-}
-
-// Exclusive scan of nb <= 1024 block sums in one workgroup (four per thread).
-template <typename T>
-__global__ __launch_bounds__(256) void k_scan_sums(T *__restrict__ sums, uint32_t nb) {
-  __shared__ T lds[256];
-  const uint32_t i0 = 4u * threadIdx.x;
-  T x[4], v = 0;
-  for (uint32_t q = 0; q < 4u; ++q) {
-    x[q] = i0 + q < nb ? sums[i0 + q] : T(0);
-    v += x[q];
-  }
-  T total;
-  T run = block_exclusive(v, lds, &total);
-  for (uint32_t q = 0; q < 4u; ++q) {
-    if (i0 + q < nb) sums[i0 + q] = run;
-    run += x[q];
-  }
-}
-
-template <typename T>
-__global__ __launch_bounds__(256) void k_scan_apply(T *__restrict__ a, uint32_t n, const T *__restrict__ sums,
-                                                    uint32_t nb) {
-  __shared__ T lds[256];
-  const uint32_t i0 = blockIdx.x * kScanBlock + 4u * threadIdx.x;
-  T x[4], v = 0;
-  for (uint32_t q = 0; q < 4u; ++q) {
-    x[q] = i0 + q < n ? a[i0 + q] : T(0);
-    v += x[q];
-  }
-  T total;
-  T run = block_exclusive(v, lds, &total) + sums[blockIdx.x];
-  for (uint32_t q = 0; q < 4u; ++q) {
-    if (i0 + q < n) a[i0 + q] = run;
-    run += x[q];
-  }
-  if (blockIdx.x == nb - 1u && threadIdx.x == 0) a[n] = sums[blockIdx.x] + total;
-}
-
-// Exclusive prefix sums of a[0, n) in place and their total at a[n]
-// (n <= kPlanMaxElems; sums holds 1024 values of T).
-template <typename T>
-hipError_t scan(T *a, uint32_t n, T *sums, hipStream_t stream) {
-  const uint32_t nb = n ? (n + kScanBlock - 1) / kScanBlock : 1u;
-  hipError_t e = launch(k_scan_reduce<T>, dim3(nb), dim3(256), 0, stream, a, n, sums);
-  if (e == hipSuccess) e = launch(k_scan_sums<T>, dim3(1), dim3(256), 0, stream, sums, nb);
-  if (e == hipSuccess) e = launch(k_scan_apply<T>, dim3(nb), dim3(256), 0, stream, a, n, sums, nb);
-  return e;
-}
-
-// ---- planner steps -----------------------------------------------------------
-
-__global__ void k_plan_start(uint32_t *__restrict__ work, uint32_t *__restrict__ meta) {
-  if (threadIdx.x < 64) {
-    work[threadIdx.x] = 0u;
-    meta[threadIdx.x] = 0u;
-  }
-}
-
-// keys[i] for i < key_n: request i's (stream << 32 | i), with stream
-// 0xFFFFFFFF (sorted after every valid stream) for a request that fails the
-// checks, and all ones past the table.
-__global__ __launch_bounds__(256) void k_plan_keys(const xg_request *__restrict__ reqs, uint32_t num_reqs,
-                                                   uint64_t num_streams, uint64_t *__restrict__ keys,
-                                                   uint32_t key_n, uint32_t *__restrict__ work,
-                                                   uint32_t *__restrict__ meta) {
-  const uint32_t i = blockIdx.x * 256u + threadIdx.x;
-  if (i >= key_n) return;
-  uint64_t key = ~0ull;
-  bool valid = false;
-  if (i < num_reqs) {
-    const xg_request q = reqs[i];
-    valid = q.stream < num_streams && q.dtype <= XG_NORMAL && q.flags == 0u;
-    key = ((valid ? q.stream : 0xFFFFFFFFull) << 32) | i;
-    if (!valid) atomicOr(&work[1], 1u);
-  }
-  keys[i] = key;
-  const uint64_t mask = __ballot(valid);
-  if ((threadIdx.x & 63u) == 0 && mask) atomicAdd(&meta[kMetaValid], (uint32_t)__popcll(mask));
-}
-
-// For sorted position i: heads[i] = 1 where a group starts, costs[i] = the
-// request's cost (both 0 past the valid requests).
-__global__ __launch_bounds__(256) void k_plan_heads(const xg_request *__restrict__ reqs, uint32_t num_reqs,
-                                                    const uint64_t *__restrict__ keys,
-                                                    const uint32_t *__restrict__ meta, uint32_t *__restrict__ heads,
-                                                    uint64_t *__restrict__ costs) {
-  const uint32_t i = blockIdx.x * 256u + threadIdx.x;
-  if (i >= num_reqs) return;
-  const uint32_t valid = meta[kMetaValid];
-  uint32_t head = 0;
-  uint64_t cost = 0;
-  if (i < valid) {
-    const uint64_t k = keys[i];
-    head = i == 0 || (k >> 32) != (keys[i - 1] >> 32);
-    const xg_request q = reqs[(uint32_t)k];
-    cost = cost_of(q.n, q.dtype);
-  }
-  heads[i] = head;
-  costs[i] = cost;
-}
-
-// After the scan of heads: hp[g] = first sorted position of group g, and
-// hp[G] = the number of valid requests.
-__global__ __launch_bounds__(256) void k_plan_groups(uint32_t num_reqs, const uint32_t *__restrict__ heads,
-                                                     const uint32_t *__restrict__ meta, uint32_t *__restrict__ hp) {
-  const uint32_t i = blockIdx.x * 256u + threadIdx.x;
-  if (i >= num_reqs) return;
-  if (heads[i + 1] != heads[i]) hp[heads[i]] = i;
-  if (i == 0) hp[heads[num_reqs]] = meta[kMetaValid];
-}
-
-// tiles[g] = the tiles group g asks for: ceil(words / L) for a group of one
-// request split into 2 .. kMaxSegments tiles, else 0.
-__global__ __launch_bounds__(256) void k_plan_want(const xg_request *__restrict__ reqs, uint32_t num_reqs,
-                                                   const uint64_t *__restrict__ keys,
-                                                   const uint32_t *__restrict__ heads,
-                                                   const uint32_t *__restrict__ hp, uint64_t tile_words,
-                                                   uint32_t *__restrict__ tiles) {
-  const uint32_t g = blockIdx.x * 256u + threadIdx.x;
-  if (g >= num_reqs) return;
-  uint32_t want = 0;
-  if (g < heads[num_reqs] && tile_words && hp[g + 1] - hp[g] == 1u) {
-    const xg_request q = reqs[(uint32_t)keys[hp[g]]];
-    const uint64_t parts = (words_of(q.n, q.dtype) + tile_words - 1) / tile_words;
-    if (parts > 1 && parts <= kMaxSegments) want = (uint32_t)parts;
-  }
-  tiles[g] = want;
-}
-
-// After the scan of tiles: groups split in order while their tiles fit
-// max_tiles slots; meta[kMetaTiles] = the slots so used.
-__global__ __launch_bounds__(256) void k_plan_budget(uint32_t num_reqs, const uint32_t *__restrict__ tiles,
-                                                     uint32_t max_tiles, uint32_t *__restrict__ meta) {
-  const uint32_t g = blockIdx.x * 256u + threadIdx.x;
-  if (g > num_reqs) return;
-  const uint32_t v = tiles[g];
-  if (v <= max_tiles && v) atomicMax(&meta[kMetaTiles], v);
-}
-
-__device__ __forceinline__ bool group_split(const uint32_t *tiles, uint32_t g, uint32_t used) {
-  return tiles[g + 1] != tiles[g] && tiles[g + 1] <= used;
-}
-
-__global__ __launch_bounds__(256) void k_fill_ones(uint64_t *__restrict__ a, uint32_t n) {
-  const uint32_t i = blockIdx.x * 256u + threadIdx.x;
-  if (i < n) a[i] = ~0ull;
-}
-
-__global__ __launch_bounds__(256) void k_fill_zero(uint32_t *__restrict__ a, uint32_t n) {
-  const uint32_t i = blockIdx.x * 256u + threadIdx.x;
-  if (i < n) a[i] = 0u;
-}
-
-// Queue items: tile k of split group g at slot tiles[g] + k, every other group
-// g at tile_cap + g (unused places keep all ones and sort last).
-__global__ __launch_bounds__(256) void k_plan_items(const xg_request *__restrict__ reqs, uint32_t num_reqs,
-                                                    const uint64_t *__restrict__ keys,
-                                                    const uint32_t *__restrict__ heads,
-                                                    const uint64_t *__restrict__ costs,
-                                                    const uint32_t *__restrict__ hp,
-                                                    const uint32_t *__restrict__ tiles, uint64_t tile_words,
-                                                    uint32_t tile_cap, uint32_t *__restrict__ meta,
-                                                    uint64_t *__restrict__ items) {
-  const uint32_t g = blockIdx.x * 256u + threadIdx.x;
-  if (g >= num_reqs || g >= heads[num_reqs]) return;
-  if (group_split(tiles, g, meta[kMetaTiles])) {
-    const xg_request q = reqs[(uint32_t)keys[hp[g]]];
-    const uint32_t t = tiles[g + 1] - tiles[g];
-    for (uint32_t k = 0; k < t; ++k) {
-      const uint64_t first = k * tile_words;
-      const uint64_t nk = q.n - first < tile_words ? q.n - first : tile_words;
-      items[tiles[g] + k] = item_key(cost_of(nk, q.dtype), g, k);
-    }
-    atomicAdd(&meta[kMetaItems], t);
-  } else {
-    items[tile_cap + g] = item_key(costs[hp[g + 1]] - costs[hp[g]], g, 0);
-    atomicAdd(&meta[kMetaItems], 1u);
-  }
-}
-
-// offs[p] = table entries of sorted item p (0 past the items).
-__global__ __launch_bounds__(256) void k_plan_counts(uint32_t item_n, const uint64_t *__restrict__ items,
-                                                     const uint32_t *__restrict__ hp,
-                                                     const uint32_t *__restrict__ tiles,
-                                                     const uint32_t *__restrict__ meta, uint32_t *__restrict__ offs) {
-  const uint32_t p = blockIdx.x * 256u + threadIdx.x;
-  if (p >= item_n) return;
-  uint32_t cnt = 0;
-  if (p < meta[kMetaItems]) {
-    const uint32_t g = (uint32_t)items[p] >> 8;
-    cnt = group_split(tiles, g, meta[kMetaTiles]) ? 1u : hp[g + 1] - hp[g];
-  }
-  offs[p] = cnt;
-}
-
-// Table entry e: the j-th request of its item's group, or the item's tile as a
-// segment entry.  Entry 0 also publishes the counts for the batch kernel.
-__global__ __launch_bounds__(256) void k_plan_emit(const xg_request *__restrict__ reqs,
-                                                   const uint64_t *__restrict__ keys,
-                                                   const uint32_t *__restrict__ hp,
-                                                   const uint32_t *__restrict__ tiles, uint64_t tile_words,
-                                                   const uint64_t *__restrict__ items, uint32_t item_n,
-                                                   const uint32_t *__restrict__ offs,
-                                                   const uint32_t *__restrict__ meta,
-                                                   xg_request *__restrict__ table, uint32_t *__restrict__ work) {
-  const uint32_t e = blockIdx.x * 256u + threadIdx.x;
-  const uint32_t num_items = meta[kMetaItems], entries = offs[item_n];
-  if (e == 0) {
-    work[2] = num_items;
-    work[3] = entries;
-  }
-  if (e >= entries) return;
-  // The item holding entry e: the last p < num_items with offs[p] <= e.
-  uint32_t lo = 0, hi = num_items;  // offs[lo] <= e < offs[hi]
-  while (hi - lo > 1u) {
-    const uint32_t mid = (lo + hi) >> 1;
-    if (offs[mid] <= e) lo = mid;
-    else hi = mid;
-  }
-  const uint64_t it = items[lo];
-  const uint32_t g = (uint32_t)it >> 8, k = (uint32_t)it & 0xFFu;
-  if (group_split(tiles, g, meta[kMetaTiles])) {
-    xg_request q = reqs[(uint32_t)keys[hp[g]]];
-    const uint64_t first = k * tile_words;
-    const uint32_t t = tiles[g + 1] - tiles[g], slot = tiles[g] + k;
-    q.n = q.n - first < tile_words ? q.n - first : tile_words;
-    q.out_offset += first;
-    q.flags = kReqSegment | (k << 8) | (slot << 16) | (k + 1 == t ? kReqLast : 0u);
-    table[e] = q;
-  } else {
-    table[e] = reqs[(uint32_t)keys[hp[g] + (e - offs[lo])]];
-  }
-}
-
-// ---- small tables: the whole plan in one workgroup ---------------------------
-
-// Table entries plus tile slots that one workgroup plans with a single launch
-// instead of the multi-kernel sequence above (the plan is the same): N
-// elements, EPT = N / THREADS consecutive ones per thread, N from 256 to 4096 (160
-// KB of LDS).  Latency bounds it, so the sorts keep their keys in registers
-// and exchange them by lane swaps; only distances beyond a wavefront go
-// through LDS, with one barrier each.  384 requests take 9 us (24 us with
-// every pass through LDS in 1024 elements).
-constexpr uint32_t kSmallPlanMax = 4096;
 
 // Exclusive prefix sums of the workgroup's values, EPT consecutive ones per
 // thread (v[e] is element EPT t + e): on return v[e] holds the sum of every
@@ -529,6 +160,376 @@ __device__ __forceinline__ void wg_sort(uint64_t (&k)[N / THREADS], uint64_t *ld
   sort_passes<N, THREADS, K, K / 2>(k, lds, half);
   if constexpr (K < N) wg_sort<N, THREADS, 2 * K>(k, lds, half);
 }
+
+// ---- sort of 64-bit keys over the device -------------------------------------
+
+// Sorts each kSortBlock places of a table of keys, src to dst (which may be the
+// same).  REQS: key i is request i's (stream << 32 | i), with stream 0xFFFFFFFF
+// (sorted after every valid stream) for a request that fails the checks and all
+// ones past the table; the launch also clears the counters.
+template <bool REQS>
+__global__ __launch_bounds__(kSortThreads) void k_sort_blocks(const uint64_t *src, uint64_t *dst,
+                                                      const xg_request *__restrict__ reqs, uint32_t num_reqs,
+                                                      uint64_t num_streams, uint32_t *__restrict__ work,
+                                                      uint32_t *__restrict__ meta) {
+  __shared__ uint64_t lds[2 * kSortBlock];
+  const uint32_t t = threadIdx.x, i0 = blockIdx.x * kSortBlock + 2u * t;
+  uint64_t key[2];
+  uint32_t half = 0;
+#pragma unroll
+  for (uint32_t e = 0; e < 2u; ++e) {
+    if constexpr (REQS) {
+      const uint32_t i = i0 + e;
+      key[e] = ~0ull;
+      if (i < num_reqs) {
+        const xg_request q = reqs[i];
+        const bool valid = q.stream < num_streams && q.dtype <= XG_NORMAL && q.flags == 0u;
+        key[e] = ((valid ? q.stream : 0xFFFFFFFFull) << 32) | i;
+      }
+    } else {
+      key[e] = src[i0 + e];
+    }
+  }
+  if (REQS && blockIdx.x == 0 && t < 64u) {
+    work[t] = 0u;
+    meta[t] = 0u;
+  }
+  wg_sort<kSortBlock, kSortThreads>(key, lds, half);
+#pragma unroll
+  for (uint32_t e = 0; e < 2u; ++e) dst[i0 + e] = key[e];
+}
+
+// Merges each W sorted runs of 2^run_log2 keys of src into one of dst: a key's
+// place is its own in its run plus, for each other run, the keys there that
+// come before it (equal keys, the all-ones ones, in run order), found by W
+// searches side by side.  The chain of a search's loads bounds it while the table is
+// small (8192 keys of 1024 in 5.4 us, 16384 in 8 us; the bitonic passes that
+// one merge stands for took seven launches, 35 us), the number of loads when it
+// is large.
+template <uint32_t W>
+__global__ __launch_bounds__(256) void k_merge(const uint64_t *__restrict__ src, uint64_t *__restrict__ dst,
+                                               uint32_t n, uint32_t run_log2) {
+  const uint32_t i = blockIdx.x * 256u + threadIdx.x;
+  if (i >= n) return;
+  const uint32_t run = 1u << run_log2, base = i & ~(W * run - 1u);
+  const uint32_t mine = (i - base) >> run_log2;
+  const uint64_t x = src[i];
+  uint32_t at[W];  // keys of run q known to come before x
+#pragma unroll
+  for (uint32_t q = 0; q < W; ++q) at[q] = 0;
+  for (uint32_t step = run >> 1; step; step >>= 1) {
+#pragma unroll
+    for (uint32_t q = 0; q < W; ++q) {
+      const uint64_t y = src[base + (q << run_log2) + at[q] + step - 1u];
+      if (y < x || (y == x && q < mine)) at[q] += step;
+    }
+  }
+  uint32_t place = base + (i & (run - 1u));
+#pragma unroll
+  for (uint32_t q = 0; q < W; ++q) {
+    const uint64_t y = src[base + (q << run_log2) + at[q]];
+    const uint32_t before = at[q] + (y < x || (y == x && q < mine) ? 1u : 0u);
+    place += q == mine ? 0u : before;
+  }
+  dst[place] = x;
+}
+
+uint32_t log2_of(uint32_t pow2) { return 31u - (uint32_t)__builtin_clz(pow2); }
+
+// Sorts a[0, n) ascending, n a power of two >= kSortBlock, with tmp for n keys;
+// with reqs the keys are theirs (k_sort_blocks).  Merges are eightfold, or
+// sixteenfold where one then ends the sort; wider ones search more than a pass
+// saves (plan and batch of 900000 short requests: 952 us with eight, 1049 with
+// sixteen).
+hipError_t sort_keys(uint64_t *a, uint64_t *tmp, uint32_t n, const xg_request *reqs, uint32_t num_reqs,
+                     uint64_t num_streams, uint32_t *work, uint32_t *meta, hipStream_t stream) {
+  uint32_t run = log2_of(kSortBlock), left = log2_of(n) - run;  // merges left, in powers of two
+  const uint32_t most = left == 4 ? 4 : 3, passes = (left + most - 1) / most;
+  uint64_t *at = passes % 2 ? tmp : a;  // so that the last pass ends in a
+  const dim3 blocks(n / kSortBlock), threads(kSortThreads);
+  hipError_t e =
+      reqs ? launch(k_sort_blocks<true>, blocks, threads, 0, stream, a, at, reqs, num_reqs, num_streams, work, meta)
+           : launch(k_sort_blocks<false>, blocks, threads, 0, stream, a, at, reqs, num_reqs, num_streams, work, meta);
+  while (left && e == hipSuccess) {
+    uint64_t *to = at == a ? tmp : a;
+    const dim3 grid((n + 255) / 256), b256(256);
+    const uint32_t by = left < most ? left : most;
+    e = by == 4   ? launch(k_merge<16>, grid, b256, 0, stream, at, to, n, run)
+        : by == 3 ? launch(k_merge<8>, grid, b256, 0, stream, at, to, n, run)
+        : by == 2 ? launch(k_merge<4>, grid, b256, 0, stream, at, to, n, run)
+                  : launch(k_merge<2>, grid, b256, 0, stream, at, to, n, run);
+    at = to;
+    run += by;
+    left -= by;
+  }
+  return e;
+}
+
+// ---- exclusive prefix sums in place, total at a[n] ---------------------------
+
+// The kernel that writes a[0, n) leaves the sum of each kScanBlock values in
+// sums, and the scan's workgroups add up the sums before their own (at most
+// 1024 of them).
+template <typename T>
+__device__ __forceinline__ T sums_before(const T *__restrict__ sums, T *wsum) {
+  T v = 0;
+  for (uint32_t b = threadIdx.x; b < blockIdx.x; b += 256u) v += sums[b];
+  return wg_sum<T, 256>(v, wsum);
+}
+
+// Exclusive prefix sums of this workgroup's kScanBlock values of a[0, n), four
+// per thread, in x (0 past n) and in a; the last workgroup writes a[n].
+template <typename T>
+__device__ __forceinline__ void scan_block(T *__restrict__ a, uint32_t n, const T *__restrict__ sums, T (&x)[4],
+                                           T *wsum) {
+  const uint32_t i0 = blockIdx.x * kScanBlock + 4u * threadIdx.x;
+#pragma unroll
+  for (uint32_t q = 0; q < 4u; ++q) x[q] = i0 + q < n ? a[i0 + q] : T(0);
+  const T base = sums_before(sums, wsum);
+  T total;
+  wg_exclusive<T, 256, 4>(x, wsum, &total);
+#pragma unroll
+  for (uint32_t q = 0; q < 4u; ++q) {
+    x[q] += base;
+    if (i0 + q < n) a[i0 + q] = x[q];
+  }
+  if (blockIdx.x == gridDim.x - 1u && threadIdx.x == 0) a[n] = base + total;
+}
+
+__global__ __launch_bounds__(256) void k_scan(uint32_t *__restrict__ a, uint32_t n,
+                                              const uint32_t *__restrict__ sums) {
+  __shared__ uint32_t wsum[4];
+  uint32_t x[4];
+  scan_block(a, n, sums, x, wsum);
+}
+
+// ---- planner steps -----------------------------------------------------------
+
+// For sorted position i: heads[i] = 1 where a group starts, costs[i] = the
+// request's cost (both 0 past the valid requests), and their sums by
+// kScanBlock; the number of valid requests, and the error word where one is not.
+__global__ __launch_bounds__(256) void k_plan_heads(const xg_request *__restrict__ reqs, uint32_t num_reqs,
+                                                    const uint64_t *__restrict__ keys, uint32_t *__restrict__ meta,
+                                                    uint32_t *__restrict__ work, uint32_t *__restrict__ heads,
+                                                    uint64_t *__restrict__ costs, uint32_t *__restrict__ head_sums,
+                                                    uint64_t *__restrict__ cost_sums) {
+  __shared__ uint32_t wsum32[4];
+  __shared__ uint64_t wsum[4];
+  const uint32_t i0 = blockIdx.x * kScanBlock + 4u * threadIdx.x;
+  uint32_t my_heads = 0;
+  uint64_t my_costs = 0;
+#pragma unroll
+  for (uint32_t e = 0; e < 4u; ++e) {
+    const uint32_t i = i0 + e;
+    if (i >= num_reqs) continue;
+    const uint64_t k = keys[i];
+    uint32_t head = 0;
+    uint64_t cost = 0;
+    if ((k >> 32) != 0xFFFFFFFFull) {
+      head = i == 0 || (k >> 32) != (keys[i - 1] >> 32);
+      const xg_request q = reqs[(uint32_t)k];
+      cost = cost_of(q.n, q.dtype);
+      if (i + 1 == num_reqs || (keys[i + 1] >> 32) == 0xFFFFFFFFull) meta[kMetaValid] = i + 1;
+    } else if (i + 1 == num_reqs) {
+      work[1] = 1u;
+    }
+    heads[i] = head;
+    costs[i] = cost;
+    my_heads += head;
+    my_costs += cost;
+  }
+  const uint32_t h = wg_sum<uint32_t, 256>(my_heads, wsum32);
+  const uint64_t c = wg_sum<uint64_t, 256>(my_costs, wsum);
+  if (threadIdx.x == 0) {
+    head_sums[blockIdx.x] = h;
+    cost_sums[blockIdx.x] = c;
+  }
+}
+
+// Prefix sums of heads (each request's group) and costs; hp[g] = first sorted
+// position of group g, and hp[G] = the number of valid requests; every tile
+// prefix sum 0 where there are no tiles, and every queue item all ones.
+__global__ __launch_bounds__(256) void k_plan_groups(uint32_t num_reqs, uint32_t *__restrict__ heads,
+                                                     uint64_t *__restrict__ costs,
+                                                     const uint32_t *__restrict__ head_sums,
+                                                     const uint64_t *__restrict__ cost_sums,
+                                                     const uint32_t *__restrict__ meta, uint32_t *__restrict__ hp,
+                                                     uint32_t *__restrict__ zero_tiles,
+                                                     uint64_t *__restrict__ items, uint32_t item_n) {
+  __shared__ uint32_t wsum32[4];
+  __shared__ uint64_t wsum[4];
+  const uint32_t i0 = blockIdx.x * kScanBlock + 4u * threadIdx.x;
+  bool head[4];
+#pragma unroll
+  for (uint32_t q = 0; q < 4u; ++q) head[q] = i0 + q < num_reqs && heads[i0 + q] != 0u;
+  uint32_t g[4];
+  uint64_t c[4];
+  scan_block(heads, num_reqs, head_sums, g, wsum32);
+  scan_block(costs, num_reqs, cost_sums, c, wsum);
+#pragma unroll
+  for (uint32_t q = 0; q < 4u; ++q)
+    if (head[q]) hp[g[q]] = i0 + q;
+  if (blockIdx.x == gridDim.x - 1u && threadIdx.x == 0) hp[heads[num_reqs]] = meta[kMetaValid];
+  const uint32_t step = gridDim.x * 256u, t = blockIdx.x * 256u + threadIdx.x;
+  if (zero_tiles)
+    for (uint32_t i = t; i <= num_reqs; i += step) zero_tiles[i] = 0u;
+  for (uint32_t i = t; i < item_n; i += step) items[i] = ~0ull;
+}
+
+// tiles[g] = the tiles group g asks for: ceil(words / L) for a group of one
+// request split into 2 .. kMaxSegments tiles, else 0; and their sums.
+__global__ __launch_bounds__(256) void k_plan_want(const xg_request *__restrict__ reqs, uint32_t num_reqs,
+                                                   const uint64_t *__restrict__ keys,
+                                                   const uint32_t *__restrict__ heads,
+                                                   const uint32_t *__restrict__ hp, uint64_t tile_words,
+                                                   uint32_t *__restrict__ tiles, uint32_t *__restrict__ sums) {
+  __shared__ uint32_t wsum[4];
+  const uint32_t g0 = blockIdx.x * kScanBlock + 4u * threadIdx.x, num_groups = heads[num_reqs];
+  uint32_t mine = 0;
+#pragma unroll
+  for (uint32_t e = 0; e < 4u; ++e) {
+    const uint32_t g = g0 + e;
+    if (g >= num_reqs) continue;
+    uint32_t want = 0;
+    if (g < num_groups && hp[g + 1] - hp[g] == 1u) {
+      const xg_request q = reqs[(uint32_t)keys[hp[g]]];
+      const uint64_t parts = (words_of(q.n, q.dtype) + tile_words - 1) / tile_words;
+      if (parts > 1 && parts <= kMaxSegments) want = (uint32_t)parts;
+    }
+    tiles[g] = want;
+    mine += want;
+  }
+  const uint32_t all = wg_sum<uint32_t, 256>(mine, wsum);
+  if (threadIdx.x == 0) sums[blockIdx.x] = all;
+}
+
+// Prefix sums of tiles.  Groups split in order while their tiles fit max_tiles
+// slots; meta[kMetaTiles] = the slots so used.
+__global__ __launch_bounds__(256) void k_plan_budget(uint32_t num_reqs, uint32_t *__restrict__ tiles,
+                                                     const uint32_t *__restrict__ sums, uint32_t max_tiles,
+                                                     uint32_t *__restrict__ meta) {
+  __shared__ uint32_t wsum[4];
+  const uint32_t i0 = blockIdx.x * kScanBlock + 4u * threadIdx.x;
+  uint32_t x[4];
+  scan_block(tiles, num_reqs, sums, x, wsum);
+  uint32_t most = 0;
+#pragma unroll
+  for (uint32_t q = 0; q < 4u; ++q)
+    if (i0 + q < num_reqs && x[q] <= max_tiles) most = x[q];
+  if (blockIdx.x == gridDim.x - 1u && threadIdx.x == 0 && tiles[num_reqs] <= max_tiles) most = tiles[num_reqs];
+#pragma unroll
+  for (uint32_t d = 32; d; d >>= 1) {
+    const uint32_t other = __shfl_xor(most, d);
+    most = other > most ? other : most;
+  }
+  if ((threadIdx.x & 63u) == 0 && most) atomicMax(&meta[kMetaTiles], most);
+}
+
+__device__ __forceinline__ bool group_split(const uint32_t *tiles, uint32_t g, uint32_t used) {
+  return tiles[g + 1] != tiles[g] && tiles[g + 1] <= used;
+}
+
+// Queue items: tile k of split group g at slot tiles[g] + k, every other group
+// g at tile_cap + g (unused places keep all ones and sort last).
+__global__ __launch_bounds__(256) void k_plan_items(const xg_request *__restrict__ reqs, uint32_t num_reqs,
+                                                    const uint64_t *__restrict__ keys,
+                                                    const uint32_t *__restrict__ heads,
+                                                    const uint64_t *__restrict__ costs,
+                                                    const uint32_t *__restrict__ hp,
+                                                    const uint32_t *__restrict__ tiles, uint64_t tile_words,
+                                                    uint32_t tile_cap, uint32_t *__restrict__ meta,
+                                                    uint64_t *__restrict__ items) {
+  const uint32_t g = blockIdx.x * 256u + threadIdx.x;
+  if (g >= num_reqs || g >= heads[num_reqs]) return;
+  if (group_split(tiles, g, meta[kMetaTiles])) {
+    const xg_request q = reqs[(uint32_t)keys[hp[g]]];
+    const uint32_t t = tiles[g + 1] - tiles[g];
+    for (uint32_t k = 0; k < t; ++k) {
+      const uint64_t first = k * tile_words;
+      const uint64_t nk = q.n - first < tile_words ? q.n - first : tile_words;
+      items[tiles[g] + k] = item_key(cost_of(nk, q.dtype), g, k);
+    }
+    atomicAdd(&meta[kMetaItems], t);
+  } else {
+    items[tile_cap + g] = item_key(costs[hp[g + 1]] - costs[hp[g]], g, 0);
+    atomicAdd(&meta[kMetaItems], 1u);
+  }
+}
+
+// offs[p] = table entries of sorted item p (0 past the items), and their sums.
+__global__ __launch_bounds__(256) void k_plan_counts(uint32_t item_n, const uint64_t *__restrict__ items,
+                                                     const uint32_t *__restrict__ hp,
+                                                     const uint32_t *__restrict__ tiles,
+                                                     const uint32_t *__restrict__ meta, uint32_t *__restrict__ offs,
+                                                     uint32_t *__restrict__ sums) {
+  __shared__ uint32_t wsum[4];
+  const uint32_t p0 = blockIdx.x * kScanBlock + 4u * threadIdx.x;
+  uint32_t mine = 0;
+#pragma unroll
+  for (uint32_t e = 0; e < 4u; ++e) {
+    const uint32_t p = p0 + e;
+    if (p >= item_n) continue;
+    uint32_t cnt = 0;
+    if (p < meta[kMetaItems]) {
+      const uint32_t g = (uint32_t)items[p] >> 8;
+      cnt = group_split(tiles, g, meta[kMetaTiles]) ? 1u : hp[g + 1] - hp[g];
+    }
+    offs[p] = cnt;
+    mine += cnt;
+  }
+  const uint32_t all = wg_sum<uint32_t, 256>(mine, wsum);
+  if (threadIdx.x == 0) sums[blockIdx.x] = all;
+}
+
+// Table entry e: the j-th request of its item's group, or the item's tile as a
+// segment entry.  Entry 0 also publishes the counts for the batch kernel.
+__global__ __launch_bounds__(256) void k_plan_emit(const xg_request *__restrict__ reqs,
+                                                   const uint64_t *__restrict__ keys,
+                                                   const uint32_t *__restrict__ hp,
+                                                   const uint32_t *__restrict__ tiles, uint64_t tile_words,
+                                                   const uint64_t *__restrict__ items, uint32_t item_n,
+                                                   const uint32_t *__restrict__ offs,
+                                                   const uint32_t *__restrict__ meta,
+                                                   xg_request *__restrict__ table, uint32_t *__restrict__ work) {
+  const uint32_t e = blockIdx.x * 256u + threadIdx.x;
+  const uint32_t num_items = meta[kMetaItems], entries = offs[item_n];
+  if (e == 0) {
+    work[2] = num_items;
+    work[3] = entries;
+  }
+  if (e >= entries) return;
+  // The item holding entry e: the last p < num_items with offs[p] <= e.
+  uint32_t lo = 0, hi = num_items;  // offs[lo] <= e < offs[hi]
+  while (hi - lo > 1u) {
+    const uint32_t mid = (lo + hi) >> 1;
+    if (offs[mid] <= e) lo = mid;
+    else hi = mid;
+  }
+  const uint64_t it = items[lo];
+  const uint32_t g = (uint32_t)it >> 8, k = (uint32_t)it & 0xFFu;
+  if (group_split(tiles, g, meta[kMetaTiles])) {
+    xg_request q = reqs[(uint32_t)keys[hp[g]]];
+    const uint64_t first = k * tile_words;
+    const uint32_t t = tiles[g + 1] - tiles[g], slot = tiles[g] + k;
+    q.n = q.n - first < tile_words ? q.n - first : tile_words;
+    q.out_offset += first;
+    q.flags = kReqSegment | (k << 8) | (slot << 16) | (k + 1 == t ? kReqLast : 0u);
+    table[e] = q;
+  } else {
+    table[e] = reqs[(uint32_t)keys[hp[g] + (e - offs[lo])]];
+  }
+}
+
+// ---- small tables: the whole plan in one workgroup ---------------------------
+
+// Table entries plus tile slots that one workgroup plans with a single launch
+// instead of the multi-kernel sequence above (the plan is the same): N
+// elements, EPT = N / THREADS consecutive ones per thread, N from 256 to 4096 (160
+// KB of LDS).  Latency bounds it, so the sorts keep their keys in registers
+// and exchange them by lane swaps; only distances beyond a wavefront go
+// through LDS, with one barrier each.  384 requests take 9 us (24 us with
+// every pass through LDS in 1024 elements).
+constexpr uint32_t kSmallPlanMax = 4096;
 
 // Adds the workgroup's flags to *count: one atomic per wavefront.
 template <uint32_t EPT>
@@ -762,9 +763,9 @@ size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
 
 PlanLayout plan_layout(uint32_t max_reqs, uint32_t max_tiles, uint32_t state_bytes, uint32_t jump_bytes) {
   PlanLayout l;
-  l.key_cap = pow2_at_least(max_reqs > kSortBlock ? max_reqs : kSortBlock);
+  l.key_cap = pow2_at_least(max_reqs > kLeastKeys ? max_reqs : kLeastKeys);
   const uint32_t items = max_reqs + max_tiles;
-  l.item_cap = pow2_at_least(items > kSortBlock ? items : kSortBlock);
+  l.item_cap = pow2_at_least(items > kLeastKeys ? items : kLeastKeys);
   size_t o = 0;
   auto take = [&](size_t bytes) {
     const size_t at = o;
@@ -823,41 +824,42 @@ hipError_t launch_plan(const PlanPtrs &p, const PlanLayout &l, const xg_request 
     if (elems <= 2048) return run(k_plan_small<2048, 1024>, 1024);
     return run(k_plan_small<4096, 1024>, 1024);
   }
-  const uint32_t key_n = pow2_at_least(num_reqs > kSortBlock ? num_reqs : kSortBlock);
+  const uint32_t key_n = pow2_at_least(num_reqs > kLeastKeys ? num_reqs : kLeastKeys);
   const uint32_t items = num_reqs + tile_cap;
-  const uint32_t item_n = pow2_at_least(items > kSortBlock ? items : kSortBlock);
-  if (key_n > l.key_cap || item_n > l.item_cap || items > kPlanMaxElems) return hipErrorInvalidValue;
+  const uint32_t item_n = pow2_at_least(items > kLeastKeys ? items : kLeastKeys);
+  // The sorts' second buffer is the table, which the last step writes; the
+  // head sums lie in offs, which the items' counts fill later.
+  const uint32_t sorted = key_n > item_n ? key_n : item_n;
+  if (key_n > l.key_cap || item_n > l.item_cap || items > kPlanMaxElems ||
+      (uint64_t)sorted * 8 > l.sums - l.table || l.table - l.offs < 1024 * 4)
+    return hipErrorInvalidValue;
   const dim3 b256(256);
   auto grid = [](uint32_t n) { return dim3(n ? (n + 255) / 256 : 1u); };
+  auto scan_grid = [](uint32_t n) { return dim3(n ? (n + kScanBlock - 1) / kScanBlock : 1u); };
+  uint64_t *tmp = reinterpret_cast<uint64_t *>(p.table);
   uint32_t *u32sums = reinterpret_cast<uint32_t *>(p.sums);
-  hipError_t e = launch(k_plan_start, dim3(1), dim3(64), 0, stream, p.work, p.meta);
+  hipError_t e = sort_keys(p.keys, tmp, key_n, reqs, num_reqs, num_streams, p.work, p.meta, stream);
   if (e == hipSuccess)
-    e = launch(k_plan_keys, grid(key_n), b256, 0, stream, reqs, num_reqs, num_streams, p.keys, key_n, p.work, p.meta);
-  if (e == hipSuccess) e = bitonic_sort(p.keys, key_n, stream);
+    e = launch(k_plan_heads, scan_grid(num_reqs), b256, 0, stream, reqs, num_reqs, p.keys, p.meta, p.work, p.heads,
+               p.costs, p.offs, p.sums);
   if (e == hipSuccess)
-    e = launch(k_plan_heads, grid(num_reqs), b256, 0, stream, reqs, num_reqs, p.keys, p.meta, p.heads, p.costs);
-  if (e == hipSuccess) e = scan<uint32_t>(p.heads, num_reqs, u32sums, stream);
-  if (e == hipSuccess) e = scan<uint64_t>(p.costs, num_reqs, p.sums, stream);
-  if (e == hipSuccess) e = launch(k_plan_groups, grid(num_reqs), b256, 0, stream, num_reqs, p.heads, p.meta, p.hp);
+    e = launch(k_plan_groups, scan_grid(num_reqs), b256, 0, stream, num_reqs, p.heads, p.costs, p.offs, p.sums,
+               p.meta, p.hp, tile_cap ? nullptr : p.tiles, p.items, item_n);
   if (tile_cap) {
     if (e == hipSuccess)
-      e = launch(k_plan_want, grid(num_reqs), b256, 0, stream, reqs, num_reqs, p.keys, p.heads, p.hp, tile_words,
-                 p.tiles);
-    if (e == hipSuccess) e = scan<uint32_t>(p.tiles, num_reqs, u32sums, stream);
+      e = launch(k_plan_want, scan_grid(num_reqs), b256, 0, stream, reqs, num_reqs, p.keys, p.heads, p.hp,
+                 tile_words, p.tiles, u32sums);
     if (e == hipSuccess)
-      e = launch(k_plan_budget, grid(num_reqs + 1), b256, 0, stream, num_reqs, p.tiles, tile_cap, p.meta);
-  } else if (e == hipSuccess) {
-    // no tiles: every group's tile prefix sum is 0
-    e = launch(k_fill_zero, grid(num_reqs + 1), b256, 0, stream, p.tiles, num_reqs + 1);
+      e = launch(k_plan_budget, scan_grid(num_reqs), b256, 0, stream, num_reqs, p.tiles, u32sums, tile_cap, p.meta);
   }
-  if (e == hipSuccess) e = launch(k_fill_ones, grid(item_n), b256, 0, stream, p.items, item_n);
   if (e == hipSuccess)
     e = launch(k_plan_items, grid(num_reqs), b256, 0, stream, reqs, num_reqs, p.keys, p.heads, p.costs, p.hp,
                p.tiles, tile_words, tile_cap, p.meta, p.items);
-  if (e == hipSuccess) e = bitonic_sort(p.items, item_n, stream);
+  if (e == hipSuccess) e = sort_keys(p.items, tmp, item_n, nullptr, 0, 0, p.work, p.meta, stream);
   if (e == hipSuccess)
-    e = launch(k_plan_counts, grid(items), b256, 0, stream, items, p.items, p.hp, p.tiles, p.meta, p.offs);
-  if (e == hipSuccess) e = scan<uint32_t>(p.offs, items, u32sums, stream);
+    e = launch(k_plan_counts, scan_grid(items), b256, 0, stream, items, p.items, p.hp, p.tiles, p.meta, p.offs,
+               u32sums);
+  if (e == hipSuccess) e = launch(k_scan, scan_grid(items), b256, 0, stream, p.offs, items, u32sums);
   if (e == hipSuccess)
     e = launch(k_plan_emit, grid(items), b256, 0, stream, reqs, p.keys, p.hp, p.tiles, tile_words, p.items, items,
                p.offs, p.meta, p.table, p.work);
