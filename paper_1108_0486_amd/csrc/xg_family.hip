@@ -657,7 +657,7 @@ __global__ __launch_bounds__(1024) void k_fam_batch(unsigned char *__restrict__ 
   L.k = 0;
   L.active = true;
   // Queue items are pairs of groups (one per half), largest first; a
-  // wavefront takes `take` consecutive pairs per atomic, as k_batch does.
+  // wavefront takes batch_take consecutive pairs per atomic, as k_batch does.
   // The first pair is the wavefront's own index in the grid; later trips
   // take pairs from the counter, offset by the wavefronts in the grid.
   const uint32_t num_pairs = (uint32_t)((num_groups + 1ull) / 2);
@@ -764,9 +764,7 @@ __global__ __launch_bounds__(1024) void k_fam_batch(unsigned char *__restrict__ 
         }
       }
     }
-    const uint64_t budget = kBatchTakeWords * (p_end - p0);
-    take = 1;
-    while (take < kBatchMaxTake && served * (2u * take) <= budget) take <<= 1;
+    take = batch_take(served, p_end - p0, p0, num_pairs, waves);
     uint32_t c = 0;
     if (L.lane == 0) c = atomicAdd(&work[0], take);
     p0 = waves + (uint32_t)__builtin_amdgcn_readfirstlane((int)c);

@@ -40,12 +40,24 @@ uint32_t auto_waves_per_block(uint64_t count, int num_cus);
 // ones).  With fewer items each wavefront's own rate decides, and eight
 // wavefronts per compute unit at eight chunks per trip serve a group fastest.
 // Neither uses the wide stores: staging through LDS gained nothing.
-// Queue items a batch wavefront takes per atomic: up to kBatchTakeWords
-// words' worth at the size of the items it just served, at most
-// kBatchMaxTake (one counter serves every wavefront, and same-address atomics
-// complete one at a time).
+// Queue items (largest first) a batch wavefront takes on its next trip to the
+// queue, after `served` words in the `items` items from `at` of `all`: a power
+// of two, as many as fit kBatchTakeWords words at the size of the items it just
+// served and at most kBatchMaxTake (one counter serves every wavefront, and
+// same-address atomics complete one at a time), but no more than its share of
+// the items left, which would leave other wavefronts idle (plan and batch of
+// 10000 requests of 2^6 to 2^12 words, without that limit and with it: Section
+// 2's member 130 and 116 us, the 32-bit r = 64 member 159 and 117, the 64-bit
+// one 170 and 120).
 constexpr uint32_t kBatchMaxTake = 16;
 constexpr uint64_t kBatchTakeWords = 65536;
+__host__ __device__ inline uint32_t batch_take(uint64_t served, uint32_t items, uint32_t at, uint32_t all,
+                                               uint32_t waves) {
+  const uint64_t budget = kBatchTakeWords * items, left = all - at;
+  uint32_t take = 1;
+  while (take < kBatchMaxTake && served * (2u * take) <= budget && (uint64_t)waves * (2u * take) <= left) take <<= 1;
+  return take;
+}
 
 constexpr Shape kBatchThroughput{4, 8, 2, 1};
 constexpr Shape kBatchLatency{4, 8, 8, 1};

@@ -87,23 +87,27 @@ __device__ __forceinline__ uint32_t ring_step(Ring &g, bool lane0) {
 __device__ __forceinline__ uint32_t lane_id() { return threadIdx.x & (kWave - 1); }
 
 
-// Writes the 128-word window ending `rem` words into chunk `x` (rem in 1..63),
-// i.e. words [rem, rem + 128) of the concatenation prev | cur | x, as the new
-// linear ring; rem == 0 writes prev | cur.
-__device__ __forceinline__ void store_ring(uint32_t *st, uint32_t prev, uint32_t cur, uint32_t x,
-                                           uint32_t rem, uint32_t lane) {
-  uint32_t lo = prev, hi = cur;
+// Makes prev | cur the 128-word window ending `rem` words into chunk `x` (rem
+// in 1..63), i.e. words [rem, rem + 128) of the concatenation prev | cur | x;
+// rem == 0 leaves them.
+__device__ __forceinline__ void turn_ring(uint32_t &prev, uint32_t &cur, uint32_t x, uint32_t rem, uint32_t lane) {
   if (rem) {
     const int src = (int)((rem + lane) & 63u);
     const uint32_t a = (uint32_t)__shfl((int)prev, src);
     const uint32_t b = (uint32_t)__shfl((int)cur, src);
     const uint32_t c = (uint32_t)__shfl((int)x, src);
     const bool wrap = rem + lane >= 64u;
-    lo = wrap ? b : a;
-    hi = wrap ? c : b;
+    prev = wrap ? b : a;
+    cur = wrap ? c : b;
   }
-  st[lane] = lo;
-  st[64 + lane] = hi;
+}
+
+// Writes that window as the new linear ring.
+__device__ __forceinline__ void store_ring(uint32_t *st, uint32_t prev, uint32_t cur, uint32_t x,
+                                           uint32_t rem, uint32_t lane) {
+  turn_ring(prev, cur, x, rem, lane);
+  st[lane] = prev;
+  st[64 + lane] = cur;
 }
 
 __device__ __forceinline__ void store_weyl_pos(uint32_t *st, uint32_t weyl, uint64_t pos,
@@ -202,6 +206,24 @@ __device__ __forceinline__ void write_state(uint32_t *dst, uint32_t prev, uint32
   store_weyl_pos(dst, weyl, pos, lane);
 }
 
+// Where a request's end state goes, a window as in write_state: to memory (or
+// nowhere), or into registers for the stream's next request.
+struct ToMemory {
+  uint32_t *dst;
+  __device__ __forceinline__ void operator()(uint32_t prev, uint32_t cur, uint32_t x, uint32_t rem, uint32_t weyl,
+                                             uint64_t pos, uint32_t lane) const {
+    write_state(dst, prev, cur, x, rem, weyl, pos, lane);
+  }
+};
+struct ToRegisters {
+  StreamState *s;
+  __device__ __forceinline__ void operator()(uint32_t prev, uint32_t cur, uint32_t x, uint32_t rem, uint32_t weyl,
+                                             uint64_t pos, uint32_t lane) const {
+    turn_ring(prev, cur, x, rem, lane);
+    *s = StreamState{prev, cur, weyl, pos};
+  }
+};
+
 // ---------------------------------------------------------------------------
 // One stream's word sequence inside a wavefront: open (from a state), next
 // (one 64-word chunk of outputs, lane j holding word j), close (the ragged last
@@ -239,10 +261,9 @@ __device__ __forceinline__ uint32_t next_chunk(WordStream &s) {
 }
 
 // Emits the last rem (< 64) words of an n-word request through `tail`
-// (lane-indexed: lane j writes tail[j], j < rem) and writes the end state to
-// dst (nullptr: nowhere).
-template <uint32_t KIND, bool NT = true>
-__device__ __forceinline__ void close_stream(uint32_t *dst, WordStream &s, uint64_t n, uint32_t rem,
+// (lane-indexed: lane j writes tail[j], j < rem) and hands the end state to `end`.
+template <uint32_t KIND, bool NT = true, class End>
+__device__ __forceinline__ void close_stream(End end, WordStream &s, uint64_t n, uint32_t rem,
                                              uint32_t *tail) {
   const uint32_t p0 = s.g.prev, c0 = s.g.cur;
   uint32_t x = 0u;
@@ -251,7 +272,7 @@ __device__ __forceinline__ void close_stream(uint32_t *dst, WordStream &s, uint6
     const uint32_t w = s.wbase + s.wlane;
     if (s.lane < rem) emit_word<KIND, false, NT>(tail, x + temper_weyl(w));
   }
-  write_state(dst, p0, c0, x, rem, s.w_start + (uint32_t)n * kOmega, s.pos + n, s.lane);
+  end(p0, c0, x, rem, s.w_start + (uint32_t)n * kOmega, s.pos + n, s.lane);
 }
 
 // ---------------------------------------------------------------------------
@@ -260,9 +281,9 @@ __device__ __forceinline__ void close_stream(uint32_t *dst, WordStream &s, uint6
 // the wavefront's LDS slot and leave as one 16-byte store per lane (1 KB per
 // store instruction instead of 256 B); the rest uses one 4-byte store per lane.
 // ---------------------------------------------------------------------------
-template <uint32_t KIND, int UNROLL, bool WIDE, bool PACED = false, bool NT = true>
+template <uint32_t KIND, int UNROLL, bool WIDE, bool PACED = false, bool NT = true, class End>
 __device__ __forceinline__ void serve_words_from(const StreamState &s0, uint64_t n, uint32_t *__restrict__ out,
-                                                 uint32_t *dst) {
+                                                 End end) {
   WordStream s = open_from(s0);
   const uint32_t lane = s.lane;
   const uint64_t nfull = n >> 6;
@@ -306,12 +327,12 @@ __device__ __forceinline__ void serve_words_from(const StreamState &s0, uint64_t
     emit_word<KIND, PACED, NT>(o, next_chunk(s));
     o += 64;
   }
-  close_stream<KIND, NT>(dst, s, n, rem, o);
+  close_stream<KIND, NT>(end, s, n, rem, o);
 }
 
 template <uint32_t KIND, int UNROLL, bool WIDE, bool PACED = false>
 __device__ __forceinline__ void serve_words(uint32_t *st, uint64_t n, uint32_t *__restrict__ out) {
-  serve_words_from<KIND, UNROLL, WIDE, PACED>(load_state(st), n, out, st);
+  serve_words_from<KIND, UNROLL, WIDE, PACED>(load_state(st), n, out, ToMemory{st});
 }
 
 // ---------------------------------------------------------------------------
@@ -343,7 +364,7 @@ __device__ __forceinline__ void serve_chunks(const StreamState &s0, uint64_t n, 
     emit_word<KIND, false, NT>(o, next_chunk(s));
     o += stride;
   }
-  close_stream<KIND, NT>(dst, s, n, rem, tail);
+  close_stream<KIND, NT>(ToMemory{dst}, s, n, rem, tail);
 }
 
 template <uint32_t KIND, int UNROLL>
@@ -454,9 +475,9 @@ __device__ __forceinline__ void consume_quad(u32x4 w, float *out, Moments &m) {
 // n normals of one stream; MOMENTS: reduce to (sum z, sum z^2) in sums[0..1]
 // instead of storing them.  Consumes 2 ceil(n / 2) words.  DPP picks the
 // pair gather (above).
-template <bool MOMENTS, int UNROLL, bool DPP, bool NT = true>
+template <bool MOMENTS, int UNROLL, bool DPP, bool NT = true, class End>
 __device__ __forceinline__ void serve_normals_from(const StreamState &s0, uint64_t n, float *__restrict__ out,
-                                                   float *__restrict__ sums, uint32_t *dst) {
+                                                   float *__restrict__ sums, End end) {
   const uint32_t lane = lane_id();
   const bool lane0 = lane == 0;
   Ring g = ring_from(s0.prev, s0.cur);
@@ -545,7 +566,7 @@ __device__ __forceinline__ void serve_normals_from(const StreamState &s0, uint64
     if (poff < rw) consume_pair<MOMENTS, true, NT>(e, o, (nblk << 7) + poff, n, out, m);
     if (MOMENTS) group_close(m);
   }
-  write_state(dst, p0, c0, xl, rem, w_start + (uint32_t)words * kOmega, pos + words, lane);
+  end(p0, c0, xl, rem, w_start + (uint32_t)words * kOmega, pos + words, lane);
   if constexpr (MOMENTS) {
     // The lanes' compensated sums are folded and reduced across the
     // wavefront in FP64, then rounded once to FP32: the reduction then adds
@@ -566,7 +587,7 @@ __device__ __forceinline__ void serve_normals_from(const StreamState &s0, uint64
 template <bool MOMENTS, int UNROLL, bool DPP>
 __device__ __forceinline__ void serve_normals(uint32_t *st, uint64_t n, float *__restrict__ out,
                                               float *__restrict__ sums) {
-  serve_normals_from<MOMENTS, UNROLL, DPP>(load_state(st), n, out, sums, st);
+  serve_normals_from<MOMENTS, UNROLL, DPP>(load_state(st), n, out, sums, ToMemory{st});
 }
 
 // ---------------------------------------------------------------------------
@@ -624,9 +645,9 @@ __global__ __launch_bounds__(1024) void k_rows_cached(uint32_t *__restrict__ sta
   if (wid >= count) return;
   uint32_t *st = state + (first + wid) * kStateWords;
   if constexpr (KIND == kNormal) {
-    serve_normals_from<false, 8, DPP, false>(load_state(st), n, reinterpret_cast<float *>(out) + wid * n, nullptr, st);
+    serve_normals_from<false, 8, DPP, false>(load_state(st), n, reinterpret_cast<float *>(out) + wid * n, nullptr, ToMemory{st});
   } else {
-    serve_words_from<KIND, 8, false, false, false>(load_state(st), n, out + wid * n, st);
+    serve_words_from<KIND, 8, false, false, false>(load_state(st), n, out + wid * n, ToMemory{st});
   }
 }
 
@@ -896,13 +917,13 @@ __global__ __launch_bounds__(256) void k_split(uint32_t *__restrict__ state, uin
   const StreamState s0 = load_split(o, at.chunk);
   uint32_t *dst = last ? state + (first + i) * kStateWords : nullptr;
   if constexpr (KIND == kNormal) {
-    serve_normals_from<false, 8, true, false>(s0, nk, reinterpret_cast<float *>(o), nullptr, dst);
+    serve_normals_from<false, 8, true, false>(s0, nk, reinterpret_cast<float *>(o), nullptr, ToMemory{dst});
   } else if constexpr (FILL) {
     const uint32_t lane = lane_id();
     uint32_t *tail = out + (n >> 6) * at.chunk + i * (n & 63u) + lane;
     serve_chunks<KIND, 8, false>(s0, nk, o + lane, at.chunk, tail, dst);
   } else {
-    serve_words_from<KIND, 8, false, false, false>(s0, nk, o, dst);
+    serve_words_from<KIND, 8, false, false, false>(s0, nk, o, ToMemory{dst});
   }
 }
 
@@ -989,15 +1010,10 @@ __global__ __launch_bounds__(1024) void k_batch(uint32_t *__restrict__ state, ui
                                                 SegmentArgs seg) {
   const uint32_t lane = lane_id();
   const uint32_t num_groups = work[2], num_reqs = work[3];
-  // Items come largest first.  A wavefront takes `take` consecutive items per
-  // trip to the queue: one while they are large, then as many (a power of two
-  // up to kBatchMaxTake) as fit kBatchTakeWords words at the size of the items
-  // it served last, so that small items do not make the one counter's atomics
-  // the bound (same-address atomics complete one at a time, and 2048
-  // wavefronts on items of a few thousand words ask for more than that).
-  // A wavefront's first item is its own index in the grid (the first pops
-  // would hand out exactly those items, one atomic at a time); later trips
-  // take items from the counter, offset by the wavefronts in the grid.
+  // Items come largest first.  A wavefront takes batch_take consecutive items
+  // per trip to the queue.  Its first item is its own index in the grid (the
+  // first pops would hand out exactly those items, one atomic at a time); later
+  // trips take items from the counter, offset by the wavefronts in the grid.
   const uint32_t wpb = blockDim.x >> 6;
   const uint32_t waves = gridDim.x * wpb;
   uint32_t g0 = blockIdx.x * wpb + (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -1012,35 +1028,51 @@ __global__ __launch_bounds__(1024) void k_batch(uint32_t *__restrict__ state, ui
         if (lane == 0) atomicOr(&work[1], 1u);
         continue;
       }
+      // A group's requests continue one stream, whose state stays in registers
+      // between them, and the next request is loaded while one is served: both
+      // chains of loads bound short requests (plan and batch of 4000 requests
+      // of 2^6 to 2^10 words on 400 streams: 69 us with the state in memory, 64
+      // so).
+      StreamState s{};
+      uint32_t *held = nullptr;  // whose state s is
+      auto put_back = [&] {
+        if (held) write_state(held, s.prev, s.cur, 0u, 0u, s.weyl, s.pos, lane);
+        held = nullptr;
+      };
+      xg_request q{};
+      if (r0 < r1) q = reqs[r0];
       for (uint32_t r = r0; r < r1; ++r) {
-        const xg_request q = reqs[r];
+        const xg_request next = reqs[r + 1 < r1 ? r + 1 : r];  // on its way while q is served
         const bool is_seg = (q.flags & kReqSegment) != 0;
         const bool ok = (is_seg ? seg_entry_ok(q, num_streams, seg)
                                 : q.stream < num_streams && q.dtype <= XG_NORMAL && q.flags == 0u) &&
                         q.out_offset <= out_elems && q.n <= out_elems - q.out_offset;
-        if (!ok) {
-          if (lane == 0) atomicOr(&work[1], 1u);
-          continue;
+        if (ok) {
+          uint32_t *st = state + q.stream * kStateWords;
+          if (is_seg || st != held) {
+            put_back();
+            s = load_state(is_seg ? seg.stage + (uint64_t)(q.flags >> 16) * kStateWords : st);
+          }
+          held = !is_seg || (q.flags & kReqLast) ? st : nullptr;
+          uint32_t *o = out + q.out_offset;
+          const StreamState s0 = s;
+          if (q.dtype == XG_U32) {
+            serve_words_from<kU32, UNROLL, WIDE, false, false>(s0, q.n, o, ToRegisters{&s});
+          } else if (q.dtype == XG_F32) {
+            serve_words_from<kF32, UNROLL, WIDE, false, false>(s0, q.n, o, ToRegisters{&s});
+          } else {
+            serve_normals_from<false, UNROLL, true, false>(s0, q.n, reinterpret_cast<float *>(o), nullptr,
+                                                           ToRegisters{&s});
+          }
+          served += q.n;
+        } else if (lane == 0) {
+          atomicOr(&work[1], 1u);
         }
-        uint32_t *st = state + q.stream * kStateWords;
-        const uint32_t *src = is_seg ? seg.stage + (uint64_t)(q.flags >> 16) * kStateWords : st;
-        uint32_t *dst = !is_seg || (q.flags & kReqLast) ? st : nullptr;
-        const StreamState s0 = load_state(src);
-        uint32_t *o = out + q.out_offset;
-        if (q.dtype == XG_U32) {
-          serve_words_from<kU32, UNROLL, WIDE, false, false>(s0, q.n, o, dst);
-        } else if (q.dtype == XG_F32) {
-          serve_words_from<kF32, UNROLL, WIDE, false, false>(s0, q.n, o, dst);
-        } else {
-          serve_normals_from<false, UNROLL, true, false>(s0, q.n, reinterpret_cast<float *>(o), nullptr, dst);
-        }
-        served += q.n;
+        q = next;
       }
+      put_back();
     }
-    // the largest power of two t <= kBatchMaxTake with t such items in kBatchTakeWords
-    const uint64_t budget = kBatchTakeWords * (g_end - g0);
-    take = 1;
-    while (take < kBatchMaxTake && served * (2u * take) <= budget) take <<= 1;
+    take = batch_take(served, g_end - g0, g0, num_groups, waves);
     uint32_t c = 0;
     if (lane == 0) c = atomicAdd(&work[0], take);
     g0 = waves + (uint32_t)__builtin_amdgcn_readfirstlane((int)c);

@@ -15,9 +15,9 @@
 // most of it not work), so each step does all it can before it needs the whole
 // table again: a sort is one launch over blocks of 1024 keys and one for each
 // eightfold merge, and the producer of a prefix sum's input leaves its block sums.
-// Plan and batch of short requests, 11 launches now and 28 before: 4100
-// requests 126 -> 65 us, 16384 199 -> 126, 65536 281 -> 173,
-// 900000 1130 -> 952.
+// Plan and batch of short requests, ten launches of the plan now and 32 before
+// (16384 requests): 4100 requests 126 -> 65 us, 16384 199 -> 126, 65536 281 ->
+// 173, 900000 1130 -> 952.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
