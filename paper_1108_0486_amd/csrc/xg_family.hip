@@ -638,6 +638,28 @@ __device__ __forceinline__ uint64_t lane_value(uint64_t v, int src) {
          (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)x);
 }
 
+// Whether pairs of groups would hold each other up, by up to 32 of them spread
+// over the table: the halves of a wavefront run one type at a time and part
+// where either's request ends.  Then a wavefront for each group is faster, where
+// there are enough (plan and batch of 384 requests of mixed types and 2^8 to
+// 2^14 words on 200 streams: 97 us in pairs and 60, 64 bits 167 and 95; 16384
+// of 2^6 to 2^10 on 1024: 140 and 107, 159 and 112).  It is slower where each
+// group is one request of one type (1000 of 2^6 to 2^12 uint32: 29 and 33).
+__device__ __forceinline__ bool pairs_uneven(const xg_request *__restrict__ reqs, uint32_t num_reqs,
+                                             const uint32_t *__restrict__ groups, uint32_t num_groups, const Lanes &L) {
+  uint32_t type = 0;
+  bool several = false;
+  if (num_groups) {
+    const uint32_t pairs = (uint32_t)((num_groups + 1ull) / 2);
+    const uint32_t first = 2u * (uint32_t)((uint64_t)L.j * pairs / 32u);  // of the pair this lane and the next look at
+    const uint32_t g = first + L.h < num_groups ? first + L.h : first;
+    const uint32_t r = groups[g], end = groups[g + 1];
+    several = r < end && end - r > 1u;
+    if (r < num_reqs) type = reqs[r].dtype;
+  }
+  return __any(several || (uint32_t)__shfl_xor((int)type, 1) != type) != 0;
+}
+
 template <class M, int UNROLL>
 __global__ __launch_bounds__(1024) void k_fam_batch(unsigned char *__restrict__ state, uint64_t num_streams,
                                                     const xg_request *__restrict__ reqs,
@@ -656,13 +678,14 @@ __global__ __launch_bounds__(1024) void k_fam_batch(unsigned char *__restrict__ 
   L.j = L.lane >> 1;
   L.k = 0;
   L.active = true;
-  // Queue items are pairs of groups (one per half), largest first; a
-  // wavefront takes batch_take consecutive pairs per atomic, as k_batch does.
-  // The first pair is the wavefront's own index in the grid; later trips
-  // take pairs from the counter, offset by the wavefronts in the grid.
-  const uint32_t num_pairs = (uint32_t)((num_groups + 1ull) / 2);
+  // Queue items are pairs of groups (one per half) or lone groups, largest
+  // first; a wavefront takes batch_take consecutive items per atomic, as k_batch
+  // does.  The first item is the wavefront's own index in the grid; later trips
+  // take items from the counter, offset by the wavefronts in the grid.
   const uint32_t wpb = blockDim.x >> 6;
   const uint32_t waves = gridDim.x * wpb;
+  const bool alone = num_groups <= waves && pairs_uneven(reqs, num_reqs, groups, num_groups, L);
+  const uint32_t num_pairs = alone ? num_groups : (uint32_t)((num_groups + 1ull) / 2);
   uint32_t p0 = blockIdx.x * wpb + (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   uint32_t take = 1;
   for (;;) {
@@ -670,7 +693,7 @@ __global__ __launch_bounds__(1024) void k_fam_batch(unsigned char *__restrict__ 
     const uint32_t p_end = num_pairs - p0 < take ? num_pairs : p0 + take;
     uint64_t served = 0;  // words of the trips run for these pairs
     for (uint32_t p = p0; p < p_end; ++p) {
-      const uint64_t g = 2ull * p + L.h;
+      const uint64_t g = alone ? p : 2ull * p + L.h;  // alone: both halves run it, as a lone stream's do
       uint32_t r = 0, r_end = 0;
       if (g < num_groups) {
         r = groups[g];
@@ -1235,15 +1258,20 @@ hipError_t launch_family_generate(uint32_t family, Kind kind, bool fill, const S
   return e;
 }
 
+// Groups per compute unit up to which there is a wavefront for each (see
+// pairs_uneven; 1500 requests of mixed types and 2^8 to 2^14 words: 81 us in pairs
+// and 64, 2000 81 and 72, and more than two wavefronts per SIMD gain nothing).
+constexpr uint64_t kAlone = 8;
 hipError_t launch_family_batch(uint32_t family, const Shape &shape, int num_cus, unsigned char *state,
                                uint64_t num_streams, const xg_request *reqs, const uint32_t *groups,
                                uint32_t max_groups, void *out, uint64_t out_elems, uint32_t *work,
                                hipStream_t stream) {
   if (family != XG_FAMILY_R64_W32 && family != XG_FAMILY_R64_W64) return hipErrorInvalidValue;
   hipError_t e = hipSuccess;
-  const uint64_t pairs = ((uint64_t)max_groups + 1) / 2;
-  uint64_t blocks = (uint64_t)(num_cus > 0 ? num_cus : 1) * shape.blocks_per_cu;
-  const uint64_t need = (pairs + shape.waves_per_block - 1) / shape.waves_per_block;
+  const uint64_t cus = num_cus > 0 ? num_cus : 1;
+  const uint64_t items = max_groups <= kAlone * cus ? max_groups : ((uint64_t)max_groups + 1) / 2;
+  uint64_t blocks = cus * shape.blocks_per_cu;
+  const uint64_t need = (items + shape.waves_per_block - 1) / shape.waves_per_block;
   if (need < blocks) blocks = need ? need : 1;
   const dim3 block(shape.waves_per_block * kWave);
   if (family == XG_FAMILY_R64_W32)

@@ -18,14 +18,16 @@ from paper_1108_0486_amd.streams import XorgensStreams  # noqa: E402
 EDGES = [0, 1, 2, 31, 32, 33, 63, 64, 65, 127, 128, 129, 255, 256, 257, 511, 513, 1025]
 
 
-@pytest.mark.parametrize("streams", [1, 7, 3001])
+@pytest.mark.parametrize("mixed", [False, True])
+@pytest.mark.parametrize("lone", [False, True])     # one request to a stream
+@pytest.mark.parametrize("streams", [1, 2, 7, 64, 1501, 3001])
 @pytest.mark.parametrize("family", [0, 1, 2])
-def test_groups_continue_their_stream(streams, family):
+def test_groups_continue_their_stream(streams, family, lone, mixed):
     rng = np.random.default_rng(streams + family)
-    k = max(60, 3 * streams)
-    stream = rng.integers(0, streams, k)
+    k = streams if lone else max(60, 3 * streams)
+    stream = rng.permutation(streams) if lone else rng.integers(0, streams, k)
     n = rng.choice(EDGES, k)
-    dtype = rng.integers(0, 3, k)
+    dtype = rng.integers(0, 3, k) if mixed else np.full(k, streams % 3)
     off = np.concatenate([[0], np.cumsum(n)])
     gs = XorgensStreams(streams, seed=21, family=family)
     b = Batch(gs, [(int(stream[i]), int(n[i]), int(off[i]), int(dtype[i])) for i in range(k)], int(off[-1]))
