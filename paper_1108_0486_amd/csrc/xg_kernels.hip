@@ -995,9 +995,10 @@ __global__ __launch_bounds__(kJumpWaves * 64, 4) void k_seg_starts(const uint32_
 }
 
 // Persistent batched kernel (launched with no more blocks than the device
-// holds at once): each wavefront serves the group of its own index, then takes
-// groups from an atomic queue (work[0], counting from the grid's wavefronts)
-// until it passes work[2] groups; every wavefront reaches the exit.  A plain
+// holds at once): each wavefront serves the group of its own index, then its
+// further ones, dealt or taken from an atomic queue (work[0], counting from the
+// grid's wavefronts), until it passes work[2] groups; every wavefront reaches
+// the exit.  A plain
 // entry reads and rewrites its stream's state; a segment entry
 // starts from its staged start state and only the request's last segment
 // writes the stream's state.  Outputs leave through plain (cached) stores
@@ -1010,14 +1011,17 @@ __global__ __launch_bounds__(1024) void k_batch(uint32_t *__restrict__ state, ui
                                                 SegmentArgs seg) {
   const uint32_t lane = lane_id();
   const uint32_t num_groups = work[2], num_reqs = work[3];
-  // Items come largest first.  A wavefront takes batch_take consecutive items
-  // per trip to the queue.  Its first item is its own index in the grid (the
-  // first pops would hand out exactly those items, one atomic at a time); later
-  // trips take items from the counter, offset by the wavefronts in the grid.
+  // Items come largest first.  A wavefront's first item is its own index in the
+  // grid (the first pops would hand out exactly those items, one atomic at a
+  // time); small ones after that are dealt (deal_items), and trips to the queue
+  // take batch_take others from the counter, offset by the wavefronts in the
+  // grid.
   const uint32_t wpb = blockDim.x >> 6;
   const uint32_t waves = gridDim.x * wpb;
-  uint32_t g0 = blockIdx.x * wpb + (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  uint32_t take = 1;
+  const uint32_t wave = blockIdx.x * wpb + (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const bool dealt = deal_items(reqs, num_reqs, groups, num_groups, waves, 1u << 16);
+  uint32_t g0 = wave;
+  uint32_t take = 1, round = 0;
   for (;;) {
     if (g0 >= num_groups) break;
     const uint32_t g_end = num_groups - g0 < take ? num_groups : g0 + take;
@@ -1071,6 +1075,10 @@ __global__ __launch_bounds__(1024) void k_batch(uint32_t *__restrict__ state, ui
         q = next;
       }
       put_back();
+    }
+    if (dealt) {
+      g0 = dealt_item(++round, wave, waves, num_groups);
+      continue;
     }
     take = batch_take(served, g_end - g0, g0, num_groups, waves);
     uint32_t c = 0;

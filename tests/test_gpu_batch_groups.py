@@ -20,7 +20,7 @@ EDGES = [0, 1, 2, 31, 32, 33, 63, 64, 65, 127, 128, 129, 255, 256, 257, 511, 513
 
 @pytest.mark.parametrize("mixed", [False, True])
 @pytest.mark.parametrize("lone", [False, True])     # one request to a stream
-@pytest.mark.parametrize("streams", [1, 2, 7, 64, 1501, 3001])
+@pytest.mark.parametrize("streams", [1, 2, 7, 64, 1501, 3001, 13001])
 @pytest.mark.parametrize("family", [0, 1, 2])
 def test_groups_continue_their_stream(streams, family, lone, mixed):
     rng = np.random.default_rng(streams + family)
