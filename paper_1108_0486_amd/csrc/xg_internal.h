@@ -33,22 +33,16 @@ constexpr Shape kDefaultPlain{0, 0, 1, 4};  // waves_per_block and unroll chosen
 // the wavefronts spread one per SIMD before any SIMD gets two.  (Blocks of two
 // do not: 700 streams x 100003 uint32 took 84 us in them, 52 in blocks of one.)
 uint32_t auto_waves_per_block(uint64_t count, int num_cus);
-// Default persistent-batch shapes, chosen by the number of queue items.  With
-// at least eight items per compute unit the batch is bound by HBM writes, and
-// eight wavefronts per compute unit write fastest (every unroll takes the same
-// time on unaligned requests; eight chunks per trip are faster on aligned
-// ones).  With fewer items each wavefront's own rate decides, and eight
-// wavefronts per compute unit at eight chunks per trip serve a group fastest.
-// Neither uses the wide stores: staging through LDS gained nothing.
+
 // Queue items (largest first) a batch wavefront takes on its next trip to the
 // queue, after `served` words in the `items` items from `at` of `all`: a power
 // of two, as many as fit kBatchTakeWords words at the size of the items it just
 // served and at most kBatchMaxTake (one counter serves every wavefront, and
 // same-address atomics complete one at a time), but no more than its share of
 // the items left, which would leave other wavefronts idle (plan and batch of
-// 10000 requests of 2^6 to 2^12 words, without that limit and with it: Section
-// 2's member 130 and 116 us, the 32-bit r = 64 member 159 and 117, the 64-bit
-// one 170 and 120).
+// 10000 requests of 2^6 to 2^12 words, all from the queue, without that limit
+// and with it: Section 2's member 130 and 116 us, the 32-bit r = 64 member 159
+// and 117, the 64-bit one 170 and 120).
 constexpr uint32_t kBatchMaxTake = 16;
 constexpr uint64_t kBatchTakeWords = 65536;
 __host__ __device__ inline uint32_t batch_take(uint64_t served, uint32_t items, uint32_t at, uint32_t all,
@@ -59,14 +53,14 @@ __host__ __device__ inline uint32_t batch_take(uint64_t served, uint32_t items, 
   return take;
 }
 
-// Whether every wavefront's items are fixed from the start (dealt_item) instead of
-// taken from the queue, whose counter serves one atomic after another, 10 to 20 ns
-// each for the whole device: with no more than the first items, and where the
-// first of the later ones, which is the largest of them, costs at most `limit`.  Wavefronts
-// then differ by no more than an item of that size; over larger ones the queue
-// keeps them better together.  Plan and batch, from the queue and dealt: 1000
-// requests of 2^6 to 2^12 words 31 and 22 us, 10000 116 and 76, 3000 of 2^8
-// to 2^14 87 and 60, 16384 155 and 110, 16384 of 2^8 to 2^16 (limit 2^16) 250
+// Whether every wavefront's items are fixed from the start (dealt_item) instead
+// of taken from the queue, whose counter serves one atomic after another, 10 to
+// 20 ns each for the whole device: with no more than the first items, and where
+// the first of the later ones, the largest of them, costs at most `limit`.
+// Wavefronts then differ by no more than an item of that size; over larger ones
+// the queue keeps them better together.  Plan and batch, from the queue and
+// dealt: 1000 requests of 2^6 to 2^12 words 31 and 22 us, 10000 116 and 76,
+// 3000 of 2^8 to 2^14 87 and 60, 16384 155 and 110, 16384 of 2^8 to 2^16 250
 // and 241; r = 64 members 16384 of 2^6 to 2^10 134 and 88, 135 and 90.
 __device__ __forceinline__ bool deal_items(const xg_request *__restrict__ reqs, uint32_t num_reqs,
                                            const uint32_t *__restrict__ groups, uint32_t num_groups,
@@ -84,6 +78,13 @@ __device__ __forceinline__ uint32_t dealt_item(uint32_t round, uint32_t wave, ui
   return at < items ? (uint32_t)at : items;
 }
 
+// Default persistent-batch shapes, chosen by the number of queue items.  With
+// at least eight items per compute unit the batch is bound by HBM writes, and
+// eight wavefronts per compute unit write fastest (every unroll takes the same
+// time on unaligned requests; eight chunks per trip are faster on aligned
+// ones).  With fewer items each wavefront's own rate decides, and eight
+// wavefronts per compute unit at eight chunks per trip serve a group fastest.
+// Neither uses the wide stores: staging through LDS gained nothing.
 constexpr Shape kBatchThroughput{4, 8, 2, 1};
 constexpr Shape kBatchLatency{4, 8, 8, 1};
 inline Shape default_batch_shape(uint64_t items, int num_cus) {
