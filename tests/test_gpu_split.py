@@ -92,3 +92,9 @@ def test_split_in_a_graph():
         torch.cuda.synchronize()
         want = b.normal(70_001)
         assert torch.equal(out, want) and torch.equal(a.state, b.state), replay
+
+
+@pytest.mark.parametrize("family,count", [(0, 512), (0, 400), (1, 1024), (1, 901), (2, 1023)])
+def test_half_of_the_simds(family, count):
+    """As many streams as are ever cut, in two parts; the second one longer."""
+    test_split_equals_unsplit(family, count, (1 << 18) + 133)
