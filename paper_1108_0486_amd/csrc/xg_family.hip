@@ -1113,16 +1113,18 @@ hipError_t launch_fam_k(uint32_t unroll, dim3 grid, dim3 block, unsigned char *s
 }
 
 // The bulk-fill layout takes non-temporal stores, as do stream-major rows on
-// whole 128-byte lines with less than a wavefront per SIMD (5 % faster than
-// cached ones: 300 x 10016 uint64 16.5 us against 17.3); the others cached
-// ones (64-bit member, 4096 x 2^16: 390 us against 414; rows that start inside
-// a line, 4096 x 65537: 403 and 727 us, 32-bit member 211 and 535).
+// whole 128-byte lines, or of less than 32 MB in all, with less than a wavefront
+// per SIMD (5 % faster than cached ones: 300 x 10016 uint64 16.5 us against
+// 17.3, 300 x 9000 15.9 against 16.7); the others cached ones (64-bit member,
+// 4096 x 2^16: 390 us against 414; rows that start inside a line, 4096 x 65537:
+// 403 and 727 us, 32-bit member 211 and 535).
 template <class M, uint32_t KIND>
 hipError_t launch_fam_layout(bool fill, uint32_t unroll, int num_cus, dim3 grid, dim3 block, unsigned char *state,
                              uint64_t first, uint64_t count, uint64_t n, void *out, hipStream_t stream) {
   if (fill) return launch_fam_k<M, KIND, true, true>(unroll, grid, block, state, first, count, n, out, stream);
-  const bool lines = (n * sizeof(typename M::word) | reinterpret_cast<uintptr_t>(out)) % 128 == 0;
-  if (lines && count < 8 * (uint64_t)(num_cus > 0 ? num_cus : 1))
+  const uint64_t row = n * sizeof(typename M::word);
+  const bool lines = (row | reinterpret_cast<uintptr_t>(out)) % 128 == 0;
+  if ((lines || count * row < (32ull << 20)) && count < 8 * (uint64_t)(num_cus > 0 ? num_cus : 1))
     return launch_fam_k<M, KIND, false, true>(unroll, grid, block, state, first, count, n, out, stream);
   return launch_fam_k<M, KIND, false, false>(unroll, grid, block, state, first, count, n, out, stream);
 }

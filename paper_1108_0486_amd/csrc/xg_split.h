@@ -53,10 +53,11 @@ struct SplitCost {
 };
 constexpr uint64_t kSplitLaunchNs = 3000;  // a plain launch without its values
 constexpr uint64_t kSplitBaseNs = 5000;    // the two launches without jumps and values
-// What either form writes at best.  (At 5000, and a fifth to be saved, launches
-// on half of the SIMDs stayed whole: 512 x 2^20 uint32 486 us and 390 cut in
-// two, FP32 568 and 397; 1024 x 2^20 of the 32-bit r = 64 member 1032 and 817,
-// bulk-fill 1085 and 671.)
+// What either form writes at best.  (At 5000, long launches on half of the SIMDs
+// stayed whole: 512 x 2^20 uint32 486 us and 390 cut in two, FP32 568 and 397;
+// 1024 x 2^20 of the 32-bit r = 64 member 1032 and 817, bulk-fill 1085 and 671.
+// A saving of a tenth by these costs is not always one: 300 x 40001 normals 40
+// us whole and 42.)
 constexpr uint64_t kSplitBytesPerNs = 5800;
 // Measured (a wavefront alone on its SIMD; 1 to 1024 workgroups).  By member
 // (XG_FAMILY_*), then words and normals.
@@ -69,14 +70,14 @@ constexpr SplitCost kSplitCost[3][2] = {
 // The parts of a launch of `waves` wavefronts (one per stream, or one per two
 // streams for the r = 64 members) with n values per stream on `cus` compute
 // units: those of the least time by the costs above, with at most one
-// wavefront per SIMD; none where that saves less than a tenth, or where more
+// wavefront per SIMD; none where that saves less than a fifth, or where more
 // than half of the SIMDs have a wavefront as it is.
 inline Split plan_split(uint64_t waves, uint64_t n, uint64_t cus, const SplitCost &c) {
   Split s;
   const uint64_t slots = 4 * cus;
   if (waves == 0 || n < 2 * kSplitMinPart || 2 * waves > slots || n >> 40) return s;
   const uint64_t write_ns = n * waves * c.value_bytes / kSplitBytesPerNs, whole_ns = n * c.value_ps / 1000;
-  uint64_t best = (kSplitLaunchNs + (whole_ns > write_ns ? whole_ns : write_ns)) * 9 / 10;
+  uint64_t best = (kSplitLaunchNs + (whole_ns > write_ns ? whole_ns : write_ns)) * 4 / 5;
   for (uint32_t e = kSplitMinExp; e <= kSplitMaxExp; ++e) {
     const uint64_t parts = ((n - kSplitMinPart) >> e) + 1;
     if (parts < 2) break;
