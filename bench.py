@@ -44,7 +44,7 @@ SIMD_CYCLES_PER_S = 256 * 4 * 2.4e9
 # includes.  The committed counter records are used only while it matches.
 KERNEL_SOURCES = [os.path.join(ROOT, "paper_1108_0486_amd", "csrc", f)
                   for f in ("xg_kernels.hip", "xg_device.h", "xg_normal.h", "xg_internal.h", "xg_host.h",
-                            "xg_jump_mm.h", "xg_split.h")]
+                            "xg_jump_mm.h")]
 
 
 def kernel_source_hash() -> str:
