@@ -161,7 +161,8 @@ xg_status run_plain(xg_ctx *ctx, xg::Kind kind, bool fill_layout, uint64_t first
     e = xg::launch_split(kind, fill_layout, sp, ctx->d_state, first, count, n, ctx->split_table, out, ctx->num_cus, s);
   else if (fill_layout)
     e = xg::launch_fill(kind, shape, ctx->d_state, first, count, n, static_cast<uint32_t *>(out), s);
-  else if (!ctx->plain.unroll && xg::cached_stores(kind, count, n, out, ctx->num_cus))
+  else if (!ctx->plain.unroll &&
+           xg::cached_stores(ctx->family, kind, count, n, reinterpret_cast<uintptr_t>(out), ctx->num_cus))
     e = xg::launch_rows_cached(kind, shape.waves_per_block, ctx->d_state, first, count, n, out, ctx->num_cus, s);
   else
     e = xg::launch_generate(kind, shape, ctx->d_state, first, count, n, out, ctx->num_cus, s);

@@ -1125,21 +1125,13 @@ hipError_t launch_fam_k(uint32_t unroll, dim3 grid, dim3 block, unsigned char *s
   }
 }
 
-// The bulk-fill layout takes non-temporal stores, as do stream-major rows on
-// whole 128-byte lines, or of less than 32 MB in all, with less than a wavefront
-// per SIMD (5 % faster than cached ones: 300 x 10016 uint64 16.5 us against
-// 17.3, 300 x 9000 15.9 against 16.7); the others cached ones (64-bit member,
-// 4096 x 2^16: 390 us against 414; rows that start inside a line, 4096 x 65537:
-// 403 and 727 us, 32-bit member 211 and 535).
+// The bulk-fill layout takes non-temporal stores, stream-major rows those of cached_stores.
 template <class M, uint32_t KIND>
-hipError_t launch_fam_layout(bool fill, uint32_t unroll, int num_cus, dim3 grid, dim3 block, unsigned char *state,
+hipError_t launch_fam_layout(bool fill, bool cached, uint32_t unroll, dim3 grid, dim3 block, unsigned char *state,
                              uint64_t first, uint64_t count, uint64_t n, void *out, hipStream_t stream) {
   if (fill) return launch_fam_k<M, KIND, true, true>(unroll, grid, block, state, first, count, n, out, stream);
-  const uint64_t row = n * sizeof(typename M::word);
-  const bool lines = (row | reinterpret_cast<uintptr_t>(out)) % 128 == 0;
-  if ((lines || count * row < (32ull << 20)) && count < 8 * (uint64_t)(num_cus > 0 ? num_cus : 1))
-    return launch_fam_k<M, KIND, false, true>(unroll, grid, block, state, first, count, n, out, stream);
-  return launch_fam_k<M, KIND, false, false>(unroll, grid, block, state, first, count, n, out, stream);
+  if (cached) return launch_fam_k<M, KIND, false, false>(unroll, grid, block, state, first, count, n, out, stream);
+  return launch_fam_k<M, KIND, false, true>(unroll, grid, block, state, first, count, n, out, stream);
 }
 
 // The 32-bit member's normals with more than a wavefront per SIMD gather their
@@ -1253,11 +1245,9 @@ hipError_t launch_family_generate(uint32_t family, Kind kind, bool fill, const S
   const uint64_t pairs = (count + 1) / 2;
   const uint64_t wpb = shape.waves_per_block;
   const dim3 grid((uint32_t)((pairs + wpb - 1) / wpb)), block((uint32_t)(wpb * kWave));
+  const bool cached = cached_stores(family, kind, count, n, reinterpret_cast<uintptr_t>(out), num_cus);
   if (kind == kNormal || kind == kMoments) {
-    // Non-temporal stores while every row starts on a cache line; rows that
-    // start inside one leave partial lines, which only cached stores merge.
-    const uint64_t row_bytes = n * (family == XG_FAMILY_R64_W64 ? 8 : 4);
-    const bool nt = kind == kNormal && (row_bytes | reinterpret_cast<uintptr_t>(out)) % 128 == 0;
+    const bool nt = kind == kNormal && !cached;
     if (family == XG_FAMILY_R64_W32)
       return launch_fam_normals<MemberN2048>(kind, nt, pairs, num_cus, grid, block, state, first, count, n, out, stream);
     if (family == XG_FAMILY_R64_W64)
@@ -1265,17 +1255,13 @@ hipError_t launch_family_generate(uint32_t family, Kind kind, bool fill, const S
     return hipErrorInvalidValue;
   }
   if (family == XG_FAMILY_R64_W32 && kind == kU32)
-    e = launch_fam_layout<MemberN2048, kU32>(fill, shape.unroll, num_cus, grid, block, state, first, count, n, out,
-                                                stream);
+    e = launch_fam_layout<MemberN2048, kU32>(fill, cached, shape.unroll, grid, block, state, first, count, n, out, stream);
   else if (family == XG_FAMILY_R64_W32 && kind == kF32)
-    e = launch_fam_layout<MemberN2048, kF32>(fill, shape.unroll, num_cus, grid, block, state, first, count, n, out,
-                                                stream);
+    e = launch_fam_layout<MemberN2048, kF32>(fill, cached, shape.unroll, grid, block, state, first, count, n, out, stream);
   else if (family == XG_FAMILY_R64_W64 && kind == kU64)
-    e = launch_fam_layout<MemberW64, kU64>(fill, shape.unroll, num_cus, grid, block, state, first, count, n, out,
-                                                stream);
+    e = launch_fam_layout<MemberW64, kU64>(fill, cached, shape.unroll, grid, block, state, first, count, n, out, stream);
   else if (family == XG_FAMILY_R64_W64 && kind == kF64)
-    e = launch_fam_layout<MemberW64, kF64>(fill, shape.unroll, num_cus, grid, block, state, first, count, n, out,
-                                                stream);
+    e = launch_fam_layout<MemberW64, kF64>(fill, cached, shape.unroll, grid, block, state, first, count, n, out, stream);
   else
     return hipErrorInvalidValue;
   return e;

@@ -8,16 +8,13 @@
 #include "xg.h"
 #include "xg_host.h"
 #include "xg_plan_dev.h"
+#include "xg_shape.h"
 #include "xg_split.h"
 
 namespace xg {
 
 constexpr uint32_t kStateWords = XG_STATE_WORDS;
 constexpr uint32_t kWave = 64;
-
-// Request kinds of the plain launch (the three output types of xg.h plus the
-// fused normal-moments reduction).
-enum Kind : uint32_t { kU32 = XG_U32, kF32 = XG_F32, kNormal = XG_NORMAL, kMoments = 3, kU64 = XG_U64, kF64 = XG_F64 };
 
 struct Shape {
   uint32_t waves_per_block;  // 1, 2, 4, 8, 16; 0 (plain launches only): chosen per launch
@@ -100,21 +97,7 @@ hipError_t launch_init(uint32_t *state, uint64_t num_streams, uint64_t seed, hip
 hipError_t launch_generate(Kind kind, const Shape &shape, uint32_t *state, uint64_t first,
                            uint64_t count, uint64_t n, void *out, int num_cus, hipStream_t stream);
 
-// Whether a stream-major launch of Section 2's member takes cached stores
-// (launch_rows_cached) instead of non-temporal ones:
-//  - where rows start inside a 128-byte line: non-temporal stores write both
-//    ends of each wavefront's 256 bytes as partial lines (4096 x 65537 uint32:
-//    366 us against 199; 1024 x 100003: 137 and 80, normals 137 and 98).  Outputs
-//    under 32 MB keep them, since what a launch leaves in the caches is written
-//    back at its end (1071 x 4848 FP32: 7.8 us against 8.4);
-//  - uint32 and FP32 with two wavefronts or more per SIMD (4096 x 2^18 uint32:
-//    805 us and 760); normals stay 2 % faster with non-temporal ones, as does
-//    one wavefront per SIMD (1024 x 2^20 uint32: 705 us and 730).
-inline bool cached_stores(Kind kind, uint64_t count, uint64_t n, const void *out, int num_cus) {
-  if (kind != kU32 && kind != kF32 && kind != kNormal) return false;
-  if ((n * 4 | reinterpret_cast<uintptr_t>(out)) % 128 != 0 && count * n >= (32ull << 20) / 4) return true;
-  return kind != kNormal && count >= 8u * (uint64_t)(num_cus > 0 ? num_cus : 1);
-}
+// Stream-major launch of Section 2's member with cached stores (cached_stores).
 hipError_t launch_rows_cached(Kind kind, uint32_t waves_per_block, uint32_t *state, uint64_t first, uint64_t count,
                               uint64_t n, void *out, int num_cus, hipStream_t stream);
 

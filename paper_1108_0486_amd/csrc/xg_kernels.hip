@@ -637,7 +637,7 @@ __global__ __launch_bounds__(1024) void k_generate(uint32_t *__restrict__ state,
 }
 
 // The same with cached stores, for rows that start inside a cache line and for
-// words with two or more wavefronts per SIMD (cached_stores in xg_internal.h).
+// words with two or more wavefronts per SIMD (cached_stores in xg_shape.h).
 template <uint32_t KIND, bool DPP = false>
 __global__ __launch_bounds__(1024) void k_rows_cached(uint32_t *__restrict__ state, uint64_t first, uint64_t count,
                                                       uint64_t n, uint32_t *__restrict__ out) {
