@@ -53,19 +53,34 @@ __host__ __device__ inline uint32_t batch_take(uint64_t served, uint32_t items, 
 // Whether every wavefront's items are fixed from the start (dealt_item) instead
 // of taken from the queue, whose counter serves one atomic after another, 10 to
 // 20 ns each for the whole device: with no more than the first items, and where
-// the first of the later ones, the largest of them, costs at most `limit`.
+// the first of the later ones, the largest of them, costs at most `limit` (the
+// words of all its requests, normals weighted four times as in the table's order).
 // Wavefronts then differ by no more than an item of that size; over larger ones
 // the queue keeps them better together.  Plan and batch, from the queue and
 // dealt: 1000 requests of 2^6 to 2^12 words 31 and 22 us, 10000 116 and 76,
 // 3000 of 2^8 to 2^14 87 and 60, 16384 155 and 110, 16384 of 2^8 to 2^16 250
 // and 241; r = 64 members 16384 of 2^6 to 2^10 134 and 88, 135 and 90.
+// Every lane of the wavefront calls it.
+constexpr uint32_t kDealRequests = 1024;  // in an item that is looked at, 64 at a time
 __device__ __forceinline__ bool deal_items(const xg_request *__restrict__ reqs, uint32_t num_reqs,
                                            const uint32_t *__restrict__ groups, uint32_t num_groups,
-                                           uint32_t first, uint64_t limit) {
+                                           uint32_t first, uint32_t limit) {
   if (num_groups <= first) return true;
   const uint32_t r = groups[first], end = groups[first + 1];
-  if (r >= num_reqs || end <= r) return false;
-  return reqs[r].n <= (reqs[r].dtype == XG_NORMAL ? limit / 4 : limit) / (end - r);
+  if (r >= end || end > num_reqs || end - r > kDealRequests) return false;
+  // A request's cost, or limit + 1 where it is more.
+  auto cost = [&](uint32_t i) -> uint32_t {
+    const uint64_t n = reqs[i].n;
+    if (n > limit) return limit + 1u;
+    const uint32_t c = reqs[i].dtype == XG_NORMAL ? 4u * ((uint32_t)n + ((uint32_t)n & 1u)) : (uint32_t)n;
+    return c <= limit ? c : limit + 1u;
+  };
+  if (end - r == 1u) return cost(r) <= limit;
+  uint32_t sum = 0;
+  for (uint32_t i = r + (threadIdx.x & 63u); i < end; i += 64u) sum += cost(i);
+#pragma unroll
+  for (uint32_t d = 32; d; d >>= 1) sum += (uint32_t)__shfl_xor((int)sum, (int)d);
+  return (uint32_t)__builtin_amdgcn_readfirstlane((int)sum) <= limit;  // uniform, so that the items stay so
 }
 
 // The wavefront's item of a round (items: none left): items fall in cost, so
