@@ -226,7 +226,6 @@ __device__ __forceinline__ FamState<M> fam_load(const unsigned char *__restrict_
 
 // Waits here for a state's loads.  Where a use of them comes after a loop of
 // stores, the wait otherwise does too, and one counter serves loads and stores
-<<<<<<< Updated upstream
 // in order, so that it waits for every store: 6 x 11422 uint32 of the 32-bit
 // member 13.2 us, 12.8 with the wait in front.  THROUGH: the values pass through the
 // statement, which gives the compiler's schedule of the FP64 loop 4 % (512 x
@@ -235,12 +234,6 @@ template <class M, bool THROUGH>
 __device__ __forceinline__ void arrive(FamState<M> &s) {
   if constexpr (THROUGH) asm volatile("" : "+v"(s.prev), "+v"(s.cur), "+v"(s.weyl), "+v"(s.pos));
   else asm volatile("" : : "v"(s.prev), "v"(s.cur), "v"(s.weyl), "v"(s.pos));
-=======
-// in order, so that it waits for every store.
-template <class M>
-__device__ __forceinline__ void arrive(FamState<M> &s) {
-  asm volatile("" : "+v"(s.prev), "+v"(s.cur), "+v"(s.weyl), "+v"(s.pos));
->>>>>>> Stashed changes
 }
 
 template <bool NT, class T>
@@ -261,11 +254,7 @@ __device__ __forceinline__ void fam_run(FamState<M> s0, unsigned char *__restric
                                         typename M::word *__restrict__ tail) {
   using word = typename M::word;
   L.active = on && keep;
-<<<<<<< Updated upstream
   arrive<M, KIND == kF64>(s0);
-=======
-  arrive(s0);
->>>>>>> Stashed changes
   const word w_start = s0.weyl;
   Ring2<M> g;
   g.open(s0.prev, s0.cur);
