@@ -229,7 +229,8 @@ __device__ __forceinline__ FamState<M> fam_load(const unsigned char *__restrict_
 // in order, so that it waits for every store: 6 x 11422 uint32 of the 32-bit
 // member 13.2 us, 12.8 with the wait in front.  THROUGH: the values pass through the
 // statement, which gives the compiler's schedule of the FP64 loop 4 % (512 x
-// 40001: 71.1 us and 68.3; the uint64 loop loses 1 %).
+// 40001: 71.1 us and 68.3; the uint64 loop loses 1 %).  Plain launches
+// only: batches gained nothing.
 template <class M, bool THROUGH>
 __device__ __forceinline__ void arrive(FamState<M> &s) {
   if constexpr (THROUGH) asm volatile("" : "+v"(s.prev), "+v"(s.cur), "+v"(s.weyl), "+v"(s.pos));
@@ -249,12 +250,11 @@ __device__ __forceinline__ void store_value(T v, T *p) {
 // lane's stores (that half's stream is absent), keep = false leaves st as it
 // is; n is wave-uniform.  NT: non-temporal stores.
 template <class M, uint32_t KIND, int UNROLL, bool NT = true>
-__device__ __forceinline__ void fam_run(FamState<M> s0, unsigned char *__restrict__ st, bool on, bool keep,
+__device__ __forceinline__ void fam_run(const FamState<M> &s0, unsigned char *__restrict__ st, bool on, bool keep,
                                         Lanes L, uint64_t n, typename M::word *__restrict__ o, uint64_t stride,
                                         typename M::word *__restrict__ tail) {
   using word = typename M::word;
   L.active = on && keep;
-  arrive<M, KIND == kF64>(s0);
   const word w_start = s0.weyl;
   Ring2<M> g;
   g.open(s0.prev, s0.cur);
@@ -303,7 +303,8 @@ __device__ __forceinline__ void fam_serve(unsigned char *__restrict__ state, con
                                           uint64_t count, uint64_t n, typename M::word *__restrict__ out) {
   using word = typename M::word;
   unsigned char *st = state + (first + L.k) * M::state_bytes;
-  const FamState<M> s0 = fam_load<M>(st, true, L);
+  FamState<M> s0 = fam_load<M>(st, true, L);
+  arrive<M, KIND == kF64>(s0);
   if constexpr (FILL) {
     word *tail = out + (n / kStep) * count * kStep + L.k * (n % kStep) + L.j;
     fam_run<M, KIND, UNROLL, NT>(s0, st, true, true, L, n, out + L.k * kStep + L.j, count * kStep, tail);
@@ -651,26 +652,50 @@ __device__ __forceinline__ uint64_t lane_value(uint64_t v, int src) {
          (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)x);
 }
 
-// Whether pairs of groups would hold each other up, by up to 32 of them spread
-// over the table: the halves of a wavefront run one type at a time and part
-// where either's request ends.  Then a wavefront for each group is faster, where
-// there are enough (plan and batch of 384 requests of mixed types and 2^8 to
-// 2^14 words on 200 streams: 97 us in pairs and 60, 64 bits 167 and 95; 16384
-// of 2^6 to 2^10 on 1024: 140 and 107, 159 and 112).  It is slower where each
-// group is one request of one type (1000 of 2^6 to 2^12 uint32: 29 and 33).
-__device__ __forceinline__ bool pairs_uneven(const xg_request *__restrict__ reqs, uint32_t num_reqs,
-                                             const uint32_t *__restrict__ groups, uint32_t num_groups, const Lanes &L) {
-  uint32_t type = 0;
-  bool several = false;
+// How evenly pairs of groups run, by up to 32 of them spread over the table and
+// each group's first request.  The halves of a wavefront part where either's
+// request ends, and run one type at a time.
+//  - apart: pairs of different lengths or types.  A wavefront for each group is
+//    then faster, where there are enough (plan and batch of 384 requests of mixed types and
+//    2^8 to 2^14 words on 200 streams: 97 us in pairs and 60, 64 bits 167 and 95;
+//    1000 single uint32 requests of 2^6 to 2^12 words 29.3 and 27.9), but slower where
+//    pairs step together (two uint32 requests of 2^16 on each of 2000 streams, lone groups
+//    being two wavefronts to a SIMD: 273 and 330; normals 335 and 500, FP64
+//    normals 652 and 1072).
+//  - uneven: pairs of different types, or of several requests of different
+//    lengths, whose times differ more than their costs.
+// Either wants a quarter of the pairs, or one of two types long enough to end last.
+struct PairLook {
+  bool apart, uneven;
+};
+__device__ __forceinline__ uint32_t other_half(uint32_t v) { return dev::lane_xor<1>(v); }
+__device__ __forceinline__ float other_half(float v) { return __uint_as_float(dev::lane_xor<1>(__float_as_uint(v))); }
+__device__ __forceinline__ PairLook look_at_pairs(const xg_request *__restrict__ reqs, uint32_t num_reqs,
+                                                  const uint32_t *__restrict__ groups, uint32_t num_groups,
+                                                  const Lanes &L) {
+  uint32_t type = 0, count = 0;
+  float n = 0.0f;  // of the first request
   if (num_groups) {
     const uint32_t pairs = (uint32_t)((num_groups + 1ull) / 2);
     const uint32_t first = 2u * (uint32_t)((uint64_t)L.j * pairs / 32u);  // of the pair this lane and the next look at
     const uint32_t g = first + L.h < num_groups ? first + L.h : first;
     const uint32_t r = groups[g], end = groups[g + 1];
-    several = r < end && end - r > 1u;
-    if (r < num_reqs) type = reqs[r].dtype;
+    if (r < end && r < num_reqs) {
+      type = reqs[r].dtype;
+      n = reqs[r].n >> 32 ? 4294967296.0f : (float)(uint32_t)reqs[r].n;
+      count = end - r;
+    }
   }
-  return __any(several || (uint32_t)__shfl_xor((int)type, 1) != type) != 0;
+  const float time = n * (float)count * (type == XG_NORMAL ? 2.0f : 1.0f);  // of the group, in words
+  // Lane 0 has the first group, and groups fall in cost.
+  const float largest = __uint_as_float((uint32_t)__builtin_amdgcn_readfirstlane((int)__float_as_uint(time)));
+  const float both = time + other_half(time);
+  const uint32_t counts = count + other_half(count);
+  const bool types = other_half(type) != type, lengths = other_half(n) != n;
+  const bool last = __any(types && both > 1.25f * largest) != 0;
+  constexpr int kQuarter = 16;  // lanes, two to a pair
+  return {last || __popcll(__ballot(types || lengths)) >= kQuarter,
+          last || __popcll(__ballot(types || (counts > 2u && lengths))) >= kQuarter};
 }
 
 template <class M, int UNROLL>
@@ -695,14 +720,18 @@ __global__ __launch_bounds__(1024) void k_fam_batch(unsigned char *__restrict__ 
   // first, handed out as k_batch's: the first by the wavefront's index in the
   // grid, later ones dealt or from the counter.  Pairs that hold each other up
   // differ more in time than in cost, so fewer of them are dealt (16384 requests of
-  // mixed types and 2^8 to 2^14 words: 157 us from the queue, 177 dealt).
+  // mixed types and 2^8 to 2^14 words: 157 us from the queue, 177 dealt; two of
+  // mixed types and 2^12 words on each of 6000 streams: 126 and 137), even ones up to 64 KB
+  // (two uint32 requests of 2^12 words on each: 117 and 98; 16384 of 2^8 to 2^15
+  // uint64, not dealt: 255 and 269).
+  constexpr uint32_t kDealEven = (1u << 16) / sizeof(word);
   const uint32_t wpb = blockDim.x >> 6;
   const uint32_t waves = gridDim.x * wpb;
-  const bool uneven = pairs_uneven(reqs, num_reqs, groups, num_groups, L);
-  const bool alone = num_groups <= waves && uneven;
+  const PairLook look = look_at_pairs(reqs, num_reqs, groups, num_groups, L);
+  const bool alone = num_groups <= waves && look.apart;
   const uint32_t num_pairs = alone ? num_groups : (uint32_t)((num_groups + 1ull) / 2);
   const uint32_t wave = blockIdx.x * wpb + (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const bool dealt = alone || deal_items(reqs, num_reqs, groups, num_groups, 2 * waves, uneven ? 1u << 12 : 1u << 13);
+  const bool dealt = alone || deal_items(reqs, num_reqs, groups, num_groups, 2 * waves, look.uneven ? 1u << 12 : kDealEven);
   uint32_t p0 = wave;
   uint32_t take = 1, round = 0;
   for (;;) {
@@ -1268,7 +1297,7 @@ hipError_t launch_family_generate(uint32_t family, Kind kind, bool fill, const S
 }
 
 // Groups per compute unit up to which there is a wavefront for each (see
-// pairs_uneven; 1500 requests of mixed types and 2^8 to 2^14 words: 81 us in pairs
+// look_at_pairs; 1500 requests of mixed types and 2^8 to 2^14 words: 81 us in pairs
 // and 64, 2000 81 and 72, and more than two wavefronts per SIMD gain nothing).
 constexpr uint64_t kAlone = 8;
 hipError_t launch_family_batch(uint32_t family, const Shape &shape, int num_cus, unsigned char *state,
