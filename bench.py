@@ -495,7 +495,7 @@ def main() -> int:
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--waves-per-block", type=int, default=None)
     ap.add_argument("--unroll", type=int, default=None)
-    ap.add_argument("--store-words", type=int, default=None)
+    ap.add_argument("--store-words", type=int, default=None, help="with --unroll")
     ap.add_argument("--no-extras", action="store_true",
                     help="skip the ragged-batch, fused-moments, family and serving measurements")
     ap.add_argument("--extras", default="ragged,fused,family,serving",
@@ -647,7 +647,8 @@ def main() -> int:
             "rn_per_step": rn_per_step,
             "params": "(r,s,a,b,c,d)=(128,65,15,14,12,17), w=32, omega=0x9E3779B9, gamma=16",
             "launch": {"waves_per_block": wpb or "auto: 4 (one stream per SIMD)",
-                       "unroll": un or "auto: 2 for the stream-major launches", "store_words": sw},
+                       "unroll": un or "auto: 2 for the stream-major launches",
+                       "store_words": sw if un else "auto: 1"},
         },
         "roofline": {
             "bound": "hbm",

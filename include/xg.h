@@ -179,16 +179,33 @@ typedef struct {
 
 /* Launch shape of the plain and fill launches of this handle
  * (waves_per_block, unroll and store_words are used; blocks_per_cu is
- * ignored).  waves_per_block 0 chooses per launch: 4 when count >= 4 x the
- * compute units, else 2 when count >= 2 x, else 1, so one stream's wavefront
- * lands on each SIMD before any SIMD gets a second.  unroll 0 chooses per
- * launch (measured fastest for each): for Section 2's member, when count is
- * at least 4 x the compute units, 4 for the bulk-fill uint32 launch, 8 for
- * the bulk-fill FP32 launch, and 2 with 4-byte stores for the stream-major
- * uint32 and FP32 launches; for XG_FAMILY_R64_W32 (count at least 8 x the
- * compute units: two streams per wavefront) 2 for its stream-major launches;
- * 8 for every other launch.  The default is {0, 0, 1, 4}.  Output bits do not
- * depend on it.
+ * ignored).  Output bits do not depend on it.
+ *   waves_per_block  0 chooses per launch: 4 when the wavefronts (one per stream;
+ *     one per two streams of the r = 64 members) number at least 4 x the compute
+ *     units, else 1, so one wavefront lands on each SIMD before any SIMD gets
+ *     a second; always 1 for XG_FAMILY_R64_W64.
+ *   unroll  0 chooses per launch (measured fastest for each): for Section 2's
+ *     member, when count is at least 4 x the compute units, 4 for the bulk-fill
+ *     uint32 launch, 8 for the bulk-fill FP32 launch, and 2 for the
+ *     stream-major uint32 and FP32 launches; for XG_FAMILY_R64_W32 (count at
+ *     least 8 x the compute units) 2 for its stream-major launches; 8 for every
+ *     other launch.
+ *   store_words  the widest store allowed.  With an explicit unroll it is the
+ *     width of Section 2's stream-major uint32 and FP32 launches.  With unroll
+ *     0 the width is chosen with the unroll, and every launch now stores 4
+ *     bytes per lane whether 1 or 4 is allowed, because the staged 16-byte
+ *     stores are slower at each of those shapes (512 streams x 2^16 uint32:
+ *     43 us, 34 with 4-byte stores).
+ * A shape given here also keeps the launch whole and simple:
+ *   - an explicit waves_per_block or unroll keeps the rows of few streams in one
+ *     piece.  By default they are cut into up to 256 parts that run side by
+ *     side (one stream x 2^20 uint32: 10 us cut, 544 us whole), which rows of 2^28
+ *     values or more (of 2^20 per SIMD, over several streams) are not;
+ *   - an explicit unroll keeps the non-temporal stores of Section 2's
+ *     stream-major launches, where by default long rows that start inside a
+ *     cache line and launches of many streams take cached ones (4096 streams x
+ *     65537 uint32: 199 us cached, 366 non-temporal).
+ * The default is {0, 0, 1, 4}.
  * Errors: XG_EINVAL (NULL pointer or a shape outside the ranges of xg_tune). */
 xg_status xg_set_plain_tune(xg_ctx *ctx, const xg_tune *tune);
 xg_status xg_get_plain_tune(const xg_ctx *ctx, xg_tune *tune);

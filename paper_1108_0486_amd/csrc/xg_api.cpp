@@ -104,9 +104,9 @@ bool paper_member(const xg_ctx *ctx) { return ctx && ctx->family == XG_FAMILY_R1
 // against 789-812 us, three boxes); its fills keep 8.
 // Those were measured with a wavefront on every SIMD; smaller launches (fewer
 // than 4 x CUs wavefronts, e.g. one stream per launch) take unroll 8, as does
-// the 64-bit member.  Every automatic shape stores 4 bytes per lane.  Rows of
-// Section 2's member that take cached stores (cached_stores) have a kernel of their own,
-// unroll 8.
+// the 64-bit member.  Every automatic shape stores 4 bytes per lane, also where
+// store_words allows more.  Rows of Section 2's member that take cached stores
+// (cached_stores) have a kernel of their own, unroll 8.
 xg::Shape plain_shape(const xg_ctx *ctx, uint64_t count, xg::Kind kind, bool fill_layout) {
   xg::Shape s = ctx->plain;
   const uint64_t waves = ctx->family == XG_FAMILY_R128_W32 ? count : (count + 1) / 2;

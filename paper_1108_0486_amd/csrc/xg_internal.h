@@ -23,7 +23,8 @@ struct Shape {
   uint32_t store_words;      // 1 or 4 (4 needs unroll >= 4)
 };
 
-constexpr Shape kDefaultPlain{0, 0, 1, 4};  // waves_per_block and unroll chosen per launch
+// waves_per_block, unroll and, within the width allowed, store_words chosen per launch
+constexpr Shape kDefaultPlain{0, 0, 1, 4};
 
 // Waves per block for a plain launch of `count` streams on `num_cus` compute
 // units: four once that gives every compute unit a block, else one, so that
