@@ -12,8 +12,8 @@
 // sqrt and sincospi took about 390.  VALU issue bounds the kernel: 2048 streams
 // x 2^17 normals went from 1389 us to 590 us (1.55 to 3.6 TB/s).  Against a
 // 113-bit reference over 2^18 normals the results are nearer than the
-// library's functions gave: at most 1.93 ulp off (before 2.33), 6.7e-17 in
-// the mean (before 8.1e-17).
+// library's functions gave: at most 1.93 ulp off (before 2.33), a root mean
+// square relative error of 6.7e-17 (before 8.1e-17).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -72,6 +72,8 @@ __device__ __forceinline__ void horner(const double (&c)[N], const double (&x)[P
   }
 }
 
+// The reduction and the form of the sum are those of the published logarithm of
+// Sun's fdlibm (e_log.c); the polynomial and the quotient are this file's own.
 // ln u1 = k ln 2 + ln m with m = u1 2^-k in [0.7071, 1.4142) (the exponent is
 // taken after adding 1 - 0.7071 to u1's high word, so that u1 just below 1 has
 // k = 0 and f = m - 1 is exact).  With s = f / (2 + f), ln m = 2 s + s z Q(z),

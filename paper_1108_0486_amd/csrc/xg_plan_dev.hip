@@ -15,9 +15,10 @@
 // most of it not work), so each step does all it can before it needs the whole
 // table again: a sort is one launch over blocks of 1024 keys and one for each
 // eightfold merge, and the producer of a prefix sum's input leaves its block sums.
-// Plan and batch of short requests, ten launches of the plan now and 32 before
-// (16384 requests): 4100 requests 126 -> 65 us, 16384 199 -> 126, 65536 281 ->
-// 173, 900000 1130 -> 952.
+// Without tiles a plan takes 10 launches up to 16384 requests, 12 at 65536 and 16 at
+// a million (two more with tiles); it took 28 at 8192, 32 at 16384, 44 at 65536 and 74.
+// Plan and batch of short requests: 4100 requests 126 -> 65 us, 16384 199 -> 126,
+// 65536 281 -> 173, 900000 1130 -> 952.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 

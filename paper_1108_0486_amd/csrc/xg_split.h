@@ -71,7 +71,11 @@ constexpr SplitCost kSplitCost[3][2] = {
 // streams for the r = 64 members) with n values per stream on `cus` compute
 // units: those of the least time by the costs above, with at most one
 // wavefront per SIMD; none where that saves less than a fifth, or where more
-// than half of the SIMDs have a wavefront as it is.
+// than half of the SIMDs have a wavefront as it is.  Nor are rows cut that are too
+// long for the stored distances: 256 parts of 2^20 values (and the 255 more
+// that a last part may have), or 2^20 for each SIMD where several wavefronts
+// share them.  One value more and such a row runs whole, as every row
+// did before: one stream x 2^28 words takes some 0.6 ms in parts and 130 whole.
 inline Split plan_split(uint64_t waves, uint64_t n, uint64_t cus, const SplitCost &c) {
   Split s;
   const uint64_t slots = 4 * cus;

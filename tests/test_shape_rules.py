@@ -9,6 +9,8 @@ import pytest
 from paper_1108_0486_amd import build as B
 from paper_1108_0486_amd import xg
 
+from split_cases import EXPONENTS, LONGEST
+
 HERE = os.path.dirname(os.path.abspath(__file__))
 U32, F32, NORMAL, MOMENTS, U64, F64 = xg.XG_U32, xg.XG_F32, xg.XG_NORMAL, 3, 4, 5
 
@@ -61,3 +63,16 @@ STORES = [
 def test_stores(rules):
     got = rules(*[("stores", *c[:5]) for c in STORES])
     assert [(c, g) for c, (g,) in zip(STORES, got) if g != c[5]] == []
+
+
+@pytest.mark.parametrize("family,kind", [(0, U32), (0, NORMAL), (1, U32), (1, NORMAL), (2, U64), (2, NORMAL)])
+def test_parts_of_every_exponent(rules, family, kind):
+    got = rules(*[("split", family, kind, 1, n) for n in EXPONENTS.values()])
+    assert got == [(129, e) for e in EXPONENTS]
+
+
+@pytest.mark.parametrize("family,kind", [(0, U32), (0, NORMAL), (1, U32), (1, NORMAL), (2, U64), (2, NORMAL)])
+def test_longest_rows_that_are_cut(rules, family, kind):
+    per = 1 if family == 0 else 2
+    got = rules(*[("split", family, kind, per * waves, n) for waves, n, _, _ in LONGEST])
+    assert got == [(parts, e) for _, _, parts, e in LONGEST]
