@@ -22,6 +22,7 @@ import argparse
 import hashlib
 import json
 import os
+import re
 import sys
 import time
 
@@ -40,11 +41,26 @@ VALU_FILE = os.path.join(ROOT, "profiles", "valu_fused_moments.json")
 # lanes per cycle, 39.3e12 lane operations/s), per 2 cycles for FP32 add /
 # mul / FMA (the published 157.3 TFLOP/s) and per 8 cycles for transcendentals.
 SIMD_CYCLES_PER_S = 256 * 4 * 2.4e9
-# The bulk and normal kernels' source: the kernel file and the headers it
-# includes.  The committed counter records are used only while it matches.
-KERNEL_SOURCES = [os.path.join(ROOT, "paper_1108_0486_amd", "csrc", f)
-                  for f in ("xg_kernels.hip", "xg_device.h", "xg_normal.h", "xg_internal.h", "xg_host.h",
-                            "xg_jump_mm.h")]
+CSRC = os.path.join(ROOT, "paper_1108_0486_amd", "csrc")
+
+
+def kernel_sources() -> list:
+    """The source of the bulk and normal kernels and of the rules that pick one:
+    the kernel file, the C ABI's, and every header of the folder they include."""
+    todo, seen = ["xg_kernels.hip", "xg_api.cpp"], set()
+    while todo:
+        name = todo.pop()
+        path = os.path.join(CSRC, name)
+        if name in seen or not os.path.exists(path):
+            continue
+        seen.add(name)
+        with open(path) as f:
+            todo += re.findall(r'^#include "([^"]+)"', f.read(), re.M)
+    return [os.path.join(CSRC, name) for name in sorted(seen)]
+
+
+# The committed counter records are used only while this source matches.
+KERNEL_SOURCES = kernel_sources()
 
 
 def kernel_source_hash() -> str:

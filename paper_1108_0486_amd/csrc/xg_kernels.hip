@@ -388,7 +388,8 @@ __device__ __forceinline__ void serve_words_fill(uint32_t *__restrict__ st, uint
 //    for launches with more than one wavefront per SIMD, where the VALU is the
 //    bound and the LDS latency hides: 4096 x 2^18 normals 825 us and moments
 //    722 (870 and 738 with one block at a time by four ds_bpermute and two
-//    selects, which gather_pair does for what the unrolled loop leaves over).
+//    selects, which gather_pair does for what the unrolled loop leaves over; on
+//    a slower box normals 863 and 906).
 //  - DPP (an even lane j takes words j and j + 1, an odd lane j words 63 + j
 //    and 64 + j): each lane needs one word of its neighbour in the same chunk,
 //    which a quad permutation (lanes 2i and 2i + 1 swap) supplies in the VALU,
