@@ -32,6 +32,7 @@
 #include "xg_internal.h"
 #include "xg_launch.h"
 #include "xg_fam_batch.h"
+#include "xg_pairs.h"
 
 namespace xg {
 namespace {
@@ -654,30 +655,32 @@ __device__ __forceinline__ uint64_t lane_value(uint64_t v, int src) {
 
 // How evenly pairs of groups run, by up to 32 of them spread over the table and
 // each group's first request.  The halves of a wavefront part where either's
-// request ends, and run one type at a time.
-//  - apart: pairs of different lengths or types.  A wavefront for each group is
-//    then faster, where there are enough (plan and batch of 384 requests of mixed types and
-//    2^8 to 2^14 words on 200 streams: 97 us in pairs and 60, 64 bits 167 and 95;
-//    1000 single uint32 requests of 2^6 to 2^12 words 29.3 and 27.9), but slower where
-//    pairs step together (two uint32 requests of 2^16 on each of 2000 streams, lone groups
-//    being two wavefronts to a SIMD: 273 and 330; normals 335 and 500, FP64
-//    normals 652 and 1072).
+// request ends, which costs a trip of the loop, and run one type at a time.
+//  - apart: a wavefront for each group is faster, where there are enough: pairs
+//    of two types take each other's time (384 requests of mixed types and 2^8 to 2^14
+//    words on 200 streams, plan and batch in us, pairs and alone: 97 and 60, 64 bits
+//    167 and 95), and pairs of two lengths more trips (lone_groups_pay).
 //  - uneven: pairs of different types, or of several requests of different
 //    lengths, whose times differ more than their costs.
-// Either wants a quarter of the pairs, or one of two types long enough to end last.
+// Types and lengths count where a quarter of the pairs differ, or where one pair
+// of two types is long enough to end last.
 struct PairLook {
   bool apart, uneven;
 };
 __device__ __forceinline__ uint32_t other_half(uint32_t v) { return dev::lane_xor<1>(v); }
 __device__ __forceinline__ float other_half(float v) { return __uint_as_float(dev::lane_xor<1>(__float_as_uint(v))); }
+__device__ __forceinline__ uint32_t of_lane0(uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); }
+__device__ __forceinline__ float of_lane0(float v) { return __uint_as_float(of_lane0(__float_as_uint(v))); }
+
+template <class M>
 __device__ __forceinline__ PairLook look_at_pairs(const xg_request *__restrict__ reqs, uint32_t num_reqs,
                                                   const uint32_t *__restrict__ groups, uint32_t num_groups,
-                                                  const Lanes &L) {
-  uint32_t type = 0, count = 0;
+                                                  uint32_t simds, const Lanes &L) {
+  uint32_t type = 0, count = 0, first = 0;
   float n = 0.0f;  // of the first request
   if (num_groups) {
     const uint32_t pairs = (uint32_t)((num_groups + 1ull) / 2);
-    const uint32_t first = 2u * (uint32_t)((uint64_t)L.j * pairs / 32u);  // of the pair this lane and the next look at
+    first = 2u * (uint32_t)((uint64_t)L.j * pairs / 32u);  // of the pair this lane and the next look at
     const uint32_t g = first + L.h < num_groups ? first + L.h : first;
     const uint32_t r = groups[g], end = groups[g + 1];
     if (r < end && r < num_reqs) {
@@ -686,16 +689,29 @@ __device__ __forceinline__ PairLook look_at_pairs(const xg_request *__restrict__
       count = end - r;
     }
   }
-  const float time = n * (float)count * (type == XG_NORMAL ? 2.0f : 1.0f);  // of the group, in words
-  // Lane 0 has the first group, and groups fall in cost.
-  const float largest = __uint_as_float((uint32_t)__builtin_amdgcn_readfirstlane((int)__float_as_uint(time)));
-  const float both = time + other_half(time);
-  const uint32_t counts = count + other_half(count);
-  const bool types = other_half(type) != type, lengths = other_half(n) != n;
-  const bool last = __any(types && both > 1.25f * largest) != 0;
   constexpr int kQuarter = 16;  // lanes, two to a pair
-  return {last || __popcll(__ballot(types || lengths)) >= kQuarter,
-          last || __popcll(__ballot(types || (counts > 2u && lengths))) >= kQuarter};
+  const float words = n * (float)count, time = type == XG_NORMAL ? 2.0f * words : words;  // of the group
+  const float both = time + other_half(time);
+  const uint32_t counts = count + other_half(count), more = count > counts - count ? count : counts - count;
+  const bool types = other_half(type) != type, lengths = other_half(n) != n;
+  // Lane 0 has the first group, and groups fall in cost.
+  const bool last = __any(types && both > 1.25f * of_lane0(time)) != 0;
+  const bool by_type = last || __popcll(__ballot(types)) >= kQuarter;
+  // The groups around the first that share a SIMD with others.
+  float second = 0.0f;
+  if (num_groups > simds) {
+    const uint32_t around = num_groups / 8u;
+    const bool here = first + around >= simds && first <= simds + around;
+    const int seen = __popcll(__ballot(here));
+    second = here ? words : 0.0f;
+#pragma unroll
+    for (int d = 32; d; d >>= 1) second += __shfl_xor(second, d);
+    second = seen ? of_lane0(second) / (float)seen : 0.0f;
+  }
+  const bool ends = __popcll(__ballot(types || lengths)) >= kQuarter &&
+                    lone_groups_pay(sizeof(typename M::word) == 8, of_lane0(type) == XG_NORMAL, of_lane0(more),
+                                    of_lane0(words), second);
+  return {by_type || ends, last || __popcll(__ballot(types || (counts > 2u && lengths))) >= kQuarter};
 }
 
 template <class M, int UNROLL>
@@ -703,7 +719,7 @@ __global__ __launch_bounds__(1024) void k_fam_batch(unsigned char *__restrict__ 
                                                     const xg_request *__restrict__ reqs,
                                                     const uint32_t *__restrict__ groups,
                                                     void *__restrict__ out_v, uint64_t out_elems,
-                                                    uint32_t *__restrict__ work) {
+                                                    uint32_t *__restrict__ work, uint32_t simds) {
   const uint32_t num_groups = work[2], num_reqs = work[3];
   using word = typename M::word;
   constexpr uint32_t kInt = sizeof(word) == 4 ? kU32 : kU64;
@@ -727,7 +743,7 @@ __global__ __launch_bounds__(1024) void k_fam_batch(unsigned char *__restrict__ 
   constexpr uint32_t kDealEven = (1u << 16) / sizeof(word);
   const uint32_t wpb = blockDim.x >> 6;
   const uint32_t waves = gridDim.x * wpb;
-  const PairLook look = look_at_pairs(reqs, num_reqs, groups, num_groups, L);
+  const PairLook look = look_at_pairs<M>(reqs, num_reqs, groups, num_groups, simds, L);
   const bool alone = num_groups <= waves && look.apart;
   const uint32_t num_pairs = alone ? num_groups : (uint32_t)((num_groups + 1ull) / 2);
   const uint32_t wave = blockIdx.x * wpb + (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -850,7 +866,7 @@ hipError_t launch_fam_batch_k(uint32_t unroll, uint64_t blocks, dim3 block, int 
                               uint64_t out_elems, uint32_t *work, hipStream_t stream) {
   auto run = [&](auto kernel) {
     return launch_persistent(kernel, blocks, block, 0, num_cus, stream, state, num_streams, reqs, groups, out,
-                             out_elems, work);
+                             out_elems, work, 4u * (uint32_t)(num_cus > 0 ? num_cus : 1));
   };
   switch (unroll) {
     case 1: return run(k_fam_batch<M, 1>);
